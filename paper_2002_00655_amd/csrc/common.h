@@ -54,6 +54,18 @@ struct MfData {
     float *trun_val = nullptr;        // read brings everything a row with a single entry needs
     int32_t *trun_col = nullptr;
     int64_t *blk_trun_ptr = nullptr;  // num_blocks + 1, index into row runs
+    // The second part once more, as a schedule by levels (sched_ok; see k_tail_levels): every block's row runs are cut
+    // into chunks whose factors fit in LDS beside the block's non-heavy columns; the entries of a chunk are ordered by
+    // level, and the entries of a level share neither a row nor a column.
+    bool sched_ok = false;
+    int64_t num_chunks = 0, num_levels = 0;
+    int64_t *blk_chunk_ptr = nullptr; // num_blocks + 1, index into chunks
+    uint32_t *ch_trun = nullptr;      // num_chunks + 1: first row run of a chunk
+    uint32_t *ch_lv = nullptr;        // num_chunks + 1: first level of a chunk
+    uint32_t *lv_start = nullptr;     // num_levels + 1: first entry of a level
+    uint32_t *blk_meta = nullptr;     // num_blocks: words of LDS for the block's records, row and column numbers; 0: they do not fit
+    uint2 *s_rec = nullptr;           // num_tail: where the row's and the column's factor lie in LDS (in floats, 16 bits
+                                      // each: row low, column high), and the value
     // where the groups of the heavy runs start: run r has run_gptr[r+1] - run_gptr[r] - 1 groups (none if it is not
     // heavy); gstart[run_gptr[r] + g] is the start of group g relative to the run's first entry, one more entry = length
     int64_t *run_gptr = nullptr;      // num_runs + 1
@@ -121,8 +133,20 @@ struct dpaps_ps {
     std::string last_error;
 };
 
+// LDS that a workgroup of the SGD kernels can plan with (the rest: static variables and slack).
+#define DPAPS_LDS_SLACK 1024
+// Distance (floats) of the factor rows that the second part by levels keeps in LDS: they start on 16 bytes.
+#define DPAPS_LDS_STRIDE(L) (((L) + 3) & ~3)
+#define DPAPS_SCHED_BASE 8            // floats in front of them
 // Heavy runs of a block at most.
 #define DPAPS_HEAVY_MAX 8
+// Most wavefronts that take heavy runs.
+#define DPAPS_HEAVY_WAVES 14
+// LDS (bytes) of the grouped kernel's first part: staging areas, tables, the heavy columns' factors and counters
+// (NT: tiles of 16 components of a factor).
+__host__ __device__ inline int64_t dpaps_heavy_lds(int NT, int heavy_waves) {
+    return ((int64_t)heavy_waves * 16 * (16 * NT + 4) + 60 + DPAPS_HEAVY_MAX * 16 * NT + DPAPS_HEAVY_MAX) * 4;
+}
 // Column blocks at most in an epoch with hand-over (one bit each in LDS).
 #define DPAPS_HANDOFF_MAX_COLS 4096
 
@@ -144,6 +168,8 @@ struct SgdArgs {
     const uint32_t *trun_start; const int32_t *trun_row; const uint32_t *trun_wait;
     const uint32_t *trun_ci; const float *trun_val; const int32_t *trun_col;
     const uint32_t *t_cinfo; const float *t_val;
+    const int64_t *blk_chunk_ptr; const uint32_t *ch_trun, *ch_lv, *lv_start, *blk_meta; const uint2 *s_rec;
+    uint32_t lds_words;         // dynamic LDS of the launch
     const int64_t *run_gptr; const int32_t *gstart;
     int32_t heavy_waves;        // wavefronts that take heavy runs (each has a staging area in LDS)
     int32_t team;               // 2: the heavy wavefronts follow team_plan; 1: one wavefront per heavy run, in turn

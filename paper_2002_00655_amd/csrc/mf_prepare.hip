@@ -173,7 +173,7 @@ void dpaps_mf_free(dpaps_ps *ps) {
     MfData &f = ps->mf;
     void *ptrs[] = {f.row, f.val, f.info, f.col, f.run_start, f.run_col, f.blk_run_ptr, f.multi_row, f.blk_multi_ptr,
                     f.row_bounds, f.col_bounds, f.blk_nheavy, f.t_cinfo, f.t_val, f.trun_start, f.trun_row, f.trun_wait, f.trun_ci, f.trun_val, f.trun_col,
-                    f.blk_trun_ptr, f.run_gptr, f.gstart, f.team_plan};
+                    f.blk_trun_ptr, f.blk_chunk_ptr, f.ch_trun, f.ch_lv, f.lv_start, f.s_rec, f.blk_meta, f.run_gptr, f.gstart, f.team_plan};
     for (void *p : ptrs) if (p) (void)hipFree(p);
     ps->mf = MfData();
 }
@@ -352,7 +352,7 @@ __global__ void k_tail_fill(const uint32_t *spos, const uint32_t *tq, const uint
                             const int32_t *nheavy, const int64_t *run_start, const int32_t *rows, const float *vals,
                             int64_t nnz, uint32_t *t_cinfo, float *t_val, uint32_t *trun_start, int32_t *trun_row,
                             uint32_t *trun_wait, const int32_t *run_col, uint32_t *trun_ci, float *trun_val, int32_t *trun_col,
-                            int32_t *err) {
+                            uint32_t *pos_run /* per stored position: its row run */, uint32_t *trun_blk, int32_t *err) {
     int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= nnz || !tq[q]) return;
     uint32_t p = spos[q], t = tpos[q], g = runidx[p], b = blk[p];
@@ -362,6 +362,7 @@ __global__ void k_tail_fill(const uint32_t *spos, const uint32_t *tq, const uint
     const uint32_t last = (int64_t)p + 1 == run_start[g + 1] ? 0x80000000u : 0u;      // the column's last entry in this block
     t_cinfo[t] = (uint32_t)cslot | ((uint32_t)cseq << 16) | last;
     t_val[t] = vals[p];
+    pos_run[p] = tri[q] + thead[q] - 1u;                    // (tri: row runs that start before this position)
     if (thead[q]) {
         uint32_t j = tri[q], s = seg_idx[q];
         trun_ci[j] = (uint32_t)cslot | ((uint32_t)cseq << 16) | last;
@@ -369,6 +370,7 @@ __global__ void k_tail_fill(const uint32_t *spos, const uint32_t *tq, const uint
         trun_col[j] = run_col[g];
         uint32_t before = (uint32_t)q - seg_start[s];       // the row's entries in heavy runs
         trun_start[j] = t;
+        trun_blk[j] = b;
         trun_row[j] = rows[p];
         trun_wait[j] = (before > 0 && is_multi[s]) ? (seg_slot[s] | (before << 16)) : 0xFFFFFFFFu;
     }
@@ -413,6 +415,210 @@ __global__ void k_widen_u32(const uint32_t *src, int64_t n, int64_t last, int64_
     if (i < n) dst[i] = src[i]; else if (i == n) dst[i] = last;
 }
 
+// ---- the second part as a schedule by levels ------------------------------------------------------------------
+// An entry's step needs the steps of the row's and of the column's entries before it.  level = 0 for an entry without
+// such predecessors, else one more than the larger of theirs: the entries of a level share neither a row nor a column
+// and can take their steps at the same time, and the levels in turn keep every row's and every column's stored
+// order.  (The usual levels of a sparse triangular solve.)  So that the factors a step needs are in LDS, the row runs of
+// a block are cut, in order, into chunks whose rows and entries fit there beside the block's non-heavy columns; a
+// chunk is worked off before the next, which keeps the order too - a column's entries ascend by row -, and levels
+// count inside a chunk.
+//
+// A block's records and numbers go to the end of LDS for the whole block where there is room (at most `meta_cap`
+// bytes: what the first part leaves, and a quarter); else a chunk's records come with the chunk.  A row run costs its
+// factor (and in the second case its records); a chunk holds the runs whose costs so far fall into the same stretch of
+// `room`, so its own cost is at most room and one run.
+__global__ void k_blk_meta(const int64_t *blk_trun_ptr, const uint32_t *trun_start, const int64_t *blk_run_ptr, const int32_t *nheavy, int64_t nb,
+                           int64_t meta_cap, uint32_t *blk_meta) {
+    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (b >= nb) return;
+    const int64_t j0 = blk_trun_ptr[b], j1 = blk_trun_ptr[b + 1], cols = blk_run_ptr[b + 1] - blk_run_ptr[b] - nheavy[b];
+    const int64_t words = (2 * (int64_t)(trun_start[j1] - trun_start[j0]) + (j1 - j0) + cols + 1) & ~(int64_t)1;   // (records on 8 bytes)
+    blk_meta[b] = words * 4 <= meta_cap ? (uint32_t)words : 0u;
+}
+__device__ __forceinline__ uint32_t chunk_of(int64_t run, int64_t run0, const uint32_t *trun_start, int32_t LS, int64_t rec_bytes, int64_t room) {
+    return (uint32_t)(((run - run0) * (4 * (int64_t)LS) + (int64_t)(trun_start[run] - trun_start[run0]) * rec_bytes) / room);
+}
+__global__ void k_chunk_heads(const uint32_t *trun_blk, const int64_t *blk_trun_ptr, const uint32_t *trun_start, const int64_t *blk_run_ptr,
+                              const int32_t *nheavy, const uint32_t *blk_meta, int64_t ntr, int32_t LS, int64_t budget, uint32_t *chunk, uint32_t *head) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j >= ntr) return;
+    const uint32_t b = trun_blk[j];
+    const int64_t j0 = blk_trun_ptr[b], cols = blk_run_ptr[b + 1] - blk_run_ptr[b] - nheavy[b], meta = 4 * (int64_t)blk_meta[b];
+    const int64_t room = budget - cols * 4 * LS - meta, rec = meta ? 0 : 8;
+    chunk[j] = chunk_of(j, j0, trun_start, LS, rec, room);
+    head[j] = j == j0 || chunk[j] != chunk_of(j - 1, j0, trun_start, LS, rec, room) ? 1u : 0u;
+}
+
+__global__ void k_chunk_fill(const uint32_t *head, const uint32_t *incl, int64_t ntr, uint32_t *ch_trun) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < ntr && head[j]) ch_trun[incl[j] - 1u] = (uint32_t)j;
+}
+
+// chunks before block b: those of the row runs before its first (incl: chunks up to and including a row run's)
+__global__ void k_blk_chunks(const int64_t *blk_trun_ptr, int64_t nb, const uint32_t *incl, int64_t *blk_chunk_ptr) {
+    const int64_t b = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (b <= nb) blk_chunk_ptr[b] = blk_trun_ptr[b] > 0 ? (int64_t)incl[blk_trun_ptr[b] - 1] : 0;
+}
+
+__global__ void k_run_lengths(const uint32_t *trun_start, int64_t ntr, uint32_t *len) {
+    const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (j < ntr) len[j] = trun_start[j + 1] - trun_start[j];
+}
+
+// One wavefront per block walks the block's non-heavy column runs in stored order, 64 entries of a column at a time.
+// With r_k the level count of entry k's row so far (its entries in earlier columns), the column's recursion
+// c_k = 1 + max(r_k, c_(k-1)) is c_k = 1 + k + max over i <= k of (r_i - i): a running maximum.  A chunk starts afresh:
+// chunk numbers ascend along a column, so they are put in front of the compared number.  rowlev: one count per row
+// run, zero at first, read and written past the die's first cache, which the wavefront's own atomics pass by.
+__global__ __launch_bounds__(256) void k_tail_levels(const int64_t *blk_run_ptr, const int32_t *nheavy, const int64_t *run_start, int64_t nb,
+                                                     const uint32_t *pos_run, const uint32_t *chunk, uint32_t *rowlev, uint32_t *level) {
+    const int lane = threadIdx.x & 63;
+    const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (b >= nb) return;
+    const int64_t g0 = blk_run_ptr[b] + nheavy[b], g1 = blk_run_ptr[b + 1];
+    for (int64_t g = g0; g < g1; ++g) {
+        const int64_t p0 = run_start[g], p1 = run_start[g + 1];
+        int64_t carry = 0;                                             // chunk << 32 | level count of the column's entry before
+        for (int64_t base = p0; base < p1; base += 64) {
+            const bool in = base + lane < p1;
+            const uint32_t run = in ? pos_run[base + lane] : 0u;
+            const int64_t ch = in ? (int64_t)chunk[run] << 32 : 0;
+            const uint32_t r = in ? __hip_atomic_load(&rowlev[run], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+            // (64 is added so that the low half stays positive)
+            int64_t x = in ? ch + 64 + (int64_t)r - lane : 0;
+            if (lane == 0) x = max(x, carry + 64);
+            for (int off = 1; off < 64; off <<= 1) {
+                const int64_t y = __shfl_up(x, off);
+                if (lane >= off) x = max(x, y);
+            }
+            const int64_t count = (x - ch) - 64 + 1 + lane;            // c_k, a small number
+            if (in) {
+                level[base + lane] = (uint32_t)count - 1u;
+                atomicMax(&rowlev[run], (uint32_t)count);
+            }
+            const int last = (int)(p1 - base < 64 ? p1 - base : 64) - 1;
+            carry = __shfl(ch + count, last);
+            __builtin_amdgcn_s_waitcnt(0);                             // the counts have arrived before the next column looks at them
+            __asm__ volatile("" ::: "memory");
+        }
+    }
+}
+
+// the sort key (chunk, level) and the record of every entry of the second part
+__global__ void k_sched_keys(const uint32_t *spos, const uint32_t *tq, const uint32_t *tpos, const uint32_t *pos_run, const uint32_t *chunk_incl,
+                             const uint32_t *ch_trun, const uint32_t *level, const uint32_t *trun_blk, const int64_t *blk_run_ptr,
+                             const int32_t *nheavy, const uint32_t *t_cinfo, const float *t_val, int64_t nnz, int32_t LS, uint64_t *key, uint2 *rec) {
+    const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (q >= nnz || !tq[q]) return;
+    const uint32_t t = tpos[q], p = spos[q], run = pos_run[p], c = chunk_incl[run] - 1u, b = trun_blk[run];
+    const uint32_t cols = (uint32_t)(blk_run_ptr[b + 1] - blk_run_ptr[b]) - (uint32_t)nheavy[b];
+    key[t] = ((uint64_t)c << 16) | level[p];
+    const uint32_t at_row = DPAPS_SCHED_BASE + (cols + (run - ch_trun[c])) * (uint32_t)LS, at_col = DPAPS_SCHED_BASE + (t_cinfo[t] & 0xFFFFu) * (uint32_t)LS;
+    rec[t] = make_uint2(at_row | at_col << 16, __float_as_uint(t_val[t]));
+}
+
+__global__ void k_level_heads(const uint64_t *key, int64_t n, uint32_t *head) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t < n) head[t] = t == 0 || key[t] != key[t - 1] ? 1u : 0u;
+}
+
+__global__ void k_level_fill(const uint64_t *key, const uint32_t *head, const uint32_t *incl, int64_t n, uint32_t *lv_start, uint32_t *ch_lv) {
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (t >= n || !head[t]) return;
+    lv_start[incl[t] - 1u] = (uint32_t)t;
+    if (t == 0 || (key[t] >> 16) != (key[t - 1] >> 16)) ch_lv[key[t] >> 16] = incl[t] - 1u;
+}
+
+// Builds that schedule where the data allows it.  Needs what mf_load_ratings has by then: the entries in (block, row)
+// order (spos; tq: of the second part, tpos: their number there), the row run of every stored position (pos_run) and
+// the block of every row run (trun_blk).  Sets f.sched_ok; data that does not fit is left to the other variant.
+static int build_schedule(dpaps_ps *ps, const uint32_t *spos, const uint32_t *tq, const uint32_t *tpos, const uint32_t *pos_run,
+                          const uint32_t *trun_blk, hipStream_t st) {
+    MfData &f = ps->mf;
+    const int64_t nt = f.num_tail, ntr = f.num_truns, nb = f.num_blocks, nnz = f.nnz;
+    const int32_t L = ps->L;
+    const int64_t budget = (int64_t)ps->lds_bytes - DPAPS_LDS_SLACK - 4 * DPAPS_SCHED_BASE;
+    // Half of LDS for the columns at most: with less room for rows the chunks get so short that filling LDS anew for
+    // each costs more than the steps (and LDS offsets must fit in 16 bits).
+    const int32_t LS = DPAPS_LDS_STRIDE(L);
+    if (nt == 0 || !f.sweep_ok || L > 128 || (int64_t)f.max_tail_cols * LS * 4 > budget / 2 || budget / 4 + DPAPS_SCHED_BASE >= 65536) return PS_OK;
+    const int64_t meta_cap = std::min(budget - dpaps_heavy_lds((L + 15) / 16, DPAPS_HEAVY_WAVES) - 4 * (int64_t)std::max(f.max_multi_in_block, 1), budget / 4);
+    int rc = PS_OK;
+    char *dev = nullptr;
+    Arena a;
+    size_t tmp_sort = 0, tmp_scan = 0;
+    uint32_t *chunk = nullptr, *head = nullptr, *incl = nullptr, *rowlev = nullptr, *level = nullptr, *d_max = nullptr;
+    uint64_t *key_a = nullptr, *key_b = nullptr;
+    uint2 *rec = nullptr;
+    char *tmp = nullptr;
+    uint32_t h_max = 0, h_chunks = 0, h_levels = 0;
+    int64_t longest = 0;
+    int key_bits = 17;
+    for (int pass = 0; pass < 2; ++pass) {   // pass 0 measures, pass 1 hands out
+        a.used = 0;
+        chunk = a.take<uint32_t>(ntr); head = a.take<uint32_t>(nt); incl = a.take<uint32_t>(nt); rowlev = a.take<uint32_t>(ntr);
+        level = a.take<uint32_t>(nnz); d_max = a.take<uint32_t>(1);
+        key_a = a.take<uint64_t>(nt); key_b = a.take<uint64_t>(nt); rec = a.take<uint2>(nt);
+        if (pass == 0) {
+            HIPRC(rocprim::radix_sort_pairs(nullptr, tmp_sort, key_a, key_b, (uint64_t *)rec, (uint64_t *)rec, (size_t)nt, 0, 64, st));
+            HIPRC(rocprim::inclusive_scan(nullptr, tmp_scan, head, incl, (size_t)nt, rocprim::plus<uint32_t>(), st));
+        }
+        tmp = a.take<char>(std::max(tmp_sort, tmp_scan) + 256);
+        if (pass == 0) {
+            HIPRC(hipMalloc(&dev, a.used + 256));
+            a.base = dev;
+        }
+    }
+    HIPRC(hipMemsetAsync(d_max, 0, sizeof(uint32_t), st));
+    HIPRC(hipMemsetAsync(rowlev, 0, ntr * sizeof(uint32_t), st));
+    k_run_lengths<<<grid_for(ntr, 256), 256, 0, st>>>(f.trun_start, ntr, head);
+    k_max_u32<<<grid_for(ntr, 256), 256, 0, st>>>(head, ntr, d_max);
+    HIPRC(hipGetLastError());
+    HIPRC(hipMemcpyAsync(&h_max, d_max, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HIPRC(hipStreamSynchronize(st));
+    longest = 4 * (int64_t)LS + 8 * (int64_t)h_max;              // the most that one row run costs
+    if (longest > budget / 8) goto done;
+    HIPRC(hipMalloc(&f.blk_meta, nb * sizeof(uint32_t)));
+    k_blk_meta<<<grid_for(nb, 256), 256, 0, st>>>(f.blk_trun_ptr, f.trun_start, f.blk_run_ptr, f.blk_nheavy, nb, meta_cap, f.blk_meta);
+    k_chunk_heads<<<grid_for(ntr, 256), 256, 0, st>>>(trun_blk, f.blk_trun_ptr, f.trun_start, f.blk_run_ptr, f.blk_nheavy, f.blk_meta, ntr, LS, budget - longest, chunk, head);
+    HIPRC(rocprim::inclusive_scan(tmp, tmp_scan, head, incl, (size_t)ntr, rocprim::plus<uint32_t>(), st));
+    HIPRC(hipMemcpyAsync(&h_chunks, incl + (ntr - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HIPRC(hipStreamSynchronize(st));
+    f.num_chunks = h_chunks;
+    HIPRC(hipMalloc(&f.blk_chunk_ptr, (nb + 1) * sizeof(int64_t)));
+    HIPRC(hipMalloc(&f.ch_trun, (f.num_chunks + 1) * sizeof(uint32_t)));
+    HIPRC(hipMalloc(&f.ch_lv, (f.num_chunks + 1) * sizeof(uint32_t)));
+    HIPRC(hipMalloc(&f.s_rec, nt * sizeof(uint2)));
+    k_chunk_fill<<<grid_for(ntr, 256), 256, 0, st>>>(head, incl, ntr, f.ch_trun);
+    k_blk_chunks<<<grid_for(nb + 1, 256), 256, 0, st>>>(f.blk_trun_ptr, nb, incl, f.blk_chunk_ptr);
+    k_tail_levels<<<grid_for(nb, 4), 256, 0, st>>>(f.blk_run_ptr, f.blk_nheavy, f.run_start, nb, pos_run, chunk, rowlev, level);
+    k_sched_keys<<<grid_for(nnz, 256), 256, 0, st>>>(spos, tq, tpos, pos_run, incl, f.ch_trun, level, trun_blk, f.blk_run_ptr, f.blk_nheavy, f.t_cinfo,
+                                                     f.t_val, nnz, LS, key_a, rec);
+    HIPRC(hipGetLastError());
+    while (key_bits < 64 && ((int64_t)1 << (key_bits - 16)) < f.num_chunks) ++key_bits;
+    HIPRC(rocprim::radix_sort_pairs(tmp, tmp_sort, key_a, key_b, (uint64_t *)rec, (uint64_t *)f.s_rec, (size_t)nt, 0, key_bits, st));
+    k_level_heads<<<grid_for(nt, 256), 256, 0, st>>>(key_b, nt, head);
+    HIPRC(rocprim::inclusive_scan(tmp, tmp_scan, head, incl, (size_t)nt, rocprim::plus<uint32_t>(), st));
+    HIPRC(hipMemcpyAsync(&h_levels, incl + (nt - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HIPRC(hipStreamSynchronize(st));
+    f.num_levels = h_levels;
+    HIPRC(hipMalloc(&f.lv_start, (f.num_levels + 1) * sizeof(uint32_t)));
+    k_level_fill<<<grid_for(nt, 256), 256, 0, st>>>(key_b, head, incl, nt, f.lv_start, f.ch_lv);
+    HIPRC(hipGetLastError());
+    {
+        const uint32_t ends[3] = {(uint32_t)ntr, h_levels, (uint32_t)nt};
+        HIPRC(hipMemcpyAsync(f.ch_trun + f.num_chunks, &ends[0], sizeof(uint32_t), hipMemcpyHostToDevice, st));
+        HIPRC(hipMemcpyAsync(f.ch_lv + f.num_chunks, &ends[1], sizeof(uint32_t), hipMemcpyHostToDevice, st));
+        HIPRC(hipMemcpyAsync(f.lv_start + f.num_levels, &ends[2], sizeof(uint32_t), hipMemcpyHostToDevice, st));
+        HIPRC(hipStreamSynchronize(st));
+    }
+    f.sched_ok = true;
+done:
+    if (dev) (void)hipFree(dev);
+    return rc;
+}
+
 extern "C" int mf_load_ratings(ps_handle ps, int64_t m, int64_t n, int64_t nnz, const int32_t *rows, const int32_t *cols,
                                const float *vals, int32_t d_row, int32_t d_col, const int64_t *row_bounds_host,
                                const int64_t *col_bounds_host, const int64_t *block_ptr_host, void *stream) {
@@ -444,7 +650,7 @@ extern "C" int mf_load_ratings(ps_handle ps, int64_t m, int64_t n, int64_t nnz, 
     int32_t *d_err = nullptr; uint64_t *key_a = nullptr, *key_b = nullptr; uint32_t *pos_a = nullptr, *pos_b = nullptr;
     uint32_t *seg_idx = nullptr, *seg_start = nullptr, *is_multi = nullptr, *multi_idx = nullptr, *seg_slot = nullptr;
     u64 *bm_hist = nullptr; char *tmp = nullptr;
-    uint32_t *runidx = nullptr, *tflag = nullptr, *tq = nullptr, *tpos = nullptr;
+    uint32_t *runidx = nullptr, *tflag = nullptr, *tq = nullptr, *tpos = nullptr, *pos_run = nullptr, *trun_blk = nullptr;
     int32_t *d_aux = nullptr;          // [0] largest number of non-heavy runs in a block, [1] rows descend in such a run
     int32_t h_aux[2] = {0, 0};
     uint32_t h_tail[4] = {0, 0, 0, 0};
@@ -463,6 +669,7 @@ extern "C" int mf_load_ratings(ps_handle ps, int64_t m, int64_t n, int64_t nnz, 
         bm_hist = a.take<u64>(nb);
         runidx = a.take<uint32_t>(nnz + 1); tflag = a.take<uint32_t>(nnz + 1);
         tq = a.take<uint32_t>(nnz + 1); tpos = a.take<uint32_t>(nnz + 1);
+        pos_run = a.take<uint32_t>(nnz + 1); trun_blk = a.take<uint32_t>(nnz + 1);
         d_aux = a.take<int32_t>(2);
         if (pass == 0) {
             HIPRC(rocprim::radix_sort_pairs(nullptr, tmp_sort64, key_a, key_b, pos_a, pos_b, (size_t)std::max<int64_t>(nnz, 1), 0, 64, st));
@@ -625,13 +832,15 @@ extern "C" int mf_load_ratings(ps_handle ps, int64_t m, int64_t n, int64_t nnz, 
         k_tail_fill<<<grid_for(nnz, 256), 256, 0, st>>>(pos_b, tq, tpos, head, scan, seg_idx, seg_start, is_multi, seg_slot, runidx,
                                                         blk, f.blk_run_ptr, f.blk_nheavy, f.run_start, f.row, f.val, nnz, f.t_cinfo,
                                                         f.t_val, f.trun_start, f.trun_row, f.trun_wait, f.run_col, f.trun_ci, f.trun_val,
-                                                        f.trun_col, d_err);
+                                                        f.trun_col, pos_run, trun_blk, d_err);
     }
     k_blk_ptr_from_scan<<<grid_for(nb + 1, 256), 256, 0, st>>>(d_bp, nb, nnz, scan, ntr, f.blk_trun_ptr);
     HIPRC(hipGetLastError());
     HIPRC(hipMemcpyAsync(&h_err, d_err, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPRC(hipStreamSynchronize(st));
     if (h_err) { rc = h_err; goto done; }
+    rc = build_schedule(ps, pos_b, tq, tpos, pos_run, trun_blk, st);
+    if (rc) goto done;
     // --- where the groups of the heavy runs start (head / scan are free again) ----------------------
     HIPRC(hipMalloc(&f.run_gptr, (num_runs + 1) * sizeof(int64_t)));
     if (num_runs > 0) {

@@ -569,6 +569,7 @@ static SgdArgs sgd_args(dpaps_ps *ps, const int32_t *tasks, float lr, float lamb
     a.trun_start = f.trun_start; a.trun_row = f.trun_row; a.trun_wait = f.trun_wait;
     a.trun_ci = f.trun_ci; a.trun_val = f.trun_val; a.trun_col = f.trun_col;
     a.t_cinfo = f.t_cinfo; a.t_val = f.t_val;
+    a.blk_chunk_ptr = f.blk_chunk_ptr; a.ch_trun = f.ch_trun; a.ch_lv = f.ch_lv; a.lv_start = f.lv_start; a.s_rec = f.s_rec; a.blk_meta = f.blk_meta;
     a.run_gptr = f.run_gptr; a.gstart = f.gstart;
     a.lr = lr; a.lambda = lambda; a.stats = ps->stats; a.err = ps->err;
     a.W = ps->W; a.per_home = ps->per_home; a.owner_w = ps->owner;

@@ -45,10 +45,14 @@
 #include "mf_device.h"
 
 #include <algorithm>
+#include <type_traits>
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+
+typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 
 #define CH 15                    // entries per group (the 16th row of X is the column's row)
 #define AUX_SC1 16               // cache policy of a buffer access: agent scope
@@ -119,7 +123,8 @@ __device__ __forceinline__ void solve_first() { __asm__ volatile("s_nop 4"); }
 // LONG_RUNS: the variant of the recurrence for data with column runs of very many groups (see there).
 // RICH: compiled for at most 12 wavefronts, so with a third more registers: what does not depend on the column's
 // factor is then read ahead of the wait for it.
-template <int NT, bool A4, bool AGENT_H, bool LONG_RUNS, bool RICH = false>
+// SCHED: the second part by levels (see there), for data whose blocks have their non-heavy columns fit in LDS.
+template <int NT, bool A4, bool AGENT_H, bool LONG_RUNS, bool SCHED, bool RICH = false>
 __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const int32_t worker, const int32_t rb, const int32_t cb) {
     if constexpr (!AGENT_H) {     // (in the loop, the caller looks: there all threads must take the same way)
         if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
@@ -163,7 +168,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
     const int nruns = (int)(run1 - run0);
     const int nheavy = __builtin_amdgcn_readfirstlane(a.blk_nheavy[b]);
     const int ntcols = nruns - nheavy;                                 // non-heavy columns
-    const int ncached = min(ntcols, a.hcache_cap);
+    const int ncached = SCHED ? 0 : min(ntcols, a.hcache_cap);
     const int64_t tr0 = uniform_i64(a.blk_trun_ptr[b]), tr1 = uniform_i64(a.blk_trun_ptr[b + 1]);
     const float lr = __uint_as_float(lr_), lambda = __uint_as_float(lambda_);
     const float delta = (float)((double)lr * (double)lambda);         // c = 1 - delta
@@ -211,7 +216,8 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
         if (bad) atomicExch(a.err, PS_EREMOTE);
     }
     for (int t = threadIdx.x; t < nmulti; t += blockDim.x) ticket[t] = 0;
-    for (int t = threadIdx.x; t < ntcols; t += blockDim.x) ctick[t] = 0;
+    if constexpr (!SCHED)
+        for (int t = threadIdx.x; t < ntcols; t += blockDim.x) ctick[t] = 0;
     for (int i = threadIdx.x; i < hwaves * 16 * RS; i += blockDim.x) lds_f[i] = 0.0f;
     // the heavy columns' factors (components past the rank are zero) and their group counters
     if (tid < DPAPS_HEAVY_MAX * 16 * NT) hshare[tid] = pre_heavy;
@@ -233,6 +239,45 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
     __syncthreads();
 
     unsigned int done = 0;
+    // What the second part will read has not been read in this epoch.  The wavefronts that take no heavy runs (all of them
+    // where there are none) fetch it meanwhile: the block's records, row and column numbers into the end of LDS, where
+    // there is room beside the first part's (blk_meta: its words, 0 if not), and a word of every 128 bytes of the
+    // factors, so that they are in the die's cache (the results of those loads are not used).
+    uint32_t meta_words = 0;
+    int64_t ch0 = 0, ch1 = 0;
+    uint32_t run_a = 0, ent_a = 0;                                     // the block's first row run and entry
+    int nrows_b = 0, ntail_b = 0;
+    if constexpr (SCHED) {
+        ch0 = uniform_i64(a.blk_chunk_ptr[b]); ch1 = uniform_i64(a.blk_chunk_ptr[b + 1]);
+        if (ch1 > ch0) {
+            meta_words = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.blk_meta[b]);
+            run_a = (uint32_t)tr0; nrows_b = (int)(tr1 - tr0);
+            ent_a = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.trun_start[tr0]);
+            ntail_b = (int)((uint32_t)__builtin_amdgcn_readfirstlane((int)a.trun_start[tr1]) - ent_a);
+            const bool all = nheavy == 0 || nwaves <= hwaves;
+            if (all || wave >= hwaves) {
+                const int first = all ? tid : tid - 64 * hwaves, by = 64 * (all ? nwaves : nwaves - hwaves);
+                if (meta_words != 0) {
+                    uint2 *recs = reinterpret_cast<uint2 *>(lds_f + a.lds_words - meta_words);
+                    int32_t *rids = reinterpret_cast<int32_t *>(recs + ntail_b), *cids = rids + nrows_b;
+                    for (int t = first; t < nrows_b; t += by) rids[t] = a.trun_row[run_a + t];
+                    for (int t = first; t < ntcols; t += by) cids[t] = a.run_col[run0 + nheavy + t];
+#pragma unroll 4
+                    for (int e = first; e < ntail_b; e += by) recs[e] = a.s_rec[ent_a + e];
+                }
+                if (!all) {
+                    const int lines = (L * 4 + 127) / 128;
+                    for (int t = first; t < nrows_b + ntcols; t += by) {
+                        const int64_t k = t < nrows_b ? a.trun_row[run_a + t] : a.m + a.run_col[run0 + nheavy + t - nrows_b];
+                        for (int i = 0; i < lines; ++i) {
+                            const float x = a.val[k * L + 32 * i];
+                            __asm__ volatile("" ::"v"(x));
+                        }
+                    }
+                }
+            }
+        }
+    }
     // ---- part 1: the heavy runs, in groups ----------------------------------------------
     // A heavy run is processed by a team of T wavefronts that take its groups in turn.  Only a small part
     // of a group's work depends on the column's factor h as the previous group left it: the inner products
@@ -617,6 +662,193 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
         }
     }
 
+    if constexpr (SCHED) {
+        // ---- part 2 by levels ---------------------------------------------------------------
+        // The other entries come as a schedule: the block's row runs in chunks whose factors fit in LDS beside the
+        // block's non-heavy columns, the entries of a chunk by level (see k_tail_levels), the entries of a level free of
+        // each other.  LPE lanes take an entry, four components each - the fewest lanes that hold a row, since what a
+        // step costs is its instructions, however many lanes they serve: both factors from LDS, the step, both
+        // back; a barrier ends the level.  Nothing is waited for but the barrier, no ticket is looked at and no factor
+        // leaves LDS before the chunk is done.
+        // What bounds it is the number of levels times the latency of a step and a barrier: 0.29 us a level at rank 16 (43
+        // entries each), 0.30 at rank 50, 0.34 at rank 100 (10 entries), of which the barrier is 0.03 and the trips to LDS
+        // 0.15 (alone, in a loop); LDS is filled in 4 us and the factors go back in 1 (large) to 3.  Row by row with
+        // tickets (the other variants below) a wavefront took an entry every 0.5 us, one after the other: a launch of
+        // the 1000 x 1000 configuration 213 -> 57 us, 100k x 10k 162 -> 114 us, 480,189 x 17,770 121 -> 111 us (there
+        // tickets let the second part overlap the first, which levels cannot).
+        constexpr int LPE = NT <= 1 ? 4 : NT <= 2 ? 8 : NT <= 4 ? 16 : 32, EPW = 64 / LPE;   // lanes per entry, entries per wavefront
+        if (ch1 > ch0) {
+            // (the thread's number once more, opaque to the compiler: what depends on it would otherwise be computed ahead
+            // of the first part and held - or spilled - through it)
+            int td = tid;
+            __asm__ volatile("" : "+v"(td));
+            const int ln = td & 63, j = ln & (LPE - 1), sub = ln & ~(LPE - 1), nq = EPW * nwaves;
+            const int w0 = EPW * __builtin_amdgcn_readfirstlane(td >> 6), q0 = w0 + ln / LPE;   // (w0: the same in all lanes, and said to be)
+            const int LS = DPAPS_LDS_STRIDE(L);
+            const bool have = 4 * j < L;                               // this lane has components
+            constexpr std::integral_constant<bool, false> of_row{}, in{};
+            constexpr std::integral_constant<bool, true> of_col{}, back{};
+            // `count` factors - the block's rows or columns, number id(s) for the s-th - to LDS at dst + s LS, or back.  Accesses
+            // at an offset past the end of the factors' buffer read zero and write nothing.
+            auto copy = [&](auto ids, int count, float *dst, auto which, auto dir) {
+                constexpr bool COL = decltype(which)::value, BACK = decltype(dir)::value;
+                constexpr int UN = 4, AUX = COL && AGENT_H ? AUX_SC1 : 0;
+                const __amdgpu_buffer_rsrc_t buf = COL ? hbuf : wbuf;
+                const int span = (int)(COL ? hspan : wspan), first_id = (int)(COL ? blk_c0 : blk_r0);
+#pragma unroll 1
+                for (int base = 0; base < count; base += LPE * nq) {
+                    const int mine = base + q0 + j * nq;               // (LPE rounds' offsets are in the entry's lanes)
+                    const int at = mine < count ? (ids(mine) - first_id) * L * 4 : span;
+#pragma unroll 1
+                    for (int i0 = 0; i0 < LPE && base + w0 + i0 * nq < count; i0 += UN) {
+                        f32x4 x[UN];
+                        int off[UN];
+#pragma unroll
+                        for (int u = 0; u < UN; ++u) off[u] = bperm_i(at, sub + i0 + u);
+#pragma unroll
+                        for (int u = 0; u < UN; ++u) {
+                            const int s = base + q0 + (i0 + u) * nq;
+                            const int o = s < count && have ? off[u] + 16 * j : span;
+                            const int o1 = 4 * j + 1 < L ? o : span, o2 = 4 * j + 2 < L ? o : span, o3 = 4 * j + 3 < L ? o : span;
+                            f32x4 *l = reinterpret_cast<f32x4 *>(dst + (uint32_t)s * (uint32_t)LS + 4 * j);
+                            if constexpr (!BACK) {
+                                if constexpr (A4) x[u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(buf, o, 0, AUX));
+                                else if (even_rank) {
+                                    const u32x2 p0 = __builtin_amdgcn_raw_buffer_load_b64(buf, o, 0, AUX), p1 = __builtin_amdgcn_raw_buffer_load_b64(buf, o2 + 8, 0, AUX);
+                                    const uint32_t a0 = p0[0], a1 = p0[1], a2 = p1[0], a3 = p1[1];
+                                    x[u] = f32x4{__uint_as_float(a0), __uint_as_float(a1), __uint_as_float(a2), __uint_as_float(a3)};
+                                } else {
+                                    x[u][0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, o, 0, AUX));
+                                    x[u][1] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, o1 + 4, 0, AUX));
+                                    x[u][2] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, o2 + 8, 0, AUX));
+                                    x[u][3] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, o3 + 12, 0, AUX));
+                                }
+                            } else {
+                                f32x4 y = {0.0f, 0.0f, 0.0f, 0.0f};
+                                if (s < count && have) y = *l;
+                                const uint32_t y0 = __float_as_uint(y[0]), y1 = __float_as_uint(y[1]), y2 = __float_as_uint(y[2]), y3 = __float_as_uint(y[3]);
+                                if constexpr (A4) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, y), buf, o, 0, AUX);
+                                else if (even_rank) {
+                                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{y0, y1}, buf, o, 0, AUX);
+                                    __builtin_amdgcn_raw_buffer_store_b64(u32x2{y2, y3}, buf, o2 + 8, 0, AUX);
+                                } else {
+                                    __builtin_amdgcn_raw_buffer_store_b32(y0, buf, o, 0, AUX);
+                                    __builtin_amdgcn_raw_buffer_store_b32(y1, buf, o1 + 4, 0, AUX);
+                                    __builtin_amdgcn_raw_buffer_store_b32(y2, buf, o2 + 8, 0, AUX);
+                                    __builtin_amdgcn_raw_buffer_store_b32(y3, buf, o3 + 12, 0, AUX);
+                                }
+                            }
+                        }
+                        if constexpr (!BACK) {
+#pragma unroll
+                            for (int u = 0; u < UN; ++u) {
+                                const int s = base + q0 + (i0 + u) * nq;
+                                if (s < count && have) *reinterpret_cast<f32x4 *>(dst + (uint32_t)s * (uint32_t)LS + 4 * j) = x[u];
+                            }
+                        }
+                    }
+                }
+            };
+            // lanes without an entry, or past the row's end, read zeros in front of the factors and write behind those
+            float *const colbuf = lds_f + DPAPS_SCHED_BASE, *const rowbuf = colbuf + (size_t)ntcols * LS;
+            const uint32_t meta0 = a.lds_words - meta_words;           // (in words) records, row numbers, column numbers
+            const int32_t *const lds_i = reinterpret_cast<const int32_t *>(lds_f);
+            const uint32_t rid0 = meta0 + 2 * (uint32_t)ntail_b, cid0 = rid0 + (uint32_t)nrows_b;
+            auto col_id = [&](int s) { return meta_words != 0 ? lds_i[cid0 + s] : a.run_col[run0 + nheavy + s]; };
+            // the first chunk's place in the tables, on its way while the others finish the heavy runs
+            uint32_t t0 = a.ch_trun[ch0], t1 = a.ch_trun[ch0 + 1], lv0 = a.ch_lv[ch0], lv1 = a.ch_lv[ch0 + 1], e0 = ent_a;
+            __syncthreads();                                           // the heavy runs are through, their LDS is free
+            if (td < DPAPS_SCHED_BASE) lds_f[td] = 0.0f;
+            for (int64_t c = ch0; c < ch1; ++c) {
+                const int nrows = (int)(t1 - t0), nlev = (int)(lv1 - lv0);
+                // where the levels start, 64 at a time, one per lane
+                int vb = 0;
+                auto starts = [&]() { return (int)(a.lv_start[lv0 + (vb + ln < nlev ? vb + ln : nlev)] - e0); };
+                int lv_win = starts();
+                auto start = [&](int v) { return rl_i(lv_win, (v < nlev ? v : nlev) - vb); };
+                auto row_id = [&](int s) { return meta_words != 0 ? lds_i[rid0 + (t0 - run_a) + s] : a.trun_row[t0 + s]; };
+                uint2 *const recs = reinterpret_cast<uint2 *>(meta_words != 0 ? lds_f + meta0 + 2 * (e0 - ent_a) : rowbuf + (size_t)nrows * LS);
+                const uint32_t e1 = a.lv_start[lv1];
+                if (meta_words == 0)
+                    for (uint32_t e = td; e < e1 - e0; e += blockDim.x) recs[e] = a.s_rec[e0 + e];
+                if (c == ch0) copy(col_id, ntcols, colbuf, of_col, in);
+                copy(row_id, nrows, rowbuf, of_row, in);
+                __syncthreads();
+                // this lane's pieces of the two factors of an entry (where they are read, where they go), and its value
+                struct Place { lds_f32x4 *wr, *hr, *ww, *hw; float val; };
+                auto place = [&](uint2 r, bool act) {
+                    lds_f32x4 *const zeros = (lds_f32x4 *)lds_f, *const sink = zeros + 1;
+                    lds_f32x4 *const w = (lds_f32x4 *)(lds_f + ((r.x & 0xFFFFu) + 4 * j)), *const h = (lds_f32x4 *)(lds_f + ((r.x >> 16) + 4 * j));
+                    act = act && have;
+                    return Place{act ? w : zeros, act ? h : zeros, act ? w : sink, act ? h : sink, __uint_as_float(r.y)};
+                };
+                // one step; `between` is done while the factors are on their way, `then` before they go back
+                auto step = [&](const Place at, auto between, auto then) {
+                    const f32x4 w = *at.wr, h = *at.hr;
+                    __builtin_amdgcn_sched_barrier(0);
+                    between();
+                    __builtin_amdgcn_sched_barrier(0);
+                    float p = __builtin_fmaf(w[0], h[0], w[1] * h[1]) + __builtin_fmaf(w[2], h[2], w[3] * h[3]);
+                    p = dpp_add<0xB1, 0xF>(p);                         // quad_perm [1,0,3,2]: pairs
+                    p = dpp_add<0x4E, 0xF>(p);                         // quad_perm [2,3,0,1]: quads
+                    if constexpr (LPE >= 8) p = dpp_add<0x141, 0xF>(p);    // row_half_mirror: 8 lanes
+                    if constexpr (LPE >= 16) p = dpp_add<0x140, 0xF>(p);   // row_mirror: 16 lanes
+                    if constexpr (LPE >= 32) p = add_across_row_pairs(p);  // 32 lanes
+                    // x + lr (e y - lambda x): one rounding at the size of x, as in the other variants
+                    const float le = lr * (at.val - p);
+                    f32x4 wn, hn;
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        hn[i] = h[i] + __builtin_fmaf(le, w[i], -(delta * h[i]));
+                        wn[i] = w[i] + __builtin_fmaf(le, h[i], -(delta * w[i]));
+                    }
+                    *at.hw = hn;
+                    *at.ww = wn;
+                    __builtin_amdgcn_sched_barrier(0);
+                    then();
+                };
+                int s0 = 0, s1 = start(1);
+                bool mine = w0 < s1;                                   // this wavefront has entries in the level
+                Place at = place(q0 < s1 ? recs[q0] : make_uint2(0u, 0u), q0 < s1);
+                for (int v = 0; v < nlev; ++v) {
+                    // the next level's extent and record
+                    int s2 = 0;
+                    bool act_n = false;
+                    uint2 rec = make_uint2(0u, 0u);
+                    auto next = [&]() {
+                        if (__builtin_expect(v + 2 - vb >= 64, 0)) { vb = v; lv_win = starts(); }
+                        s2 = start(v + 2);
+                        act_n = s1 + q0 < s2;
+                        if (act_n) rec = recs[s1 + q0];
+                    };
+                    if (mine) {
+                        Place at_n;
+                        step(at, next, [&]() { at_n = place(rec, act_n); });
+                        for (int q = s0 + nq; q + w0 < s1; q += nq) {  // (a level with more entries than places)
+                            const bool act = q + q0 < s1;
+                            step(place(act ? recs[q + q0] : make_uint2(0u, 0u), act), []() {}, []() {});
+                        }
+                        at = at_n;
+                    } else {
+                        next();
+                        at = place(rec, act_n);
+                    }
+                    mine = s1 + w0 < s2;
+                    s0 = s1; s1 = s2;
+                    __syncthreads();
+                }
+                copy(row_id, nrows, rowbuf, of_row, back);
+                if (wave == 0) done += e1 - e0;
+                if (c + 1 < ch1) {
+                    t0 = t1; t1 = a.ch_trun[c + 2]; lv0 = lv1; lv1 = a.ch_lv[c + 2]; e0 = e1;
+                    // (the rows lie where they lay, and each is read back by the lanes that fetch its place's next; records
+                    // that were fetched with the chunk lie elsewhere)
+                    if (meta_words == 0) __syncthreads();
+                }
+            }
+            copy(col_id, ntcols, colbuf, of_col, back);
+        }
+    }
     // ---- part 2: the other runs, row by row ---------------------------------------------
     // A wavefront takes the next D consecutive row runs, waits until the heavy runs have passed these
     // rows, reads their entries and factors in one go, and then keeps going round its rows: whichever
@@ -624,8 +856,9 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
     // looked at again in the next round.  Batches are taken in ascending order and no wavefront ever
     // waits for one particular entry, so the lowest unfinished entry of the block is always processed
     // in its wavefront's next round: every wait ends.
-    __builtin_amdgcn_s_setprio(1);
-    if constexpr (!LONG_RUNS) {
+    if constexpr (!SCHED) __builtin_amdgcn_s_setprio(1);
+    if constexpr (SCHED) {
+    } else if constexpr (!LONG_RUNS) {
         if (tr1 > tr0) {
             constexpr int D = 4;
             const int ntrow = (int)(tr1 - tr0);
@@ -947,7 +1180,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
     if (lane == 0 && done) atomicAdd(&done_entries, done);
     __syncthreads();
     // write the cached column factors back
-    {
+    if constexpr (!SCHED) {
         const int total = ncached * L;
 #pragma unroll 4
         for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
@@ -966,10 +1199,10 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
 // One workgroup per task of a stratum.
 // MAXT: the largest workgroup the kernel is compiled for (12 wavefronts leave each of them a third more registers
 // than 16 do, which the first part needs)
-template <int NT, bool A4, int MAXT, bool LONG_RUNS>
+template <int NT, bool A4, int MAXT, bool LONG_RUNS, bool SCHED>
 __global__ __launch_bounds__(MAXT) void k_mf_sgd_chunk(SgdArgs a) {
     extern __shared__ __attribute__((aligned(16))) float lds_f[];
-    sgd_block<NT, A4, false, LONG_RUNS, MAXT <= 768>(a, lds_f, a.tasks[3 * blockIdx.x], a.tasks[3 * blockIdx.x + 1], a.tasks[3 * blockIdx.x + 2]);
+    sgd_block<NT, A4, false, LONG_RUNS, SCHED, MAXT <= 768>(a, lds_f, a.tasks[3 * blockIdx.x], a.tasks[3 * blockIdx.x + 1], a.tasks[3 * blockIdx.x + 2]);
 }
 
 // ---- an epoch without barriers: column blocks handed from worker to worker ----------------------------------
@@ -1011,7 +1244,7 @@ __device__ __forceinline__ int handoff_take(const SgdArgs &a, const uint32_t *to
     }
 }
 
-template <int NT, bool A4, bool LONG_RUNS>
+template <int NT, bool A4, bool LONG_RUNS, bool SCHED>
 __global__ __launch_bounds__(1024) void k_mf_sgd_handoff(SgdArgs a) {
     extern __shared__ __attribute__((aligned(16))) float lds_f[];
     __shared__ uint32_t todo[DPAPS_HANDOFF_MAX_COLS / 32];
@@ -1041,7 +1274,7 @@ __global__ __launch_bounds__(1024) void k_mf_sgd_handoff(SgdArgs a) {
         const int cb = __builtin_amdgcn_readfirstlane(s_cb);          // the same in all lanes: block addresses stay scalar
         const int visit = __builtin_amdgcn_readfirstlane(s_visit);
         if (cb < 0) break;
-        sgd_block<NT, A4, true, LONG_RUNS>(a, lds_f, worker, worker, cb);
+        sgd_block<NT, A4, true, LONG_RUNS, SCHED>(a, lds_f, worker, worker, cb);
         // every store of this wavefront has reached memory before the barrier, every wavefront's before the release
         __builtin_amdgcn_s_waitcnt(0);
         __syncthreads();
@@ -1057,6 +1290,10 @@ static bool dpaps_wide_like(const MfData &f) {
     return f.max_run_groups >= DPAPS_LONG_RUN_GROUPS || (f.num_truns > 0 && 2 * f.num_tail < 3 * f.num_truns);
 }
 
+// The second part by levels, where a schedule was built - unless a bound on the factors in LDS is set, which only the
+// other variants observe.
+static bool use_sched(const dpaps_ps *ps) { return ps->mf.sched_ok && ps->opt_cache_rows < 0; }
+
 // Wavefronts per workgroup of the SGD kernels: what PS_OPT_MF_WAVES says, else 16 - or 12 where the grouped kernel
 // runs on data of that kind: its second part has little to wait for there, and with 12 wavefronts each has a third
 // more registers, which the first part uses to read ahead of its wait for the column's factor (measured on the
@@ -1069,8 +1306,10 @@ int dpaps_mf_waves(const dpaps_ps *ps) {
 
 // LDS plan of sgd_block: staging areas, tables and the heavy columns' factors, the two kinds of ticket counters,
 // then as many other column factors as fit.  Fills in a.ctick_cap, a.hcache_cap.
+// The second part by levels: it has all of LDS to itself once the heavy runs are through, so the first part only needs
+// its own to fit.
 template <int NT>
-static int plan_block_lds(dpaps_ps *ps, SgdArgs &a, size_t *lds_out) {
+static int plan_block_lds(dpaps_ps *ps, SgdArgs &a, bool sched, size_t *lds_out) {
     const MfData &f = ps->mf;
     const int L = a.L;
     // the kernel addresses the factors of a block's rows, and of its columns, with 32-bit byte offsets
@@ -1079,10 +1318,15 @@ static int plan_block_lds(dpaps_ps *ps, SgdArgs &a, size_t *lds_out) {
         return PS_ELIMIT;
     }
     if (!f.sweep_ok) { ps->last_error = "the grouped SGD kernel needs rows in ascending order inside the short column runs"; return PS_ELAYOUT; }
-    a.ctick_cap = f.max_tail_cols > 1 ? f.max_tail_cols : 1;
-    const int64_t fixed = ((int64_t)a.heavy_waves * 16 * (16 * NT + 4) + 60 + DPAPS_HEAVY_MAX * 16 * NT + DPAPS_HEAVY_MAX) * 4 +
-                          ((int64_t)a.ticket_cap + a.ctick_cap) * 4;
-    const int64_t budget = (int64_t)ps->lds_bytes - 1024;         // static LDS and slack
+    a.ctick_cap = sched ? 0 : (f.max_tail_cols > 1 ? f.max_tail_cols : 1);
+    const int64_t fixed = dpaps_heavy_lds(NT, a.heavy_waves) + ((int64_t)a.ticket_cap + a.ctick_cap) * 4;
+    const int64_t budget = (int64_t)ps->lds_bytes - DPAPS_LDS_SLACK;
+    if (sched && fixed <= budget) {
+        a.lds_words = (uint32_t)(budget / 4);
+        a.hcache_cap = 0;
+        *lds_out = (size_t)budget;
+        return PS_OK;
+    }
     if (fixed > budget) { ps->last_error = "not enough LDS for the grouped SGD kernel"; return PS_ELIMIT; }
     int64_t hcap = (budget - fixed) / ((int64_t)L * 4);
     if (hcap > f.max_tail_cols) hcap = f.max_tail_cols;
@@ -1092,18 +1336,18 @@ static int plan_block_lds(dpaps_ps *ps, SgdArgs &a, size_t *lds_out) {
     return PS_OK;
 }
 
-template <int NT, bool A4, int MAXT, bool LONG_RUNS>
+template <int NT, bool A4, int MAXT, bool LONG_RUNS, bool SCHED>
 static int launch_chunk_t(dpaps_ps *ps, SgdArgs a, int ntasks, int waves, hipStream_t st) {
     size_t lds = 0;
-    const int rc = plan_block_lds<NT>(ps, a, &lds);
+    const int rc = plan_block_lds<NT>(ps, a, SCHED, &lds);
     if (rc) return rc;
     static size_t configured = 0;
     if (lds > configured) {
-        PS_HIP(ps, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mf_sgd_chunk<NT, A4, MAXT, LONG_RUNS>),
+        PS_HIP(ps, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mf_sgd_chunk<NT, A4, MAXT, LONG_RUNS, SCHED>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
         configured = lds;
     }
-    k_mf_sgd_chunk<NT, A4, MAXT, LONG_RUNS><<<ntasks, 64 * waves, lds, st>>>(a);
+    k_mf_sgd_chunk<NT, A4, MAXT, LONG_RUNS, SCHED><<<ntasks, 64 * waves, lds, st>>>(a);
     PS_HIP(ps, hipGetLastError());
     return PS_OK;
 }
@@ -1111,8 +1355,10 @@ static int launch_chunk_t(dpaps_ps *ps, SgdArgs a, int ntasks, int waves, hipStr
 template <int NT, bool A4>
 static int launch_chunk(dpaps_ps *ps, SgdArgs a, int ntasks, int waves, hipStream_t st) {
     if (dpaps_wide_like(ps->mf))
-        return waves <= 12 ? launch_chunk_t<NT, A4, 768, true>(ps, a, ntasks, waves, st) : launch_chunk_t<NT, A4, 1024, true>(ps, a, ntasks, waves, st);
-    return waves <= 12 ? launch_chunk_t<NT, A4, 768, false>(ps, a, ntasks, waves, st) : launch_chunk_t<NT, A4, 1024, false>(ps, a, ntasks, waves, st);
+        return waves <= 12 ? launch_chunk_t<NT, A4, 768, true, false>(ps, a, ntasks, waves, st) : launch_chunk_t<NT, A4, 1024, true, false>(ps, a, ntasks, waves, st);
+    if (use_sched(ps))
+        return waves <= 12 ? launch_chunk_t<NT, A4, 768, false, true>(ps, a, ntasks, waves, st) : launch_chunk_t<NT, A4, 1024, false, true>(ps, a, ntasks, waves, st);
+    return waves <= 12 ? launch_chunk_t<NT, A4, 768, false, false>(ps, a, ntasks, waves, st) : launch_chunk_t<NT, A4, 1024, false, false>(ps, a, ntasks, waves, st);
 }
 
 // The plan of a block: word w of its 16 = run_first | run_last << 8 | T << 16 | mb << 24 for heavy wavefront w
@@ -1145,33 +1391,33 @@ __global__ void k_team_plan(const int64_t *blk_run_ptr, const int32_t *blk_nheav
     for (; w < 16; ++w) plan[b * 16 + w] = 0;
 }
 
-template <int NT, bool A4, bool LONG_RUNS>
+template <int NT, bool A4, bool LONG_RUNS, bool SCHED>
 static int launch_handoff_t(dpaps_ps *ps, SgdArgs a, int workers, hipStream_t st) {
     size_t lds = 0;
-    const int rc = plan_block_lds<NT>(ps, a, &lds);
+    const int rc = plan_block_lds<NT>(ps, a, SCHED, &lds);
     if (rc) return rc;
     static size_t configured = 0;
     if (lds > configured) {
-        PS_HIP(ps, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mf_sgd_handoff<NT, A4, LONG_RUNS>), hipFuncAttributeMaxDynamicSharedMemorySize,
+        PS_HIP(ps, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mf_sgd_handoff<NT, A4, LONG_RUNS, SCHED>), hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds));
         configured = lds;
     }
-    k_mf_sgd_handoff<NT, A4, LONG_RUNS><<<workers, 1024, lds, st>>>(a);
+    k_mf_sgd_handoff<NT, A4, LONG_RUNS, SCHED><<<workers, 1024, lds, st>>>(a);
     PS_HIP(ps, hipGetLastError());
     return PS_OK;
 }
 
 template <int NT, bool A4>
 static int launch_handoff(dpaps_ps *ps, SgdArgs a, int workers, hipStream_t st) {
-    return dpaps_wide_like(ps->mf) ? launch_handoff_t<NT, A4, true>(ps, a, workers, st)
-                                                          : launch_handoff_t<NT, A4, false>(ps, a, workers, st);
+    if (dpaps_wide_like(ps->mf)) return launch_handoff_t<NT, A4, true, false>(ps, a, workers, st);
+    return use_sched(ps) ? launch_handoff_t<NT, A4, false, true>(ps, a, workers, st) : launch_handoff_t<NT, A4, false, false>(ps, a, workers, st);
 }
 
 // how the wavefronts of a workgroup share the heavy runs: with 12 or more wavefronts, 12 (14 of 16) of them take
 // heavy runs as the block's plan says; else at most one per heavy run
 static int plan_teams(dpaps_ps *ps, SgdArgs &a, int waves, hipStream_t st) {
     a.team = waves >= 12 ? 2 : 1;
-    a.heavy_waves = waves >= 16 ? 14 : (waves >= 12 ? 12 : (waves < DPAPS_HEAVY_MAX ? waves : DPAPS_HEAVY_MAX));
+    a.heavy_waves = waves >= 16 ? DPAPS_HEAVY_WAVES : (waves >= 12 ? 12 : (waves < DPAPS_HEAVY_MAX ? waves : DPAPS_HEAVY_MAX));
     a.team_plan = nullptr;
     if (a.team == 2) {
         MfData &f = ps->mf;
