@@ -91,8 +91,8 @@ struct dpaps_ps {
                                       // adds to slot blockIdx.x % PS_STAT_SLOTS, so that the atomics of one launch
                                       // spread over many cache lines); ps_stats adds the slots up
     int32_t *err = nullptr;           // sticky device error flag (0 = fine)
-    // stamps for counting the distinct destinations of one call's messages
-    uint32_t *stamp_h = nullptr, *stamp_o = nullptr, *stamp_pair = nullptr;
+    // for counting the distinct destinations of one call's messages: a bit each, and stamps for pairs of many nodes
+    uint32_t *named = nullptr, *stamp_pair = nullptr;
     uint32_t call_id = 0;
     // growable scratch for ps_push
     void *ws = nullptr;
@@ -125,11 +125,15 @@ struct dpaps_ps {
     double *d_sse = nullptr;
     void *kge_ws = nullptr;           // scratch of kge_sgd_step (grows)
     size_t kge_ws_bytes = 0;
+    u64 *kge_seen = nullptr;          // K: the last slot that named the key, with its step's id in front (see k_kge_keys)
+    uint32_t *kge_shared = nullptr;   // two steps' flags, one per slot
+    size_t kge_shared_slots = 0;
+    uint32_t kge_id = 0;
     int16_t *loc = nullptr;           // location caches (PS_OPT_LOCATION_CACHES): W x K, node n's belief where key k is, -1 none
     void *handoff_ws = nullptr;       // column block states and the recorded order of mf_sgd_epoch_handoff (grows)
     size_t handoff_ws_bytes = 0;
     hipStream_t side_stream = nullptr;   // default priority: the localize calls and statistics of kge_sgd_epoch run here
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_sorted = nullptr, ev_added = nullptr;
+    hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_sorted = nullptr, ev_added = nullptr, ev_keys = nullptr;
     std::string last_error;
 };
 
@@ -192,22 +196,28 @@ int dpaps_launch_sgd_chunk(dpaps_ps *ps, const SgdArgs &a, int ntasks, int waves
 int dpaps_launch_sgd_handoff(dpaps_ps *ps, const SgdArgs &a, int workers, hipStream_t st);
 int dpaps_mf_waves(const dpaps_ps *ps);
 
+// What of a push a step has added to the store itself: the slots from the fourth of a data point on whose key no other
+// slot of the batch names (shared[slot] == id: another does; NULL: nothing has been added).
+struct PushDone {
+    const uint32_t *shared = nullptr;
+    uint32_t id = 0, slots = 1;          // slots of a data point
+    __device__ __forceinline__ bool in_place(uint32_t slot) const { return slot % slots >= 3u && shared[slot] != id; }
+};
+
 // ps_store.hip: the two halves of ps_pull and ps_push, for steps that read the store where they use the values
 // and add up the update terms of one data point before they push them
-int dpaps_account_pull(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, hipStream_t st);
-int dpaps_account_push(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, hipStream_t st);
-int dpaps_account_pull_push(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, hipStream_t st);
 int dpaps_route_pull_push(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, hipStream_t st);   // without the key check
 int dpaps_localize_checked(dpaps_ps *ps, const int64_t *keys, int64_t n, int32_t worker, hipStream_t st);
-int dpaps_push_apply(dpaps_ps *ps, const int64_t *keys, int64_t n, const float *deltas, hipStream_t st);
-int dpaps_push_sort(dpaps_ps *ps, const int64_t *keys, int64_t n, hipStream_t st);     // the two halves of dpaps_push_apply
-int dpaps_push_add(dpaps_ps *ps, int64_t n, const float *deltas, hipStream_t st);
-int dpaps_check_keys(dpaps_ps *ps, const int64_t *keys, int64_t n, hipStream_t st);     // the key check of the dpaps_account_* calls
+int dpaps_push_sort(dpaps_ps *ps, const int64_t *keys, int64_t n, hipStream_t st);     // the two halves of a push of checked keys
+int dpaps_push_add(dpaps_ps *ps, int64_t n, const float *deltas, const PushDone &done, hipStream_t st);
+int dpaps_push_add_step(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, const float *deltas, const PushDone &done, hipStream_t st);
+int64_t dpaps_few_keys();
+int dpaps_push_few_step(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, const float *deltas, hipStream_t st);
 
 // key_sort.hip: stable sort of (key, position) pairs by key (see there)
 int dpaps_key_bits(int64_t num_keys);
 size_t dpaps_sort_scratch_bytes(int64_t n, int key_bits);
-int dpaps_sort_pairs(dpaps_ps *ps, const int64_t *keys, int64_t n, int key_bits, uint64_t *skeys, uint32_t *spos, void *scratch, hipStream_t st);
+int dpaps_sort_pairs(dpaps_ps *ps, const int64_t *keys, int64_t n, int key_bits, bool check, uint64_t *skeys, uint32_t *spos, void *scratch, hipStream_t st);
 
 int dpaps_side_stream(dpaps_ps *ps);   // creates the library's second stream and its events on first use
 int dpaps_fail_hip(dpaps_ps *ps, hipError_t e, const char *what);

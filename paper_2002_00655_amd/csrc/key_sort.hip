@@ -19,6 +19,9 @@
 //                      in lane order; the wavefronts' counters are then turned into
 //                      offsets in wavefront order, so that pairs of one bucket keep their
 //                      input order - the pass is stable - and every pair is stored.
+// Up to MID_MAX pairs the tiles are few and larger, and every workgroup of the scatter works out its offsets from all
+// tiles' counters itself: two launches per pass instead of four.  Up to FEW_MAX pairs one workgroup sorts them in LDS.
+// A caller that has not checked its keys asks for it: the first kernel then sets the handle's error, which ends the rest.
 // Integer work only: the result is the same bit for bit whatever the scheduling.
 #include "common.h"
 
@@ -34,7 +37,7 @@ __device__ __forceinline__ uint32_t digit_of(uint64_t key, int shift, uint32_t m
 // positions are the indices; otherwise the pairs come from the previous pass.
 template <int ITEMS, bool FIRST>
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_count(const int64_t *keys_in, const uint64_t *pk_in, int64_t n, int shift, int bits,
-                                                             int64_t num_tiles, uint32_t *hist, const int32_t *err) {
+                                                             int64_t num_tiles, uint32_t *hist, int64_t check_below, int32_t *err) {
     if (*(volatile const int32_t *)err) return;
     __shared__ uint32_t cnt[1 << SORT_MAX_BITS];
     const int R = 1 << bits;
@@ -47,6 +50,7 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_count(const int64_t *keys
         const int64_t q = base + (int64_t)r * SORT_THREADS + threadIdx.x;
         if (q < n) {
             const uint64_t k = FIRST ? (uint64_t)keys_in[q] : pk_in[q];
+            if (FIRST && check_below > 0 && k >= (uint64_t)check_below) atomicExch(err, PS_EKEY);
             atomicAdd(&cnt[digit_of(k, shift, mask)], 1u);
         }
     }
@@ -171,6 +175,158 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(const int64_t *ke
     }
 }
 
+// ---- up to MID_MAX pairs: counters tile by tile, every workgroup of the scatter sums them itself -------------------
+constexpr int MID_THREADS = 512, MID_WAVES = MID_THREADS / 64, MID_ITEMS = 4, MID_TILE = MID_THREADS * MID_ITEMS, MID_MAX_TILES = 64;
+constexpr int64_t MID_MAX = (int64_t)MID_TILE * MID_MAX_TILES;
+static_assert(2 * MID_THREADS >= 1 << SORT_MAX_BITS, "two buckets per thread");
+
+template <bool FIRST>
+__global__ __launch_bounds__(MID_THREADS) void k_sort_mid_count(const int64_t *keys_in, const uint64_t *pk_in, int64_t n, int shift, int bits,
+                                                                uint32_t *hist, int64_t check_below, int32_t *err) {
+    if (*(volatile const int32_t *)err) return;
+    __shared__ uint32_t cnt[1 << SORT_MAX_BITS];
+    const int R = 1 << bits, tid = threadIdx.x;
+    const uint32_t mask = (uint32_t)R - 1u;
+    for (int i = tid; i < R; i += MID_THREADS) cnt[i] = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)blockIdx.x * MID_TILE;
+#pragma unroll
+    for (int r = 0; r < MID_ITEMS; ++r) {
+        const int64_t q = base + r * MID_THREADS + tid;
+        if (q < n) {
+            const uint64_t k = FIRST ? (uint64_t)keys_in[q] : pk_in[q];
+            if (FIRST && check_below > 0 && k >= (uint64_t)check_below) atomicExch(err, PS_EKEY);
+            atomicAdd(&cnt[digit_of(k, shift, mask)], 1u);
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < R; i += MID_THREADS) hist[(int64_t)blockIdx.x * R + i] = cnt[i];
+}
+
+template <bool FIRST>
+__global__ __launch_bounds__(MID_THREADS) void k_sort_mid_scatter(const int64_t *keys_in, const uint64_t *pk_in, const uint32_t *pp_in, int64_t n,
+                                                                  int shift, int bits, const uint32_t *hist, uint64_t *pk_out, uint32_t *pp_out,
+                                                                  const int32_t *err) {
+    if (*(volatile const int32_t *)err) return;
+    __shared__ __attribute__((aligned(8))) uint32_t wh[MID_WAVES][1 << SORT_MAX_BITS];
+    __shared__ uint32_t wave_sum[MID_WAVES];
+    const int R = 1 << bits, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tile = blockIdx.x, tiles = gridDim.x;
+    const uint32_t mask = (uint32_t)R - 1u;
+    // this thread's two buckets: pairs in all tiles, and in the tiles before this one
+    uint2 total = make_uint2(0u, 0u), before_tile = total;
+    if (2 * tid < R) {
+#pragma unroll 16
+        for (int t = 0; t < tiles; ++t) {
+            const uint2 v = *reinterpret_cast<const uint2 *>(&hist[(int64_t)t * R + 2 * tid]);
+            total.x += v.x; total.y += v.y;
+            if (t < tile) { before_tile.x += v.x; before_tile.y += v.y; }
+        }
+    }
+    for (int i = tid; i < MID_WAVES * (1 << SORT_MAX_BITS); i += MID_THREADS) (&wh[0][0])[i] = 0;
+    __syncthreads();
+    const int64_t base = (int64_t)tile * MID_TILE + (int64_t)wave * 64 * MID_ITEMS;
+    uint64_t key[MID_ITEMS];
+    uint32_t pos[MID_ITEMS], rank[MID_ITEMS];
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int r = 0; r < MID_ITEMS; ++r) {
+        const int64_t q = base + r * 64 + lane;
+        const bool valid = q < n;
+        key[r] = valid ? (FIRST ? (uint64_t)keys_in[q] : pk_in[q]) : 0;
+        pos[r] = valid ? (FIRST ? (uint32_t)q : pp_in[q]) : 0u;
+    }
+#pragma unroll
+    for (int r = 0; r < MID_ITEMS; ++r) {
+        const bool valid = base + r * 64 + lane < n;
+        const uint32_t d = digit_of(key[r], shift, mask);
+        uint64_t same = __ballot(valid);
+        for (int b = 0; b < bits; ++b) {
+            const bool bit = ((d >> b) & 1u) != 0u;
+            const uint64_t v = __ballot(valid && bit);
+            same &= bit ? v : ~v;
+        }
+        uint32_t before = 0;
+        const int leader = valid ? __ffsll((long long)same) - 1 : lane;
+        if (valid && lane == leader) {
+            before = wh[wave][d];
+            wh[wave][d] = before + (uint32_t)__popcll(same);
+        }
+        before = (uint32_t)__shfl((int)before, leader);
+        rank[r] = before + (uint32_t)__popcll(same & below);
+    }
+    // the pairs in lower buckets: a scan over the buckets' totals
+    const uint32_t both = total.x + total.y;
+    uint32_t incl = both;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)incl, off);
+        if (lane >= off) incl += y;
+    }
+    if (lane == 63) wave_sum[wave] = incl;
+    __syncthreads();
+    uint32_t lower = incl - both;
+    for (int w = 0; w < wave; ++w) lower += wave_sum[w];
+    // a wavefront's counters become the offsets of its first pair of each bucket
+    if (2 * tid < R) {
+        uint32_t run0 = lower + before_tile.x, run1 = lower + total.x + before_tile.y;
+#pragma unroll
+        for (int w = 0; w < MID_WAVES; ++w) {
+            uint2 *at = reinterpret_cast<uint2 *>(&wh[w][2 * tid]);
+            const uint2 c = *at;
+            *at = make_uint2(run0, run1);
+            run0 += c.x; run1 += c.y;
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < MID_ITEMS; ++r) {
+        if (base + r * 64 + lane < n) {
+            const uint32_t dst = wh[wave][digit_of(key[r], shift, mask)] + rank[r];
+            pk_out[dst] = key[r];
+            pp_out[dst] = pos[r];
+        }
+    }
+}
+
+// ---- up to FEW_MAX pairs: one workgroup, a bitonic network over key << FEW_BITS | position in LDS -----------------
+// A thread takes one comparison of every step.  Up to a distance of 64 a wavefront's comparisons stay within its 128
+// numbers, and LDS serves a wavefront's accesses in order: only longer distances need a barrier.
+constexpr int FEW_BITS = 11, FEW_MAX = 1 << FEW_BITS, FEW_THREADS = FEW_MAX / 2;
+__global__ __launch_bounds__(FEW_THREADS) void k_sort_few(const int64_t *keys, int n, uint64_t *skeys, uint32_t *spos, int64_t check_below, int32_t *err) {
+    if (*(volatile const int32_t *)err) return;
+    __shared__ uint64_t x[FEW_MAX];
+    const int tid = threadIdx.x;
+    int N = 128;
+    while (N < n) N <<= 1;
+    bool bad = false;
+    for (int i = tid; i < N; i += FEW_THREADS) {
+        const uint64_t k = i < n ? (uint64_t)keys[i] : 0;
+        bad |= i < n && check_below > 0 && k >= (uint64_t)check_below;
+        x[i] = i < n ? (k << FEW_BITS) | (uint64_t)i : ~0ull;
+    }
+    if (__syncthreads_or(bad ? 1 : 0)) {
+        if (tid == 0) atomicExch(err, PS_EKEY);
+        return;
+    }
+    for (int k = 2; k <= N; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            if (2 * tid < N) {
+                const int i = ((tid & -j) << 1) | (tid & (j - 1));      // (j: a power of two)
+                const uint64_t a = x[i], b = x[i + j];
+                const bool up = (i & k) == 0;
+                if ((a > b) == up) { x[i] = b; x[i + j] = a; }
+            }
+            __asm__ volatile("" ::: "memory");
+            // the next step reads what other wavefronts wrote: this one, or the next, reaches past 64
+            if (j > 64 || (j == 1 && k >= 128)) __syncthreads();
+        }
+    }
+    __syncthreads();
+    for (int i = tid; i < n; i += FEW_THREADS) {
+        skeys[i] = x[i] >> FEW_BITS;
+        spos[i] = (uint32_t)x[i] & (FEW_MAX - 1);
+    }
+}
+
 inline size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct SortPlan {
@@ -204,8 +360,10 @@ SortPlan sort_plan(int64_t n, int key_bits) {
     return p;
 }
 
+// ITEMS 0: up to MID_MAX pairs
 template <int ITEMS>
-int sort_run(dpaps_ps *ps, const SortPlan &p, const int64_t *keys, int64_t n, uint64_t *skeys, uint32_t *spos, void *scratch, hipStream_t st) {
+int sort_run(dpaps_ps *ps, const SortPlan &p, const int64_t *keys, int64_t n, int64_t check_below, uint64_t *skeys, uint32_t *spos, void *scratch,
+             hipStream_t st) {
     uint64_t *alt_k = (uint64_t *)((char *)scratch + p.off_pk);
     uint32_t *alt_p = (uint32_t *)((char *)scratch + p.off_pp);
     uint32_t *hist = (uint32_t *)((char *)scratch + p.off_hist);
@@ -217,16 +375,26 @@ int sort_run(dpaps_ps *ps, const SortPlan &p, const int64_t *keys, int64_t n, ui
     int shift = 0;
     for (int i = 0; i < p.passes; ++i) {
         const int bits = p.bits[i], R = 1 << bits;
-        if (i == 0) k_sort_count<ITEMS, true><<<tiles, SORT_THREADS, 0, st>>>(keys, nullptr, n, shift, bits, p.num_tiles, hist, ps->err);
-        else k_sort_count<ITEMS, false><<<tiles, SORT_THREADS, 0, st>>>(nullptr, in_k, n, shift, bits, p.num_tiles, hist, ps->err);
-        PS_HIP(ps, hipGetLastError());
-        k_sort_rowsum<<<R, 256, 0, st>>>(hist, p.num_tiles, tot, ps->err);
-        PS_HIP(ps, hipGetLastError());
-        k_sort_scan<<<R, 256, 0, st>>>(hist, p.num_tiles, tot, ps->err);
-        PS_HIP(ps, hipGetLastError());
-        if (i == 0) k_sort_scatter<ITEMS, true><<<tiles, SORT_THREADS, 0, st>>>(keys, nullptr, nullptr, n, shift, bits, p.num_tiles, hist, out_k, out_p, ps->err);
-        else k_sort_scatter<ITEMS, false><<<tiles, SORT_THREADS, 0, st>>>(nullptr, in_k, in_p, n, shift, bits, p.num_tiles, hist, out_k, out_p, ps->err);
-        PS_HIP(ps, hipGetLastError());
+        if constexpr (ITEMS == 0) {
+            const unsigned mid = (unsigned)((n + MID_TILE - 1) / MID_TILE);
+            if (i == 0) k_sort_mid_count<true><<<mid, MID_THREADS, 0, st>>>(keys, nullptr, n, shift, bits, hist, check_below, ps->err);
+            else k_sort_mid_count<false><<<mid, MID_THREADS, 0, st>>>(nullptr, in_k, n, shift, bits, hist, 0, ps->err);
+            PS_HIP(ps, hipGetLastError());
+            if (i == 0) k_sort_mid_scatter<true><<<mid, MID_THREADS, 0, st>>>(keys, nullptr, nullptr, n, shift, bits, hist, out_k, out_p, ps->err);
+            else k_sort_mid_scatter<false><<<mid, MID_THREADS, 0, st>>>(nullptr, in_k, in_p, n, shift, bits, hist, out_k, out_p, ps->err);
+            PS_HIP(ps, hipGetLastError());
+        } else {
+            if (i == 0) k_sort_count<ITEMS, true><<<tiles, SORT_THREADS, 0, st>>>(keys, nullptr, n, shift, bits, p.num_tiles, hist, check_below, ps->err);
+            else k_sort_count<ITEMS, false><<<tiles, SORT_THREADS, 0, st>>>(nullptr, in_k, n, shift, bits, p.num_tiles, hist, 0, ps->err);
+            PS_HIP(ps, hipGetLastError());
+            k_sort_rowsum<<<R, 256, 0, st>>>(hist, p.num_tiles, tot, ps->err);
+            PS_HIP(ps, hipGetLastError());
+            k_sort_scan<<<R, 256, 0, st>>>(hist, p.num_tiles, tot, ps->err);
+            PS_HIP(ps, hipGetLastError());
+            if (i == 0) k_sort_scatter<ITEMS, true><<<tiles, SORT_THREADS, 0, st>>>(keys, nullptr, nullptr, n, shift, bits, p.num_tiles, hist, out_k, out_p, ps->err);
+            else k_sort_scatter<ITEMS, false><<<tiles, SORT_THREADS, 0, st>>>(nullptr, in_k, in_p, n, shift, bits, p.num_tiles, hist, out_k, out_p, ps->err);
+            PS_HIP(ps, hipGetLastError());
+        }
         in_k = out_k; in_p = out_p;
         out_k = in_k == skeys ? alt_k : skeys;
         out_p = in_p == spos ? alt_p : spos;
@@ -248,10 +416,17 @@ int dpaps_key_bits(int64_t num_keys) {
 size_t dpaps_sort_scratch_bytes(int64_t n, int key_bits) { return sort_plan(n, key_bits).bytes; }
 
 // skeys[q], spos[q] (n each) <- the pairs (keys[p], p) ordered by key, equal keys by p.  Keys must be in
-// [0, 2^key_bits) (the kernels do nothing once the handle's error flag is set, which the key check before sets
-// for a key out of range).  Allocates nothing; asynchronous on st.
-int dpaps_sort_pairs(dpaps_ps *ps, const int64_t *keys, int64_t n, int key_bits, uint64_t *skeys, uint32_t *spos, void *scratch, hipStream_t st) {
+// [0, 2^key_bits) - or `check` is asked for: a key outside [0, num_keys) then sets the handle's error, and the kernels do
+// nothing once it is set.  Allocates nothing; asynchronous on st.
+int dpaps_sort_pairs(dpaps_ps *ps, const int64_t *keys, int64_t n, int key_bits, bool check, uint64_t *skeys, uint32_t *spos, void *scratch, hipStream_t st) {
     if (n <= 0) return PS_OK;
+    const int64_t check_below = check ? ps->K : 0;
+    if (n <= FEW_MAX && key_bits + FEW_BITS < 64) {
+        k_sort_few<<<1, FEW_THREADS, 0, st>>>(keys, (int)n, skeys, spos, check_below, ps->err);
+        PS_HIP(ps, hipGetLastError());
+        return PS_OK;
+    }
     const SortPlan p = sort_plan(n, key_bits);
-    return p.items == 4 ? sort_run<4>(ps, p, keys, n, skeys, spos, scratch, st) : sort_run<16>(ps, p, keys, n, skeys, spos, scratch, st);
+    if (n <= MID_MAX) return sort_run<0>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
+    return p.items == 4 ? sort_run<4>(ps, p, keys, n, check_below, skeys, spos, scratch, st) : sort_run<16>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
 }
