@@ -9,9 +9,9 @@
  * call.  `stream` is a hipStream_t (NULL = the null stream).  Calls are
  * asynchronous on that stream and take effect in stream order, which is the
  * program order of one client (Sec. 3.4, "Asynchronous operations"); one
- * handle must not be driven from two streams at once.  Some calls put part of
- * their work (statistics, a sort) on a second stream that the library creates
- * at default priority; that work starts after what precedes the call on
+ * handle must not be driven from two streams at once.  The knowledge-graph calls put part of
+ * their work (a sort; an epoch also its localize calls and statistics) on a second stream that the library
+ * creates at default priority; that work starts after what precedes the call on
  * `stream` and `stream` waits for it before the call's effects are complete, so
  * the order seen on `stream` is unchanged.
  *
@@ -92,7 +92,9 @@ enum {
 enum {
     PS_OPT_MF_EXACT = 1,        /* 1: the SGD kernel sums each inner product in index order with separately
                                    rounded multiplies and adds (slow; for bit-for-bit checks).  default 0 */
-    PS_OPT_MF_CACHE_ROWS = 2,   /* upper bound on row factors a workgroup keeps in LDS (-1 = as many as fit) */
+    PS_OPT_MF_CACHE_ROWS = 2,   /* upper bound on row factors a workgroup keeps in LDS (-1 = as many as fit);
+                                   0 or more also makes the grouped kernel take the entries outside long column runs row by
+                                   row instead of level by level */
     PS_OPT_MF_WAVES = 3,        /* wavefronts per workgroup in the SGD kernel: 1..16, or 0 (default): 16, but 12 for the
                                    grouped kernel on data with very long column runs or mostly one entry per row
                                    and block */
@@ -163,8 +165,7 @@ int ps_push(ps_handle ps, int32_t worker, const int64_t *keys, int64_t n, const 
  * the call makes no hipMalloc / hipFree and calls no allocating routine: its scratch (sorted pairs, the sort's
  * buffers, partial sums) is a fixed array of 16 MiB in device memory, one per device the library runs on, held
  * until the process ends.  Limits (PS_ELIMIT, nothing changed): n <= PS_PUSH_NOALLOC_MAX_KEYS and
- * ceil(n / 64) * value_len <= PS_PUSH_NOALLOC_MAX_PARTIAL.  The statistics run on `stream` itself (no second
- * stream).  All calls on one device share that device's array, whatever the handle: calls that overlap on one
+ * ceil(n / 64) * value_len <= PS_PUSH_NOALLOC_MAX_PARTIAL.  All calls on one device share that device's array, whatever the handle: calls that overlap on one
  * device (two streams, two handles) race; the array keeps the last call's contents and every call overwrites
  * what it reads.  No memset nodes are issued, so the call may be captured into a graph. */
 #define PS_PUSH_NOALLOC_MAX_KEYS 262144
