@@ -32,8 +32,8 @@ HBM_PEAK_GBS = 8000.0     # MI355X HBM3E, published
 # counters read for a plain 1 GiB copy; summaries under profiles/).  Only valid for the kernel sources they were
 # taken with and for the default settings of the workload: bytes read, bytes written.
 KERNEL_SOURCES = ("mf_sgd_chunk.hip", "mf_sgd.hip", "mf_device.h", "common.h")
-TRAFFIC = {"kernel_sha256_16": "b7ddbd8b5d104008",
-           "bytes_per_launch": {"large": (147068367.0, 125882961.0), "wide": (1324683903.0, 953180179.0)}}
+TRAFFIC = {"kernel_sha256_16": "9f3be4503eba525b",
+           "bytes_per_launch": {"large": (196044390.4, 127389696.0), "wide": (1324613427.2, 953154252.8)}}
 
 # block boundaries per workload: a column of a block weighs this many entries on top of its own (see --col-cost)
 COL_COST = {"wide": 3.0}
