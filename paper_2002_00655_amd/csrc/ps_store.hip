@@ -2,6 +2,7 @@
 // localize and the integer routing statistics (Table "Primitives", Sec. 3.1-3.3,
 // Sec. 3.5, Sec. 3.7 of the paper).
 #include "common.h"
+#include "together.h"
 
 #include <cstdio>
 #include <cstring>
@@ -254,20 +255,6 @@ __global__ __launch_bounds__(256) void k_route_access(RouteArgs a, const int32_t
     route_access_block(a, l, blockIdx.x);
 }
 
-// Whether one of the keys is out of range, for calls of few keys: every workgroup of the call's one kernel looks at
-// all of them before it does anything, so that a bad call changes nothing.  Sets the error; the same in all threads.
-constexpr int64_t FEW_KEYS = 2048;
-__device__ __forceinline__ bool few_keys_bad(const int64_t *keys, int64_t n, int64_t K, int32_t *err) {
-    bool bad = false;
-    for (int64_t p = threadIdx.x; p < n; p += blockDim.x) {
-        const int64_t k = keys[p];
-        bad |= k < 0 || k >= K;
-    }
-    const bool any = __syncthreads_or(bad ? 1 : 0) != 0;
-    if (any && threadIdx.x == 0) atomicExch(err, PS_EKEY);
-    return any;
-}
-
 // The replies of a pull or push have arrived: the requester's node knows the owner of every remote key it asked
 // for (Sec. 3.3: the caches change without messages of their own).  Several mentions of a key write the same.
 __global__ void k_cache_replies(const int64_t *keys, int64_t n, int32_t worker, const int32_t *owner, int16_t *loc_row, const int32_t *err) {
@@ -285,8 +272,7 @@ __global__ void k_cache_replies(const int64_t *keys, int64_t n, int32_t worker, 
 __global__ __launch_bounds__(256) void k_localize(const int64_t *keys, int64_t n, int32_t worker, int32_t *owner, int64_t per_home, int32_t W,
                                                    uint32_t *named, uint32_t *stamp_pair, uint32_t call_id, u64 *stats,
                                                    int16_t *loc, int64_t K, bool few, int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
-    if (few && few_keys_bad(keys, n, K, err)) return;
+    if (few ? few_keys_off(keys, n, K, err) : *(volatile const int32_t *)err != 0) return;
     __shared__ RouteLds l;
     route_lds_init(l, W);
     const double inv_per_home = 1.0 / (double)per_home;
@@ -325,8 +311,7 @@ __global__ __launch_bounds__(256) void k_localize(const int64_t *keys, int64_t n
 }
 
 __global__ __launch_bounds__(256) void k_owner(const int64_t *keys, int64_t n, const int32_t *owner, int32_t *out, int64_t K, bool few, int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
-    if (few && few_keys_bad(keys, n, K, err)) return;
+    if (few ? few_keys_off(keys, n, K, err) : *(volatile const int32_t *)err != 0) return;
     int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (p < n) out[p] = owner[keys[p]];
 }
@@ -350,8 +335,8 @@ constexpr int64_t PULL_STREAM_BYTES = (int64_t)128 << 20;
 template <class Piece, int AHEAD, bool STREAM>
 __global__ __launch_bounds__(256) void k_pull(RouteArgs route, const int64_t *keys, int64_t n, uint32_t P, double inv_P, const Piece *val, Piece *out,
                                               int64_t K, int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
-    if (n <= FEW_KEYS && few_keys_bad(keys, n, K, err)) return;
+    // (of a larger call the flag was set, or not, by the launch before)
+    if (n <= FEW_KEYS ? few_keys_off(keys, n, K, err) : *(volatile const int32_t *)err != 0) return;
     __shared__ RouteLds l;
     if ((int)blockIdx.x < route.blocks) { route_access_block(route, l, blockIdx.x); return; }
     const int64_t block = blockIdx.x - route.blocks;
@@ -514,8 +499,7 @@ __global__ __launch_bounds__(256) void k_push_ranges(RouteArgs route, PushDone d
 // last workgroup counts the statistics.
 __global__ __launch_bounds__(64) void k_push_tiny(RouteArgs route, const int64_t *keys, int n, int32_t L, const float *deltas, float *val, int64_t K,
                                                   int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
-    if (few_keys_bad(keys, n, K, err)) return;
+    if (few_keys_off(keys, n, K, err)) return;
     __shared__ RouteLds l;
     if (route.blocks && blockIdx.x == gridDim.x - 1) { route_access_block(route, l, 0); return; }
     const int lane = threadIdx.x;

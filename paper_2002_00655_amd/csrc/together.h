@@ -1,0 +1,23 @@
+// Decisions to leave that a workgroup takes as a whole.  The handle's error flag may be set by other workgroups of the
+// same launch at any moment, so wavefronts that look at it one by one can see different values; where the rest of a
+// kernel needs every thread (shares of a check, a barrier, tables filled together), one answer must hold for all.
+#pragma once
+#include <stdint.h>
+
+#include "dpaps.h"
+
+// Whether a call of few keys is to do nothing: a key is out of range, or the flag is set.  Every workgroup of the call's
+// one kernel looks at all of the keys before it does anything else, so that a bad call changes nothing, and no thread
+// leaves before all have looked.  Sets the error; the same in all threads.
+constexpr int64_t FEW_KEYS = 2048;
+__device__ __forceinline__ bool few_keys_off(const int64_t *keys, int64_t n, int64_t K, int32_t *err) {
+    const bool was_off = *(volatile const int32_t *)err != 0;
+    bool off = was_off;
+    for (int64_t p = threadIdx.x; p < n; p += blockDim.x) {
+        const int64_t k = keys[p];
+        off |= k < 0 || k >= K;
+    }
+    const bool any = __syncthreads_or(off ? 1 : 0) != 0;
+    if (any && threadIdx.x == 0 && !was_off) atomicExch(err, PS_EKEY);     // (an error that stands already is kept)
+    return any;
+}

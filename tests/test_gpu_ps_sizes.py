@@ -129,3 +129,30 @@ def test_rows_named_once_are_updated_in_place(dim, ns, no, batch, stray):
     assert np.abs(b1 - b0).max() <= 2e-5 and s1 == s0
     for x, y in zip(l1, l0):
         assert x is None or abs(x - y) <= 1e-6 * abs(x)
+
+
+@pytest.mark.parametrize("n", [300, 2048])
+def test_a_bad_key_is_seen_by_every_workgroup_of_a_call(n):
+    """Calls of few keys in hundreds of workgroups, which set the error while others start: none may miss the bad key."""
+    import torch
+    from paper_2002_00655_amd import ps as P
+    K, L = 3000, 1024
+    srv = P.ParameterServer(K, L, 300)
+    rng = np.random.default_rng(n)
+    good = rng.integers(0, K, size=n)
+    before = srv.stats()
+    out, own = torch.full((n, L), 7.0, device="cuda"), torch.full((n,), 7, dtype=torch.int32, device="cuda")
+    for place in (0, 63, 64, 200, n - 1):
+        print(f"case n={n} place={place}", flush=True)
+        keys = good.copy()
+        keys[place] = K
+        kt = torch.from_numpy(keys).cuda()
+        for call in (lambda: srv.pull(kt, 2, out=out), lambda: srv.localize(kt, 2), lambda: srv.owner(kt)):
+            call()
+            with pytest.raises(P.PSError) as e:
+                srv.status()
+            assert e.value.code == P.PS_EKEY
+    assert (out == 7.0).all() and srv.stats() == before
+    kt = torch.from_numpy(good).cuda()
+    srv.pull(kt, 2, out=out)
+    assert (out == 0.0).all() and np.array_equal(srv.owner(kt).cpu().numpy(), good // (K // 300))
