@@ -14,6 +14,7 @@
 // numbers: [0, D) real parts, [D, 2 D) imaginary parts, [2 D, 4 D) the AdaGrad
 // accumulators of those 2 D numbers.
 #include "common.h"
+#include "kge_slots.h"
 #include "mf_device.h"
 
 #include <algorithm>
@@ -21,25 +22,9 @@
 
 static inline unsigned grid_for(int64_t n, int block) { return (unsigned)((n + block - 1) / block); }
 
-// Slot j of data point b - subject, relation, object, subject negatives, object negatives - in pull and push order
-struct KgeBatch {
-    const int32_t *subj, *rel, *obj, *neg_subj, *neg_obj;
-    int32_t ns, no;
-    int64_t num_entities, batch;
-};
-__device__ __forceinline__ int64_t slot_key(const KgeBatch &t, int64_t b, int32_t j) {
-    if (j == 0) return t.subj[b];
-    if (j == 1) return t.num_entities + t.rel[b];
-    if (j == 2) return t.obj[b];
-    if (j < 3 + t.ns) return t.neg_subj[b * t.ns + (j - 3)];
-    return t.neg_obj[b * t.no + (j - 3 - t.ns)];
-}
-
 // The keys of the batch; check_below > 0: checked, before anything indexes the store with them.  seen (may be NULL): which
-// slots share their key with another slot of the batch is worked out as well - every slot but the relations' leaves its
-// number at its key, and where it finds one of this step (the id in front), both are flagged: shared[slot] = id.
-// (A key named a thousand times is a thousand exchanges on one word: the relations are left out, and the call does
-// without where that could be many of the others' keys, see in_place_step.)
+// slots share their key with another slot of the batch is worked out as well (kge_mark_slot); the call does without where
+// that could be many, see in_place_step.
 // ent (may be NULL): the keys of the subjects, objects and negatives of another `ent_batch` triples, from triple
 // ent_first on, which the caller localizes next.
 __device__ __forceinline__ int64_t entity_key(const KgeBatch &t, int64_t b, int32_t j) { return slot_key(t, b, j == 0 ? 0 : j + 1); }
@@ -53,11 +38,7 @@ __global__ void k_kge_keys(KgeBatch t, int64_t *keys, int64_t check_below, u64 *
         const bool bad = check_below > 0 && (k < 0 || k >= check_below);
         if (bad) atomicExch(err, PS_EKEY);
         keys[i] = k;
-        if (seen && !bad && i - b * rows != 1) {
-            const u64 old = atomicExch(&seen[k], ((u64)id << 32) | (u64)(uint32_t)i);
-            if ((uint32_t)(old >> 32) == id) { shared[i] = id; shared[(uint32_t)old] = id; }
-            if (k >= t.num_entities) shared[i] = id;                   // (an entity number past the entities may be a relation's key)
-        }
+        if (seen && !bad) kge_mark_slot(t.num_entities, (uint32_t)i, (int32_t)(i - b * rows), k, seen, shared, id);
     }
     const int32_t ents = 2 + ent.ns + ent.no;
     if (i < ent.batch * ents) {

@@ -156,3 +156,30 @@ def test_a_bad_key_is_seen_by_every_workgroup_of_a_call(n):
     kt = torch.from_numpy(good).cuda()
     srv.pull(kt, 2, out=out)
     assert (out == 0.0).all() and np.array_equal(srv.owner(kt).cpu().numpy(), good // (K // 300))
+
+
+def test_a_relation_number_below_zero_shares_an_entity_key():
+    """Only the key as a whole has to be in range: a relation number -j names entity E - j.  A negative elsewhere that names
+    it is not alone.  Two steps against the same steps with the push's sums only (its sequential order): same bits, since no key
+    has more than two terms, and (value + a) + b is what both orders add."""
+    import torch
+    from paper_2002_00655_amd import ps as P
+    E, R, dim, ns, no, batch = 30_000, 200, 40, 4, 4, 400
+    rng = np.random.default_rng(21)
+    K = E + R
+    ids = rng.permutation(E)[:batch * (2 + ns + no)].reshape(batch, -1)     # every entity once
+    subj, obj, negs, nego = ids[:, 0], ids[:, 1], ids[:, 2:2 + ns].copy(), ids[:, 2 + ns:].copy()
+    rel = np.arange(batch) % R
+    rel[:200] = negs[200:, 0] - E                                           # keys of negatives of other data points
+    init = np.concatenate([rng.standard_normal((K, 2 * dim)) * 0.1, np.full((K, 2 * dim), 0.01)], 1).astype(np.float32)
+    t = [torch.from_numpy(np.ascontiguousarray(x.astype(np.int32))).cuda() for x in (subj, rel, obj, negs, nego)]
+    got = []
+    for sequential in (1, 0):
+        print(f"case sequential={sequential}", flush=True)
+        srv = P.ParameterServer(K, 4 * dim, 3)
+        srv.push(torch.arange(K, device="cuda"), torch.from_numpy(init).cuda())
+        srv.set_option(P.OPT_PUSH_SEQUENTIAL, sequential)
+        losses = [srv.kge_sgd_step(E, dim, *t, 0.1, 1e-10, 1) for _ in range(2)]
+        srv.status()
+        got.append((srv.pull(torch.arange(K, device="cuda")).cpu().numpy()[:E], losses, srv.stats()))
+    assert np.array_equal(got[0][0].view(np.uint32), got[1][0].view(np.uint32)) and got[0][1:] == got[1][1:]
