@@ -43,6 +43,7 @@
 // runs lead the block), and the row's ticket tells when they are done.
 #include "common.h"
 #include "mf_device.h"
+#include "together.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -126,9 +127,8 @@ __device__ __forceinline__ void solve_first() { __asm__ volatile("s_nop 4"); }
 // SCHED: the second part by levels (see there), for data whose blocks have their non-heavy columns fit in LDS.
 template <int NT, bool A4, bool AGENT_H, bool LONG_RUNS, bool SCHED, bool RICH = false>
 __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const int32_t worker, const int32_t rb, const int32_t cb) {
-    if constexpr (!AGENT_H) {     // (in the loop, the caller looks: there all threads must take the same way)
-        if (__hip_atomic_load(a.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
-    }
+    __shared__ int stopped;       // (in the loop, the caller looks)
+    if constexpr (!AGENT_H) look_for_all(a.err, &stopped);
     constexpr int RS = 16 * NT + 4;          // row stride of the staging area in floats (conflict-free for both read patterns)
     constexpr int NV = (NT + 3) / 4;         // 64-component slices of a row
     // Called in a loop (AGENT_H): the thread's number, the rank and the step sizes pass through empty asm
@@ -229,6 +229,12 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
         cpow[pw] = (float)x; cpm1[pw] = (float)(x - 1.0); cim1[pw] = (float)(1.0 / x - 1.0);
     }
 
+    // Nothing has been written yet.  All threads go on or none: the tables in LDS are filled together, and a level's entries
+    // are dealt out to all wavefronts.
+    if constexpr (!AGENT_H) {
+        __syncthreads();
+        if (stopped != 0) return;
+    }
     if (a.fuse_localize) {
         // the localize step of this task (Sec. 2.3), which makes every parameter the worker will touch its own
         LocalizeArgs la{a.tasks, a.owner_w, a.row_bounds, a.col_bounds, a.m, a.per_home, a.W, a.stats, a.err};

@@ -21,3 +21,8 @@ __device__ __forceinline__ bool few_keys_off(const int64_t *keys, int64_t n, int
     if (any && threadIdx.x == 0 && !was_off) atomicExch(err, PS_EKEY);     // (an error that stands already is kept)
     return any;
 }
+
+// One thread's look at the flag, for the whole workgroup: what stands in `word` (in LDS) after the next barrier holds for all.
+__device__ __forceinline__ void look_for_all(const int32_t *err, int *word) {
+    if (threadIdx.x == 0) *word = *(volatile const int32_t *)err;
+}

@@ -41,8 +41,8 @@ static int atomicExch(int *p, int v) { sets = v; return 0; }
 #include "together.h"
 
 int main(int argc, char **argv) {
-    // argv: old form (1) or not (0); number of keys; the bad one's place (-1: none); the flag as the threads see it, bit by bit
-    const bool old = atoi(argv[1]); const int n = atoi(argv[2]), bad = atoi(argv[3]); const char *sees = argv[4];
+    // argv: old form (1), not (0), or one thread's look for all (2); number of keys; the bad one's place (-1: none); the flag as the threads see it, bit by bit
+    const int form = atoi(argv[1]), n = atoi(argv[2]), bad = atoi(argv[3]); const char *sees = argv[4];
     const int T = 8;
     blockDim.x = T; running = T;
     std::vector<int64_t> keys(n, 5);
@@ -52,7 +52,8 @@ int main(int argc, char **argv) {
     for (int t = 0; t < T; ++t) ts.emplace_back([&, t] {
         threadIdx.x = t;
         int32_t flag = sees[t] == '1' ? -10 : 0, clear = 0;
-        if (old) { if (!flag) went_on[t] = !few_keys_off(keys.data(), n, 10, &clear); }
+        if (form == 2) { static int word; look_for_all(&flag, &word); __syncthreads_or(0); went_on[t] = word == 0; }
+        else if (form == 1) { if (!flag) went_on[t] = !few_keys_off(keys.data(), n, 10, &clear); }
         else went_on[t] = !few_keys_off(keys.data(), n, 10, &flag);
         leave();
     });
@@ -90,6 +91,11 @@ def test_a_call_of_few_keys_goes_on_with_all_threads_or_none(model, n):
             assert err == (-2 if sees[0] == "0" else 0)        # the error is set where it did not stand
     # an earlier error: every thread sees it, nothing is done and it is kept
     assert model(False, n, -1, "11111111") == (0, 0)
+
+
+@pytest.mark.parametrize("sees", ["00000000", "01100000", "10000000", "11111110", "11111111"])
+def test_one_look_at_the_flag_holds_for_all(model, sees):
+    assert model(2, 0, -1, sees)[0] == (8 if sees[0] == "0" else 0)
 
 
 def test_leaving_one_by_one_would_let_a_bad_key_pass(model):
