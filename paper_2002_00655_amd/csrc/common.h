@@ -2,7 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
-#include <stdint.h>
+#include <cstdint>
 #include <string>
 #include <vector>
 
@@ -128,6 +128,8 @@ struct dpaps_ps {
     u64 *kge_seen = nullptr;          // K: the last slot that named the key, with its step's id in front (see k_kge_keys)
     uint32_t *kge_shared = nullptr;   // two steps' flags, one per slot
     size_t kge_shared_slots = 0;
+    bool kge_seen_refused = false;    // there was no memory for the marks,
+    size_t kge_shared_refused = SIZE_MAX;   // or for flags of this many slots
     uint32_t kge_id = 0;
     int16_t *loc = nullptr;           // location caches (PS_OPT_LOCATION_CACHES): W x K, node n's belief where key k is, -1 none
     void *handoff_ws = nullptr;       // column block states and the recorded order of mf_sgd_epoch_handoff (grows)
@@ -220,6 +222,7 @@ size_t dpaps_sort_scratch_bytes(int64_t n, int key_bits);
 int dpaps_sort_pairs(dpaps_ps *ps, const int64_t *keys, int64_t n, int key_bits, bool check, uint64_t *skeys, uint32_t *spos, void *scratch, hipStream_t st);
 
 int dpaps_side_stream(dpaps_ps *ps);   // creates the library's second stream and its events on first use
+int dpaps_zero_words(uint32_t *p, size_t words, hipStream_t st);
 int dpaps_fail_hip(dpaps_ps *ps, hipError_t e, const char *what);
 int dpaps_ws_reserve(dpaps_ps *ps, size_t bytes);
 

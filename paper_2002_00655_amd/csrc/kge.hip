@@ -270,34 +270,44 @@ __global__ __launch_bounds__(256) void k_kge_loss_sum(const double *loss, int64_
     if (threadIdx.x == 0) *out = s[0];
 }
 
+// *p <- `words` words of device memory, zero once st has passed this point; NULL if that cannot be had.  True: the memory was refused.
+template <class T>
+static bool zeroed(T **p, size_t words, hipStream_t st) {
+    *p = nullptr;
+    if (hipMalloc((void **)p, words * sizeof(uint32_t)) != hipSuccess) { (void)hipGetLastError(); *p = nullptr; return true; }
+    if (dpaps_zero_words((uint32_t *)*p, words, st)) { (void)hipFree(*p); *p = nullptr; }
+    return false;
+}
+
 // Whether a step updates the rows of keys that are named once in place (see k_kge_group), and its flags then.  It pays
 // where most negatives are alone: drawn from more entities than twice the batch's negatives, three quarters and more
 // are.  Not where the terms are to be added strictly one after the other, nor for rows so short that the
 // bookkeeping (8 bytes a key) would weigh.  Steps take turns with two sets of flags: the flags of one may be in use while the
-// next one's are written.  most: the data points of the call's largest batch.
-static bool in_place_step(dpaps_ps *ps, const KgeBatch &t, int64_t most, PushDone &done) {
+// next one's are written.  most: the data points of the call's largest batch.  st: the stream of the keys' kernel, which
+// the work of earlier calls precedes: marks and flags are made and cleared there.  Where there is no memory for them the
+// step does without, and what was refused once is not asked for again.
+static bool in_place_step(dpaps_ps *ps, const KgeBatch &t, int64_t most, hipStream_t st, PushDone &done) {
     done = PushDone{};
     const int64_t negatives = t.batch * (t.ns + t.no), slots = most * (3 + t.ns + t.no);
     if (negatives == 0 || 2 * negatives > t.num_entities || ps->L < 32 || ps->opt_push_sequential) return false;
-    if (!ps->kge_seen) {
-        if (hipMalloc(&ps->kge_seen, (size_t)ps->K * sizeof(u64)) != hipSuccess) { (void)hipGetLastError(); ps->kge_seen = nullptr; return false; }
-        if (hipMemset(ps->kge_seen, 0, (size_t)ps->K * sizeof(u64)) != hipSuccess) return false;
-        (void)hipDeviceSynchronize();
-    }
+    const size_t mark_words = 2 * (size_t)ps->K;
+    if (!ps->kge_seen && !ps->kge_seen_refused) ps->kge_seen_refused = zeroed(&ps->kge_seen, mark_words, st);
+    if (!ps->kge_seen) return false;
     if ((size_t)slots > ps->kge_shared_slots) {
-        (void)hipDeviceSynchronize();
+        if ((size_t)slots >= ps->kge_shared_refused) return false;
+        if (hipStreamSynchronize(st) != hipSuccess) return false;
         if (ps->kge_shared) (void)hipFree(ps->kge_shared);
         ps->kge_shared = nullptr; ps->kge_shared_slots = 0;
-        if (hipMalloc(&ps->kge_shared, 2 * (size_t)slots * sizeof(uint32_t)) != hipSuccess) { (void)hipGetLastError(); ps->kge_shared = nullptr; return false; }
-        if (hipMemset(ps->kge_shared, 0, 2 * (size_t)slots * sizeof(uint32_t)) != hipSuccess) return false;
-        (void)hipDeviceSynchronize();
+        if (zeroed(&ps->kge_shared, 2 * (size_t)slots, st)) ps->kge_shared_refused = (size_t)slots;
+        if (!ps->kge_shared) return false;
         ps->kge_shared_slots = (size_t)slots;
     }
     if (++ps->kge_id == 0) {                 // wrapped: forget everything
-        (void)hipDeviceSynchronize();
-        (void)hipMemset(ps->kge_seen, 0, (size_t)ps->K * sizeof(u64));
-        (void)hipMemset(ps->kge_shared, 0, 2 * ps->kge_shared_slots * sizeof(uint32_t));
-        (void)hipDeviceSynchronize();
+        if (hipDeviceSynchronize() != hipSuccess || dpaps_zero_words((uint32_t *)ps->kge_seen, mark_words, st) ||
+            dpaps_zero_words(ps->kge_shared, 2 * ps->kge_shared_slots, st)) {
+            --ps->kge_id;
+            return false;
+        }
         ps->kge_id = 1;
     }
     done.shared = ps->kge_shared + (ps->kge_id & 1u ? ps->kge_shared_slots : 0);
@@ -365,7 +375,7 @@ extern "C" int kge_sgd_step(ps_handle ps, int32_t worker, int64_t num_entities, 
         if (rc) return rc;
     } else {
         PushDone done;
-        const bool in_place = in_place_step(ps, t, batch, done);
+        const bool in_place = in_place_step(ps, t, batch, st, done);
         k_kge_keys<<<grid_for(rows, 256), 256, 0, st>>>(t, ukeys, ps->K, in_place ? ps->kge_seen : nullptr, const_cast<uint32_t *>(done.shared), done.id,
                                                         KgeBatch{}, nullptr, ps->err);
         PS_HIP(ps, hipGetLastError());
@@ -526,7 +536,7 @@ extern "C" int kge_sgd_epoch(ps_handle ps, int64_t num_entities, int32_t dim, in
             const int64_t n1 = lookahead && t1 < end ? std::min(t1 + batch, end) - t1 : 0;
             const KgeBatch next{subj + t1, rel + t1, obj + t1, neg_subj + t1 * ns, neg_obj + t1 * no, ns, no, num_entities, n1};
             PushDone done;
-            const bool in_place = in_place_step(ps, t, bmax, done);
+            const bool in_place = in_place_step(ps, t, bmax, bs, done);
             k_kge_keys<<<grid_for(std::max(nb * (3 + ns + no), n1 * ent), 256), 256, 0, bs>>>(t, ukeys, 0, in_place ? ps->kge_seen : nullptr,
                                                                                               const_cast<uint32_t *>(done.shared), done.id, next, lkeys, ps->err);
             PS_HIP(ps, hipGetLastError());

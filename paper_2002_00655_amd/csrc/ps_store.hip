@@ -681,10 +681,16 @@ __global__ void k_fill_u32(uint32_t *p, size_t n, uint32_t v) {
     if (i < n) p[i] = v;
 }
 
+// p[0 .. words) <- 0 (a kernel, not a memset node: callers may be capturing)
+int dpaps_zero_words(uint32_t *p, size_t words, hipStream_t st) {
+    k_fill_u32<<<grid_for((int64_t)words, 256), 256, 0, st>>>(p, words, 0u);
+    return hipGetLastError() == hipSuccess ? PS_OK : PS_EHIP;
+}
+
 static uint32_t next_call_id(dpaps_ps *ps, hipStream_t st) {
-    if (++ps->call_id == 0) {   // wrapped: forget all stamps (a kernel, not a memset node: callers may be capturing)
+    if (++ps->call_id == 0) {   // wrapped: forget all stamps
         const size_t W = (size_t)ps->W, words = W * W > PAIR_BITS ? W * W : 0;
-        if (words) k_fill_u32<<<grid_for((int64_t)words, 256), 256, 0, st>>>(ps->stamp_pair, words, 0u);
+        if (words) (void)dpaps_zero_words(ps->stamp_pair, words, st);
         ps->call_id = 1;
     }
     return ps->call_id;
