@@ -80,6 +80,14 @@ struct MfData {
     std::vector<int64_t> h_row_bounds, h_col_bounds, h_block_ptr;
 };
 
+#define DPAPS_LONG_RUN_GROUPS 64 // data with a column run of at least this many groups in a block: see the recurrence
+// Which variant of the kernels the loaded data gets (LONG_RUNS): a column run of very many groups in some block, or
+// rows that mostly have a single entry per block - there the second part is bound by trips to memory, not by
+// the order of a row's entries.
+inline bool dpaps_wide_like(const MfData &f) {
+    return f.max_run_groups >= DPAPS_LONG_RUN_GROUPS || (f.num_truns > 0 && 2 * f.num_tail < 3 * f.num_truns);
+}
+
 struct dpaps_ps {
     int device = 0;
     int64_t K = 0;

@@ -839,8 +839,6 @@ extern "C" int mf_load_ratings(ps_handle ps, int64_t m, int64_t n, int64_t nnz, 
     HIPRC(hipMemcpyAsync(&h_err, d_err, sizeof(int32_t), hipMemcpyDeviceToHost, st));
     HIPRC(hipStreamSynchronize(st));
     if (h_err) { rc = h_err; goto done; }
-    rc = build_schedule(ps, pos_b, tq, tpos, pos_run, trun_blk, st);
-    if (rc) goto done;
     // --- where the groups of the heavy runs start (head / scan are free again) ----------------------
     HIPRC(hipMalloc(&f.run_gptr, (num_runs + 1) * sizeof(int64_t)));
     if (num_runs > 0) {
@@ -865,6 +863,9 @@ extern "C" int mf_load_ratings(ps_handle ps, int64_t m, int64_t n, int64_t nnz, 
                                                               nullptr, scan, f.gstart);
     }
     HIPRC(hipGetLastError());
+    // (data that the SGD kernels process in the other form needs no schedule)
+    if (!dpaps_wide_like(f)) rc = build_schedule(ps, pos_b, tq, tpos, pos_run, trun_blk, st);
+    if (rc) goto done;
     HIPRC(hipStreamSynchronize(st));
 done:
     if (dev) (void)hipFree(dev);

@@ -57,7 +57,6 @@ typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 
 #define CH 15                    // entries per group (the 16th row of X is the column's row)
 #define AUX_SC1 16               // cache policy of a buffer access: agent scope
-#define DPAPS_LONG_RUN_GROUPS 64 // data with a column run of at least this many groups in a block: see the recurrence
 
 // x, which is the same in all lanes, as a scalar
 __device__ __forceinline__ int64_t uniform_i64(int64_t x) {
@@ -1316,13 +1315,6 @@ __global__ __launch_bounds__(1024) void k_mf_sgd_handoff(SgdArgs a) {
         if (threadIdx.x == 0) __hip_atomic_store(&a.col_state[cb], ((uint32_t)visit + 1u) << 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         start = cb + 1 < d_col ? cb + 1 : 0;
     }
-}
-
-// Which variant of the kernels the loaded data gets (LONG_RUNS): a column run of very many groups in some block, or
-// rows that mostly have a single entry per block - there the second part is bound by trips to memory, not by
-// the order of a row's entries.
-static bool dpaps_wide_like(const MfData &f) {
-    return f.max_run_groups >= DPAPS_LONG_RUN_GROUPS || (f.num_truns > 0 && 2 * f.num_tail < 3 * f.num_truns);
 }
 
 // The second part by levels, where a schedule was built - unless a bound on the factors in LDS is set, which only the
