@@ -169,11 +169,19 @@ done:
 // ---------------------------------------------------------------------------
 // mf_load_ratings
 // ---------------------------------------------------------------------------
+static void free_schedule(MfData &f) {
+    void *ptrs[] = {f.blk_chunk_ptr, f.ch_trun, f.ch_lv, f.lv_start, f.s_rec, f.blk_meta};
+    for (void *p : ptrs) if (p) (void)hipFree(p);
+    f.blk_chunk_ptr = nullptr; f.ch_trun = f.ch_lv = f.lv_start = f.blk_meta = nullptr; f.s_rec = nullptr;
+    f.num_chunks = f.num_levels = 0;
+}
+
 void dpaps_mf_free(dpaps_ps *ps) {
     MfData &f = ps->mf;
+    free_schedule(f);
     void *ptrs[] = {f.row, f.val, f.info, f.col, f.run_start, f.run_col, f.blk_run_ptr, f.multi_row, f.blk_multi_ptr,
                     f.row_bounds, f.col_bounds, f.blk_nheavy, f.t_cinfo, f.t_val, f.trun_start, f.trun_row, f.trun_wait, f.trun_ci, f.trun_val, f.trun_col,
-                    f.blk_trun_ptr, f.blk_chunk_ptr, f.ch_trun, f.ch_lv, f.lv_start, f.s_rec, f.blk_meta, f.run_gptr, f.gstart, f.team_plan};
+                    f.blk_trun_ptr, f.run_gptr, f.gstart, f.team_plan};
     for (void *p : ptrs) if (p) (void)hipFree(p);
     ps->mf = MfData();
 }
@@ -532,7 +540,8 @@ __global__ void k_level_fill(const uint64_t *key, const uint32_t *head, const ui
 
 // Builds that schedule where the data allows it.  Needs what mf_load_ratings has by then: the entries in (block, row)
 // order (spos; tq: of the second part, tpos: their number there), the row run of every stored position (pos_run) and
-// the block of every row run (trun_blk).  Sets f.sched_ok; data that does not fit is left to the other variant.
+// the block of every row run (trun_blk).  Sets f.sched_ok; data that does not fit, or for whose schedule there is no
+// memory (PS_ENOMEM), is left to the other variant.
 static int build_schedule(dpaps_ps *ps, const uint32_t *spos, const uint32_t *tq, const uint32_t *tpos, const uint32_t *pos_run,
                           const uint32_t *trun_blk, hipStream_t st) {
     MfData &f = ps->mf;
@@ -616,6 +625,7 @@ static int build_schedule(dpaps_ps *ps, const uint32_t *spos, const uint32_t *tq
     f.sched_ok = true;
 done:
     if (dev) (void)hipFree(dev);
+    if (!f.sched_ok) free_schedule(f);
     return rc;
 }
 
@@ -669,7 +679,6 @@ extern "C" int mf_load_ratings(ps_handle ps, int64_t m, int64_t n, int64_t nnz, 
         bm_hist = a.take<u64>(nb);
         runidx = a.take<uint32_t>(nnz + 1); tflag = a.take<uint32_t>(nnz + 1);
         tq = a.take<uint32_t>(nnz + 1); tpos = a.take<uint32_t>(nnz + 1);
-        pos_run = a.take<uint32_t>(nnz + 1); trun_blk = a.take<uint32_t>(nnz + 1);
         d_aux = a.take<int32_t>(2);
         if (pass == 0) {
             HIPRC(rocprim::radix_sort_pairs(nullptr, tmp_sort64, key_a, key_b, pos_a, pos_b, (size_t)std::max<int64_t>(nnz, 1), 0, 64, st));
@@ -828,6 +837,8 @@ extern "C" int mf_load_ratings(ps_handle ps, int64_t m, int64_t n, int64_t nnz, 
         const uint32_t end = (uint32_t)nt;
         HIPRC(hipMemcpyAsync(f.trun_start + ntr, &end, sizeof(uint32_t), hipMemcpyHostToDevice, st));
     }
+    // key_a is free again once more
+    pos_run = reinterpret_cast<uint32_t *>(key_a); trun_blk = pos_run + nnz;
     if (nnz > 0) {
         k_tail_fill<<<grid_for(nnz, 256), 256, 0, st>>>(pos_b, tq, tpos, head, scan, seg_idx, seg_start, is_multi, seg_slot, runidx,
                                                         blk, f.blk_run_ptr, f.blk_nheavy, f.run_start, f.row, f.val, nnz, f.t_cinfo,
@@ -864,7 +875,11 @@ extern "C" int mf_load_ratings(ps_handle ps, int64_t m, int64_t n, int64_t nnz, 
     }
     HIPRC(hipGetLastError());
     // (data that the SGD kernels process in the other form needs no schedule)
-    if (!dpaps_wide_like(f)) rc = build_schedule(ps, pos_b, tq, tpos, pos_run, trun_blk, st);
+    if (!dpaps_wide_like(f)) {
+        const std::string text = ps->last_error;
+        rc = build_schedule(ps, pos_b, tq, tpos, pos_run, trun_blk, st);
+        if (rc == PS_ENOMEM) { rc = PS_OK; ps->last_error = text; }     // without one, the other form serves
+    }
     if (rc) goto done;
     HIPRC(hipStreamSynchronize(st));
 done:

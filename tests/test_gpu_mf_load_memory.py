@@ -1,5 +1,5 @@
 """What mf_load_ratings allocates, seen through a hook on hipMalloc in a process of its own: the schedule by levels is made
-only for data that the SGD kernels process by levels."""
+only for data that the SGD kernels process by levels, and data loads without it where its memory is refused."""
 import os
 import subprocess
 import sys
@@ -77,4 +77,27 @@ for x in (single, long_runs):
     b = load(server(x), x)
     print(a, b, flush=True)
     assert a[1] == b[1] == 0 and b[0] <= a[0] - SCHEDULE
+""")
+
+
+def test_a_load_survives_a_refused_schedule(run):
+    """Every allocation of a load refused in turn: the load reports it and the handle takes the next load, or - for the
+    schedule's - goes on without, and an epoch gives the same factors up to the forms' rounding (1e-5, the small cases' bar)."""
+    run(r"""
+srv = server(levels)
+total, rc = load(srv, levels)
+assert rc == 0
+want = epoch(srv, levels)
+went_on = 0
+for i in range(total):
+    srv = server(levels)
+    n, rc = load(srv, levels, i)
+    assert n >= i + 1 and rc in (0, -5), (i, n, rc)
+    if rc:
+        assert load(srv, levels) == (total, 0)
+    else:
+        went_on += 1
+    assert np.abs(epoch(srv, levels) - want).max() <= 1e-5, i
+print("allocations", total, "without", went_on, flush=True)
+assert went_on == SCHEDULE
 """)
