@@ -9,10 +9,13 @@
 // Whether a call of few keys is to do nothing: a key is out of range, or the flag is set.  Every workgroup of the call's
 // one kernel looks at all of the keys before it does anything else, so that a bad call changes nothing, and no thread
 // leaves before all have looked.  Sets the error; the same in all threads.
+// AHEAD: keys of a thread whose reads are on their way together.
 constexpr int64_t FEW_KEYS = 2048;
+template <int AHEAD = 1>
 __device__ __forceinline__ bool few_keys_off(const int64_t *keys, int64_t n, int64_t K, int32_t *err) {
     const bool was_off = *(volatile const int32_t *)err != 0;
     bool off = was_off;
+#pragma unroll AHEAD
     for (int64_t p = threadIdx.x; p < n; p += blockDim.x) {
         const int64_t k = keys[p];
         off |= k < 0 || k >= K;

@@ -183,3 +183,27 @@ def test_a_relation_number_below_zero_shares_an_entity_key():
         srv.status()
         got.append((srv.pull(torch.arange(K, device="cuda")).cpu().numpy()[:E], losses, srv.stats()))
     assert np.array_equal(got[0][0].view(np.uint32), got[1][0].view(np.uint32)) and got[0][1:] == got[1][1:]
+
+
+@pytest.mark.parametrize("K,L,W", [(3000, 4, 5), (200_000, 2, 256), (200_000, 2, 257), (100_000, 1, 2048)])
+def test_statistics_at_the_sizes_where_workgroups_are_added(K, L, W):
+    """512 keys: one workgroup counts a call's statistics; 8,192: localize and owner check their keys themselves; more than
+    256 nodes: pairs by stamps.  Owners are spread by localize calls first; some calls name few destinations many times."""
+    import torch
+    from oracle.oracle import Oracle
+    from paper_2002_00655_amd import ps as P
+    rng = np.random.default_rng(W)
+    orc, srv = Oracle("f32", K, L, W), P.ParameterServer(K, L, W)
+    for n in (1, 256, 257, 511, 512, 513, 2047, 2048, 2049, 8191, 8192, 8193, 30_000):
+        for same in (False, True):
+            print(f"case K={K} W={W} n={n} same={same}", flush=True)
+            keys = rng.integers(0, K, size=n) if not same else rng.integers(0, 3, size=n) * (K // 3)
+            kt, worker, other = torch.from_numpy(keys).cuda(), int(rng.integers(0, W)), int(rng.integers(0, W))
+            d = rng.integers(-4, 5, size=(n, L)).astype(np.float32)
+            srv.pull(kt, worker); orc.pull(keys, worker)
+            srv.push(kt, torch.from_numpy(d).cuda(), other); orc.push(keys, d, other)
+            srv.localize(kt, worker); orc.localize(keys, worker)
+            assert np.array_equal(srv.owner(kt).cpu().numpy(), orc.owner()[keys]), n
+            srv.pull(kt, other); orc.pull(keys, other)
+            assert srv.stats() == orc.stats(), n
+    assert np.array_equal(srv.owner().cpu().numpy(), orc.owner())
