@@ -126,8 +126,17 @@ __device__ __forceinline__ void solve_first() { __asm__ volatile("s_nop 4"); }
 // SCHED: the second part by levels (see there), for data whose blocks have their non-heavy columns fit in LDS.
 template <int NT, bool A4, bool AGENT_H, bool LONG_RUNS, bool SCHED, bool RICH = false>
 __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const int32_t worker, const int32_t rb, const int32_t cb) {
-    __shared__ int stopped;       // (in the loop, the caller looks)
-    if constexpr (!AGENT_H) look_for_all(a.err, &stopped);
+    // All threads go on or none: the tables in LDS are filled together, and a level's entries are dealt out to all wavefronts.
+    // (In the loop, the caller looks.)  With LONG_RUNS the answer is waited for where the reads that come first are on their
+    // way, else here: 100k x 10k, an epoch 7.09 ms, 7.18 the other way.
+    __shared__ int stopped;
+    if constexpr (!AGENT_H) {
+        look_for_all(a.err, &stopped);
+        if constexpr (!LONG_RUNS) {
+            __syncthreads();
+            if (stopped != 0) return;
+        }
+    }
     constexpr int RS = 16 * NT + 4;          // row stride of the staging area in floats (conflict-free for both read patterns)
     constexpr int NV = (NT + 3) / 4;         // 64-component slices of a row
     // Called in a loop (AGENT_H): the thread's number, the rank and the step sizes pass through empty asm
@@ -216,21 +225,24 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
             if (idx < ncached_pieces) cached_piece(idx, pre_cached[q]);
         }
     }
-    // the powers of c, a thread for each (the products one after the other in double, rounded once; the divisions side
-    // by side: 17 in one thread were 3 us; its number opaque, or it stays in registers through part 1 and spills there)
-    int pw = tid;
-    __asm__ volatile("" : "+v"(pw));
-    if (pw <= 16) {
-        const double cd = 1.0 - (double)lr * (double)lambda;
-        double x = 1.0;
+    // The powers of c: the products one after the other in double, rounded once.  A thread for each, so that the divisions run
+    // side by side - 17 in one thread were 3 us; its number opaque, or it stays in registers through part 1 and spills
+    // there.  With LONG_RUNS one thread does it further down: part 1 takes thousands of steps there, and what the compiler
+    // then keeps in registers through them weighs more (60,000 x 2,000, 6M entries, 8 x 8 blocks, rank 100: 118.5 ms an epoch
+    // this way and 125 the other; 400,000 x 20,000 in 64 x 64 blocks 11.1 and 11.2).
+    if constexpr (!LONG_RUNS) {
+        int pw = tid;
+        __asm__ volatile("" : "+v"(pw));
+        if (pw <= 16) {
+            const double cd = 1.0 - (double)lr * (double)lambda;
+            double x = 1.0;
 #pragma unroll 1
-        for (int i = 0; i < pw; ++i) x = x * cd;
-        cpow[pw] = (float)x; cpm1[pw] = (float)(x - 1.0); cim1[pw] = (float)(1.0 / x - 1.0);
+            for (int i = 0; i < pw; ++i) x = x * cd;
+            cpow[pw] = (float)x; cpm1[pw] = (float)(x - 1.0); cim1[pw] = (float)(1.0 / x - 1.0);
+        }
     }
 
-    // Nothing has been written yet.  All threads go on or none: the tables in LDS are filled together, and a level's entries
-    // are dealt out to all wavefronts.
-    if constexpr (!AGENT_H) {
+    if constexpr (!AGENT_H && LONG_RUNS) {     // (nothing has been written yet)
         __syncthreads();
         if (stopped != 0) return;
     }
@@ -261,6 +273,8 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
             const int idx = tid + q * (int)blockDim.x;
             if (idx < ncached_pieces) cached_put(idx, pre_cached[q]);
         }
+        // (one component at a time in the loop of blocks: four of a thread's on their way together)
+#pragma unroll(AGENT_H ? 4 : 1)
         for (int idx = tid + HPRE * (int)blockDim.x; idx < ncached_pieces; idx += blockDim.x) {
             float x[CP];
             cached_piece(idx, x);
@@ -268,6 +282,11 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
         }
     }
     if (threadIdx.x == 0) {
+        if constexpr (LONG_RUNS) {
+            const double cd = 1.0 - (double)lr * (double)lambda;
+            double x = 1.0;
+            for (int i = 0; i <= 16; ++i) { cpow[i] = (float)x; cpm1[i] = (float)(x - 1.0); cim1[i] = (float)(1.0 / x - 1.0); x = x * cd; }
+        }
         next_run = 0; next_trow = 0; done_entries = 0; give_up = 0;
     }
     __syncthreads();
