@@ -43,6 +43,7 @@
 // runs lead the block), and the row's ticket tells when they are done.
 #include "common.h"
 #include "mf_device.h"
+#include "sgd_touch.h"
 #include "together.h"
 
 #include <algorithm>
@@ -295,7 +296,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
     // What the second part will read has not been read in this epoch.  The wavefronts that take no heavy runs (all of them
     // where there are none) fetch it meanwhile: the block's records, row and column numbers into the end of LDS, where
     // there is room beside the first part's (blk_meta: its words, 0 if not), and a word of every 128 bytes of the
-    // factors, so that they are in the die's cache (the results of those loads are not used).
+    // factors, so that they are in the die's cache (the results of those loads are not used; in the loop of blocks the rows' only).
     uint32_t meta_words = 0;
     int64_t ch0 = 0, ch1 = 0;
     uint32_t run_a = 0, ent_a = 0;                                     // the block's first row run and entry
@@ -318,16 +319,11 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
 #pragma unroll 4
                     for (int e = first; e < ntail_b; e += by) recs[e] = a.s_rec[ent_a + e];
                 }
-                if (!all) {
-                    const int lines = (L * 4 + 127) / 128;
-                    for (int t = first; t < nrows_b + ntcols; t += by) {
-                        const int64_t k = t < nrows_b ? a.trun_row[run_a + t] : a.m + a.run_col[run0 + nheavy + t - nrows_b];
-                        for (int i = 0; i < lines; ++i) {
-                            const float x = a.val[k * L + 32 * i];
-                            __asm__ volatile("" ::"v"(x));
-                        }
-                    }
-                }
+                if (!all)
+                    touch_factors<AGENT_H>(first, by, nrows_b, ntcols, a.trun_row + run_a, a.run_col + run0 + nheavy, a.m, L, [&](int64_t i) {
+                        const float x = a.val[i];
+                        __asm__ volatile("" ::"v"(x));
+                    });
             }
         }
     }
