@@ -411,9 +411,12 @@ __global__ void k_run_groups(const int64_t *run_start, const uint32_t *blk, cons
 }
 
 // out = max(out, the largest of src[0 .. n)) (out starts at zero)
-__global__ void k_max_u32(const uint32_t *src, int64_t n, uint32_t *out) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    uint32_t v = i < n ? src[i] : 0u;
+// (few workgroups that walk: atomics on one word come one by one, and with one for every 64 numbers of 50 million the
+// largest took 4.4 ms)
+constexpr int MAX_BLOCKS = 512;
+__global__ __launch_bounds__(256) void k_max_u32(const uint32_t *src, int64_t n, uint32_t *out) {
+    uint32_t v = 0;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) v = max(v, src[i]);
     for (int off = 32; off > 0; off >>= 1) v = max(v, (uint32_t)__shfl_xor((int)v, off));
     if ((threadIdx.x & 63) == 0 && v > 0) atomicMax(out, v);
 }
@@ -477,51 +480,107 @@ __global__ void k_run_lengths(const uint32_t *trun_start, int64_t ntr, uint32_t 
 // One wavefront per block walks the block's non-heavy column runs in stored order, 64 entries of a column at a time.
 // With r_k the level count of entry k's row so far (its entries in earlier columns), the column's recursion
 // c_k = 1 + max(r_k, c_(k-1)) is c_k = 1 + k + max over i <= k of (r_i - i): a running maximum.  A chunk starts afresh:
-// chunk numbers ascend along a column, so they are put in front of the compared number.  rowlev: one count per row
-// run, zero at first, read and written past the die's first cache, which the wavefront's own atomics pass by.
+// chunk numbers ascend along a column, so they are put in front of the compared number.  The level counts are small: a
+// chunk has fewer than 2^15 entries, which with their records fit in LDS.
+// Bound by the chain from column to column.  Blocks of up to LEVEL_ROWS row runs keep the rows' counts and chunks in LDS and
+// have the next column's row runs on their way; larger ones keep the counts in rowlev (one per row run, zero at first),
+// read and written past the die's first cache, which the wavefront's own atomics pass by.  1000 x 1000 in 4 x 4 blocks:
+// 158 us, with all counts in rowlev 395; 480,189 x 17,770, 100M entries in 256 x 256 blocks 1,360 and 1,809.
+constexpr int LEVEL_ROWS = 2048;
+// the running maximum over a wavefront's lanes of numbers that are not negative
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int32_t max_dpp(int32_t x) { return max(x, __builtin_amdgcn_update_dpp(0, x, CTRL, ROWS, 0xF, false)); }
+__device__ __forceinline__ int32_t running_max(int32_t x) {
+    x = max_dpp<0x111, 0xF>(x); x = max_dpp<0x112, 0xF>(x); x = max_dpp<0x114, 0xF>(x); x = max_dpp<0x118, 0xF>(x);   // row_shr 1, 2, 4, 8
+    x = max_dpp<0x142, 0xA>(x);                                                                                       // row_bcast15
+    return max_dpp<0x143, 0xC>(x);                                                                                    // row_bcast31
+}
 __global__ __launch_bounds__(256) void k_tail_levels(const int64_t *blk_run_ptr, const int32_t *nheavy, const int64_t *run_start, int64_t nb,
-                                                     const uint32_t *pos_run, const uint32_t *chunk, uint32_t *rowlev, uint32_t *level) {
-    const int lane = threadIdx.x & 63;
-    const int64_t b = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+                                                     const int64_t *blk_trun_ptr, const uint32_t *pos_run, const uint32_t *chunk, uint32_t *rowlev,
+                                                     uint32_t *level, uint32_t *max_count) {
+    __shared__ uint16_t lev_all[4][LEVEL_ROWS], ch_all[4][LEVEL_ROWS];
+    // (the block is the same for all lanes of a wavefront: said so, its columns' places stay in scalar registers)
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int64_t b = (int64_t)blockIdx.x * 4 + wave;
     if (b >= nb) return;
-    const int64_t g0 = blk_run_ptr[b] + nheavy[b], g1 = blk_run_ptr[b + 1];
-    for (int64_t g = g0; g < g1; ++g) {
-        const int64_t p0 = run_start[g], p1 = run_start[g + 1];
-        int64_t carry = 0;                                             // chunk << 32 | level count of the column's entry before
-        for (int64_t base = p0; base < p1; base += 64) {
-            const bool in = base + lane < p1;
-            const uint32_t run = in ? pos_run[base + lane] : 0u;
-            const int64_t ch = in ? (int64_t)chunk[run] << 32 : 0;
-            const uint32_t r = in ? __hip_atomic_load(&rowlev[run], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-            // (64 is added so that the low half stays positive)
-            int64_t x = in ? ch + 64 + (int64_t)r - lane : 0;
-            if (lane == 0) x = max(x, carry + 64);
-            for (int off = 1; off < 64; off <<= 1) {
-                const int64_t y = __shfl_up(x, off);
-                if (lane >= off) x = max(x, y);
+    const int64_t g0 = blk_run_ptr[b] + nheavy[b], g1 = blk_run_ptr[b + 1], j0 = blk_trun_ptr[b], nrows = blk_trun_ptr[b + 1] - j0;
+    uint32_t most = 0;
+    if (nrows <= LEVEL_ROWS) {
+        uint16_t *lev = lev_all[wave], *ch = ch_all[wave];
+        const uint32_t chunk0 = nrows > 0 ? chunk[j0] : 0u;
+        for (int i = lane; i < (int)nrows; i += 64) { lev[i] = 0; ch[i] = (uint16_t)(chunk[j0 + i] - chunk0); }
+        __asm__ volatile("" ::: "memory");                             // (LDS serves a wavefront's accesses in order)
+        // this column's entries [p0, p1), the next one's [p1, p2); run: the row runs of the first 64
+        int64_t p0 = g0 < g1 ? run_start[g0] : 0, p1 = g0 < g1 ? run_start[g0 + 1] : 0, p2 = g0 + 1 < g1 ? run_start[g0 + 2] : p1;
+        uint32_t run = p0 + lane < p1 ? pos_run[p0 + lane] : 0u;
+        for (int64_t g = g0; g < g1; ++g) {
+            const int64_t p3 = g + 2 < g1 ? run_start[g + 3] : p2;
+            const uint32_t run_n = p1 + lane < p2 ? pos_run[p1 + lane] : 0u;
+            int32_t carry = 0;                                         // chunk << 17 | level count of the column's entry before
+            for (int64_t base = p0; base < p1; base += 64) {
+                const bool in = base + lane < p1;
+                if (base > p0) run = in ? pos_run[base + lane] : 0u;
+                const int row = in ? (int)(run - (uint32_t)j0) : 0;
+                const int32_t c = in ? (int32_t)ch[row] << 17 : 0;
+                // (64 is added so that the low part stays positive)
+                int32_t x = in ? c + 64 + (int32_t)lev[row] - lane : 0;
+                if (lane == 0) x = max(x, carry + 64);
+                x = running_max(x);
+                const int32_t count = (x - c) - 64 + 1 + lane;         // c_k
+                const uint32_t below = (uint32_t)__shfl_down((int)run, 1);
+                if (in) {
+                    level[base + lane] = (uint32_t)count - 1u;
+                    most = max(most, (uint32_t)count);
+                    // (entries of one row follow one another, the last has the largest count)
+                    if (lane == 63 || base + lane + 1 >= p1 || below != run) lev[row] = (uint16_t)count;
+                }
+                const int last = (int)(p1 - base < 64 ? p1 - base : 64) - 1;
+                carry = __builtin_amdgcn_readlane(c + count, last);
+                __asm__ volatile("" ::: "memory");
             }
-            const int64_t count = (x - ch) - 64 + 1 + lane;            // c_k, a small number
-            if (in) {
-                level[base + lane] = (uint32_t)count - 1u;
-                atomicMax(&rowlev[run], (uint32_t)count);
+            p0 = p1; p1 = p2; p2 = p3; run = run_n;
+        }
+    } else {
+        for (int64_t g = g0; g < g1; ++g) {
+            const int64_t p0 = run_start[g], p1 = run_start[g + 1];
+            int64_t carry = 0;                                         // chunk << 32 | level count of the column's entry before
+            for (int64_t base = p0; base < p1; base += 64) {
+                const bool in = base + lane < p1;
+                const uint32_t run = in ? pos_run[base + lane] : 0u;
+                const int64_t ch = in ? (int64_t)chunk[run] << 32 : 0;
+                const uint32_t r = in ? __hip_atomic_load(&rowlev[run], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+                int64_t x = in ? ch + 64 + (int64_t)r - lane : 0;
+                if (lane == 0) x = max(x, carry + 64);
+                for (int off = 1; off < 64; off <<= 1) {
+                    const int64_t y = __shfl_up(x, off);
+                    if (lane >= off) x = max(x, y);
+                }
+                const int64_t count = (x - ch) - 64 + 1 + lane;
+                if (in) {
+                    level[base + lane] = (uint32_t)count - 1u;
+                    most = max(most, (uint32_t)count);
+                    atomicMax(&rowlev[run], (uint32_t)count);
+                }
+                const int last = (int)(p1 - base < 64 ? p1 - base : 64) - 1;
+                carry = __shfl(ch + count, last);
+                __builtin_amdgcn_s_waitcnt(0);                         // the counts have arrived before the next column looks at them
+                __asm__ volatile("" ::: "memory");
             }
-            const int last = (int)(p1 - base < 64 ? p1 - base : 64) - 1;
-            carry = __shfl(ch + count, last);
-            __builtin_amdgcn_s_waitcnt(0);                             // the counts have arrived before the next column looks at them
-            __asm__ volatile("" ::: "memory");
         }
     }
+    for (int off = 32; off > 0; off >>= 1) most = max(most, (uint32_t)__shfl_xor((int)most, off));
+    if (lane == 0 && most > __hip_atomic_load(max_count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(max_count, most);
 }
 
 // the sort key (chunk, level) and the record of every entry of the second part
 __global__ void k_sched_keys(const uint32_t *spos, const uint32_t *tq, const uint32_t *tpos, const uint32_t *pos_run, const uint32_t *chunk_incl,
                              const uint32_t *ch_trun, const uint32_t *level, const uint32_t *trun_blk, const int64_t *blk_run_ptr,
-                             const int32_t *nheavy, const uint32_t *t_cinfo, const float *t_val, int64_t nnz, int32_t LS, uint64_t *key, uint2 *rec) {
+                             const int32_t *nheavy, const uint32_t *t_cinfo, const float *t_val, int64_t nnz, int32_t LS, int level_bits, uint64_t *key, uint2 *rec) {
     const int64_t q = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (q >= nnz || !tq[q]) return;
     const uint32_t t = tpos[q], p = spos[q], run = pos_run[p], c = chunk_incl[run] - 1u, b = trun_blk[run];
     const uint32_t cols = (uint32_t)(blk_run_ptr[b + 1] - blk_run_ptr[b]) - (uint32_t)nheavy[b];
-    key[t] = ((uint64_t)c << 16) | level[p];
+    key[t] = ((uint64_t)c << level_bits) | level[p];
     const uint32_t at_row = DPAPS_SCHED_BASE + (cols + (run - ch_trun[c])) * (uint32_t)LS, at_col = DPAPS_SCHED_BASE + (t_cinfo[t] & 0xFFFFu) * (uint32_t)LS;
     rec[t] = make_uint2(at_row | at_col << 16, __float_as_uint(t_val[t]));
 }
@@ -531,11 +590,11 @@ __global__ void k_level_heads(const uint64_t *key, int64_t n, uint32_t *head) {
     if (t < n) head[t] = t == 0 || key[t] != key[t - 1] ? 1u : 0u;
 }
 
-__global__ void k_level_fill(const uint64_t *key, const uint32_t *head, const uint32_t *incl, int64_t n, uint32_t *lv_start, uint32_t *ch_lv) {
+__global__ void k_level_fill(const uint64_t *key, const uint32_t *head, const uint32_t *incl, int64_t n, int level_bits, uint32_t *lv_start, uint32_t *ch_lv) {
     const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n || !head[t]) return;
     lv_start[incl[t] - 1u] = (uint32_t)t;
-    if (t == 0 || (key[t] >> 16) != (key[t - 1] >> 16)) ch_lv[key[t] >> 16] = incl[t] - 1u;
+    if (t == 0 || (key[t] >> level_bits) != (key[t - 1] >> level_bits)) ch_lv[key[t] >> level_bits] = incl[t] - 1u;
 }
 
 // Builds that schedule where the data allows it.  Needs what mf_load_ratings has by then: the entries in (block, row)
@@ -561,9 +620,9 @@ static int build_schedule(dpaps_ps *ps, const uint32_t *spos, const uint32_t *tq
     uint64_t *key_a = nullptr, *key_b = nullptr;
     uint2 *rec = nullptr;
     char *tmp = nullptr;
-    uint32_t h_max = 0, h_chunks = 0, h_levels = 0;
+    uint32_t h_max = 0, h_chunks = 0, h_levels = 0, h_count = 0;
     int64_t longest = 0;
-    int key_bits = 17;
+    int level_bits = 1, key_bits = 0;
     for (int pass = 0; pass < 2; ++pass) {   // pass 0 measures, pass 1 hands out
         a.used = 0;
         chunk = a.take<uint32_t>(ntr); head = a.take<uint32_t>(nt); incl = a.take<uint32_t>(nt); rowlev = a.take<uint32_t>(ntr);
@@ -582,7 +641,7 @@ static int build_schedule(dpaps_ps *ps, const uint32_t *spos, const uint32_t *tq
     HIPRC(hipMemsetAsync(d_max, 0, sizeof(uint32_t), st));
     HIPRC(hipMemsetAsync(rowlev, 0, ntr * sizeof(uint32_t), st));
     k_run_lengths<<<grid_for(ntr, 256), 256, 0, st>>>(f.trun_start, ntr, head);
-    k_max_u32<<<grid_for(ntr, 256), 256, 0, st>>>(head, ntr, d_max);
+    k_max_u32<<<std::min(grid_for(ntr, 256), (unsigned)MAX_BLOCKS), 256, 0, st>>>(head, ntr, d_max);
     HIPRC(hipGetLastError());
     HIPRC(hipMemcpyAsync(&h_max, d_max, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HIPRC(hipStreamSynchronize(st));
@@ -593,19 +652,25 @@ static int build_schedule(dpaps_ps *ps, const uint32_t *spos, const uint32_t *tq
     k_chunk_heads<<<grid_for(ntr, 256), 256, 0, st>>>(trun_blk, f.blk_trun_ptr, f.trun_start, f.blk_run_ptr, f.blk_nheavy, f.blk_meta, ntr, LS, budget - longest, chunk, head);
     HIPRC(rocprim::inclusive_scan(tmp, tmp_scan, head, incl, (size_t)ntr, rocprim::plus<uint32_t>(), st));
     HIPRC(hipMemcpyAsync(&h_chunks, incl + (ntr - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, st));
+    HIPRC(hipMemsetAsync(d_max, 0, sizeof(uint32_t), st));
+    k_tail_levels<<<grid_for(nb, 4), 256, 0, st>>>(f.blk_run_ptr, f.blk_nheavy, f.run_start, nb, f.blk_trun_ptr, pos_run, chunk, rowlev, level, d_max);
+    HIPRC(hipGetLastError());
+    HIPRC(hipMemcpyAsync(&h_count, d_max, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
     HIPRC(hipStreamSynchronize(st));
     f.num_chunks = h_chunks;
+    // (only the bits that occur: each eight cost a pass of the sort, 0.4 ms for 70 million entries)
+    while (((uint32_t)1 << level_bits) < h_count) ++level_bits;
+    key_bits = level_bits + 1;
+    while (key_bits < 64 && ((int64_t)1 << (key_bits - level_bits)) < f.num_chunks) ++key_bits;
     HIPRC(hipMalloc(&f.blk_chunk_ptr, (nb + 1) * sizeof(int64_t)));
     HIPRC(hipMalloc(&f.ch_trun, (f.num_chunks + 1) * sizeof(uint32_t)));
     HIPRC(hipMalloc(&f.ch_lv, (f.num_chunks + 1) * sizeof(uint32_t)));
     HIPRC(hipMalloc(&f.s_rec, nt * sizeof(uint2)));
     k_chunk_fill<<<grid_for(ntr, 256), 256, 0, st>>>(head, incl, ntr, f.ch_trun);
     k_blk_chunks<<<grid_for(nb + 1, 256), 256, 0, st>>>(f.blk_trun_ptr, nb, incl, f.blk_chunk_ptr);
-    k_tail_levels<<<grid_for(nb, 4), 256, 0, st>>>(f.blk_run_ptr, f.blk_nheavy, f.run_start, nb, pos_run, chunk, rowlev, level);
     k_sched_keys<<<grid_for(nnz, 256), 256, 0, st>>>(spos, tq, tpos, pos_run, incl, f.ch_trun, level, trun_blk, f.blk_run_ptr, f.blk_nheavy, f.t_cinfo,
-                                                     f.t_val, nnz, LS, key_a, rec);
+                                                     f.t_val, nnz, LS, level_bits, key_a, rec);
     HIPRC(hipGetLastError());
-    while (key_bits < 64 && ((int64_t)1 << (key_bits - 16)) < f.num_chunks) ++key_bits;
     HIPRC(rocprim::radix_sort_pairs(tmp, tmp_sort, key_a, key_b, (uint64_t *)rec, (uint64_t *)f.s_rec, (size_t)nt, 0, key_bits, st));
     k_level_heads<<<grid_for(nt, 256), 256, 0, st>>>(key_b, nt, head);
     HIPRC(rocprim::inclusive_scan(tmp, tmp_scan, head, incl, (size_t)nt, rocprim::plus<uint32_t>(), st));
@@ -613,7 +678,7 @@ static int build_schedule(dpaps_ps *ps, const uint32_t *spos, const uint32_t *tq
     HIPRC(hipStreamSynchronize(st));
     f.num_levels = h_levels;
     HIPRC(hipMalloc(&f.lv_start, (f.num_levels + 1) * sizeof(uint32_t)));
-    k_level_fill<<<grid_for(nt, 256), 256, 0, st>>>(key_b, head, incl, nt, f.lv_start, f.ch_lv);
+    k_level_fill<<<grid_for(nt, 256), 256, 0, st>>>(key_b, head, incl, nt, level_bits, f.lv_start, f.ch_lv);
     HIPRC(hipGetLastError());
     {
         const uint32_t ends[3] = {(uint32_t)ntr, h_levels, (uint32_t)nt};
@@ -861,7 +926,7 @@ extern "C" int mf_load_ratings(ps_handle ps, int64_t m, int64_t n, int64_t nnz, 
         HIPRC(hipMemcpyAsync(&h_tail[1], head + (num_runs - 1), sizeof(uint32_t), hipMemcpyDeviceToHost, st));
         // the most groups of any run (head[r] = groups + 1 of a heavy run), into the error word, which is zero here
         uint32_t h_max = 0;
-        k_max_u32<<<grid_for(num_runs, 256), 256, 0, st>>>(head, num_runs, reinterpret_cast<uint32_t *>(d_err));
+        k_max_u32<<<std::min(grid_for(num_runs, 256), (unsigned)MAX_BLOCKS), 256, 0, st>>>(head, num_runs, reinterpret_cast<uint32_t *>(d_err));
         HIPRC(hipMemcpyAsync(&h_max, d_err, sizeof(uint32_t), hipMemcpyDeviceToHost, st));
         HIPRC(hipStreamSynchronize(st));
         f.num_gstart = (int64_t)h_tail[0] + h_tail[1];

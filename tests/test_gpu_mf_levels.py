@@ -62,3 +62,19 @@ def test_levels_with_handoff(rank):
     check_handoff_order(order)
     orc = oracle_epochs("f32", w, rb, cb, blocked, replay_schedule(order))
     compare_state(orc, srv, exact=False, atol=1e-5)
+
+
+@pytest.mark.parametrize("rows", [63, 2047, 2048, 2049, 2200])
+def test_levels_of_blocks_around_the_rows_that_lds_counts(rows):
+    """Blocks whose row runs are counted in LDS, and in memory (from 2,049 rows), columns of more than 64 entries and cells
+    revealed several times."""
+    from oracle.oracle import mf_block_ratings
+    m, n = rows, 40
+    w = _workload(m, n, m * n // 3, 16, 5, 100)
+    rb, cb = wl.equal_bounds(m, 1), wl.equal_bounds(n, 1)
+    blocked = mf_block_ratings(m, n, w.rows, w.cols, w.vals, rb, cb)
+    print(f"case {rows} rows, {np.unique(w.rows).size} with entries", flush=True)
+    sched = wl.cyclic_schedule(1)
+    orc = oracle_epochs("f32", w, rb, cb, blocked, sched)
+    srv = gpu_epochs(w, rb, cb, blocked, sched, options=[(OPT_HEAVY_LEN, 10 ** 6)])
+    compare_state(orc, srv, exact=False, atol=1e-5)
