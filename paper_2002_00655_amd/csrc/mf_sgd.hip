@@ -325,9 +325,16 @@ __global__ __launch_bounds__(1024) void k_mf_sgd(SgdArgs a) {
 //   that cache and a column's factor is read by neighbours.
 // 480,189 x 17,770, 100M entries, rank 100: 4.7 ms (80 GB of factor rows asked for, 17 TB/s out of the caches), with one
 // wavefront per entry 19.2 ms; 2M x 200k, 100M entries: 7.0 ms, before 19.5; 4 entries ahead instead of 2: 5.0 and 6.9.
-constexpr int SSE_BLOCKS = 2048;          // 8 wavefronts per vector unit; a multiple of the dies
+constexpr int SSE_BLOCKS = 2048;          // at most: 8 wavefronts per vector unit; a multiple of the dies
 constexpr int SSE_DIES = 8;
 constexpr int SSE_AHEAD = 2;
+// Workgroups for nnz entries: no more than have a batch of 64 for each of their 4 wavefronts.  (Which batch a wavefront
+// takes and the order of the partial sums are those of the full number; workgroups without a batch only add zeros, and
+// their launch and the way of their sums to the host: 300 entries 39.5 us, 41.2 with 2,048 workgroups.)
+static int sse_blocks(int64_t nnz) {
+    const int64_t share = ((nnz + 63) / 64 + SSE_DIES - 1) / SSE_DIES;
+    return (int)std::min<int64_t>(SSE_BLOCKS, SSE_DIES * std::max<int64_t>((share + 3) / 4, 1));
+}
 
 template <int V> struct SsePiece;
 template <> struct SsePiece<4> { typedef float4 type; };
@@ -750,8 +757,8 @@ extern "C" int mf_train_sse(ps_handle ps, double *sse_host_out, void *stream) {
     MfData &f = ps->mf;
     if (!f.row) { ps->last_error = "mf_train_sse before mf_load_ratings"; return PS_EINVAL; }
     hipStream_t st = (hipStream_t)stream;
-    const int blocks = SSE_BLOCKS, L = ps->L;
-    int rc = dpaps_ws_reserve(ps, blocks * sizeof(double));
+    const int blocks = sse_blocks(f.nnz), L = ps->L;
+    int rc = dpaps_ws_reserve(ps, SSE_BLOCKS * sizeof(double));
     if (rc) return rc;
     double *partial = (double *)ps->ws;
 #define MF_SSE(V, NR) k_mf_sse<V, NR><<<blocks, 256, 0, st>>>(f.row, f.col, f.val, f.nnz, ps->val, f.m, L, partial)

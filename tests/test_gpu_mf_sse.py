@@ -30,3 +30,28 @@ def test_train_sse_sums_in_double(rank):
         size = np.abs(v[rows] * v[m + cols]).sum(1) + np.abs(vals)
         bound = float((2 * np.abs(vals - dot) * size * (rank + 2)).sum() + nnz * want) * 2.0 ** -53
         assert abs(got - want) <= 2 * bound, (got, want, bound)
+
+
+@pytest.mark.parametrize("nnz", [2047, 2048, 2049, 4097, 524288, 524289, 700001])
+def test_train_sse_at_numbers_of_workgroups(nnz):
+    """Entry counts at which the launch gets more workgroups, and the most it gets; the bound as above."""
+    import torch
+    from paper_2002_00655_amd import ps as P
+    rng = np.random.default_rng(nnz)
+    m, n, rank = 900, 800, 4
+    dev = torch.device("cuda")
+    val = rng.standard_normal((m + n, rank)).astype(np.float32)
+    cell = np.sort(rng.integers(0, m * n, size=nnz))
+    cols, rows = (cell // m).astype(np.int32), (cell % m).astype(np.int32)
+    vals = rng.standard_normal(nnz).astype(np.float32)
+    srv = P.ParameterServer(m + n, rank, 1)
+    srv.push(torch.arange(m + n, device=dev), torch.from_numpy(val).to(dev))
+    srv.mf_load_ratings(m, n, *(torch.from_numpy(x).to(dev) for x in (rows, cols, vals)), [0, m], [0, n], [0, nnz])
+    print(f"case nnz={nnz}", flush=True)
+    got = srv.mf_train_sse()
+    v = val.astype(np.float64)
+    e = vals - (v[rows] * v[m + cols]).sum(1)
+    want = float((e ** 2).sum())
+    size = np.abs(v[rows] * v[m + cols]).sum(1) + np.abs(vals)
+    bound = float((2 * np.abs(e) * size * (rank + 2)).sum() + nnz * want) * 2.0 ** -53
+    assert abs(got - want) <= 2 * bound, (got, want, bound)
