@@ -9,7 +9,8 @@
  * call.  `stream` is a hipStream_t (NULL = the null stream).  Calls are
  * asynchronous on that stream and take effect in stream order, which is the
  * program order of one client (Sec. 3.4, "Asynchronous operations"); one
- * handle must not be driven from two streams at once.  The knowledge-graph calls put part of
+ * handle must not be driven from two streams at once (besides the values, a call's statistics are put
+ * together in words of the handle: calls that overlap can leave the message counts wrong for good).  The knowledge-graph calls put part of
  * their work (a sort; an epoch also its localize calls and statistics) on a second stream that the library
  * creates at default priority; that work starts after what precedes the call on
  * `stream` and `stream` waits for it before the call's effects are complete, so

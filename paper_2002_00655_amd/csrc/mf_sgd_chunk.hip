@@ -33,14 +33,19 @@
 // group, and because every column is walked by ascending row, each run's last group ends
 // up waiting for the previous run's, one after the other.  So only the leading runs of a
 // block that are long enough ("heavy" columns) are processed in groups, by the first few
-// wavefronts.  The entries of all other runs are walked row by row: a wavefront takes a few
+// wavefronts.  A row's entries in heavy runs precede its other entries in stored order (heavy
+// runs lead the block), and the row's ticket tells when they are done.
+// The entries of all other runs take one of two forms.  By levels (SCHED), where the block's
+// non-heavy columns fit in half of LDS and no column run is very long: mf_load_ratings has
+// ordered the entries by their depth in the block's dependency graph; once the heavy runs are
+// through, rows and columns are copied into LDS and worked off level by level with a barrier
+// after each (see there).  Otherwise row by row: a wavefront takes a few
 // consecutive rows, keeps a row's factor in registers for all of that row's entries, and
 // the factors of the non-heavy columns live in LDS for the subepoch, each with a ticket
 // counter that orders the column's entries as stored.  This is the same dependency graph
 // as walking those runs one after the other - every row's entries in stored order, every
 // column's entries in stored order - so the result is the same; it only takes the waiting
-// out.  A row's entries in heavy runs precede its other entries in stored order (heavy
-// runs lead the block), and the row's ticket tells when they are done.
+// out.  (So do the levels.)
 #include "common.h"
 #include "mf_device.h"
 #include "sgd_touch.h"

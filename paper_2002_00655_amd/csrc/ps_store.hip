@@ -346,7 +346,8 @@ __global__ __launch_bounds__(256) void k_pull(RouteArgs route, const int64_t *ke
     if ((int)blockIdx.x < route.blocks) { route_access_block(route, l, blockIdx.x); return; }
     const int64_t block = blockIdx.x - route.blocks;
     // the workgroup's first piece: row p0, piece c0 of it (quotients by way of 1 / P, rounded: the first in double and
-    // put right, the others, of numbers below 2048, exact with the half added)
+    // put right, the others, of numbers up to P - 1 + 256 AHEAD - 1 - 3069 at most, with 8 pieces of 4 bytes ahead and rows of
+    // 1023 -, exact with the half added: the quotient then lies 1 / (2 P) or more from a whole number, and is off by 2e-7 of itself)
     const int64_t first = block * (256 * AHEAD), total = n * P;
     const int64_t p0 = quotient(first, P, inv_P);
     const uint32_t c0 = (uint32_t)(first - p0 * P);
@@ -801,7 +802,6 @@ static int push_tiny(dpaps_ps *ps, const RouteArgs &stats, const int64_t *keys, 
     return PS_OK;
 }
 
-// stats: an access to be counted along with the sums; done: what has been added already
 // How many components a lane of a push's sums holds: as few as let one wavefront take a row (up to four).
 // A row that several wavefronts take is read in overlapping lines, long after one another.  A million keys, rows of 100:
 // the push 240 us with 2, 281 with 1; rows of 400, 20,000 keys: 47 with 4, 58 with 1.  Rows of 64 with 2: 198 instead of
@@ -811,6 +811,7 @@ static int push_width(int32_t L, const float *deltas) {
     if (L > 64 && L % 2 == 0 && ((uintptr_t)deltas & 7) == 0) return 2;
     return 1;
 }
+// stats: an access to be counted along with the sums; done: what has been added already
 static int push_add(dpaps_ps *ps, int64_t n, const float *deltas, const RouteArgs &stats, const PushDone &done, hipStream_t st) {
     if (n != ps->push_sorted_n || !ps->push_base) { ps->last_error = "push: the sums do not follow their sort"; return PS_EINVAL; }
     const int64_t nranges = (n + PUSH_RANGE - 1) / PUSH_RANGE;
