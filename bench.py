@@ -31,9 +31,9 @@ HBM_PEAK_GBS = 8000.0     # MI355X HBM3E, published
 # HBM bytes per launch of the SGD kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (scaled by what the same
 # counters read for a plain 1 GiB copy; summaries under profiles/).  Only valid for the kernel sources they were
 # taken with and for the default settings of the workload: bytes read, bytes written.
-KERNEL_SOURCES = ("mf_sgd_chunk.hip", "mf_sgd.hip", "mf_device.h", "common.h")
-TRAFFIC = {"kernel_sha256_16": "9f3be4503eba525b",
-           "bytes_per_launch": {"large": (196044390.4, 127389696.0), "wide": (1324613427.2, 953154252.8)}}
+KERNEL_SOURCES = ("mf_sgd_chunk.hip", "mf_sgd.hip", "mf_device.h", "common.h", "sgd_touch.h", "together.h")
+TRAFFIC = {"kernel_sha256_16": "f195c48c7ff97125",
+           "bytes_per_launch": {"large": (195936460.8, 127404646.4), "wide": (1324763545.6, 953185484.8)}}
 
 # block boundaries per workload: a column of a block weighs this many entries on top of its own (see --col-cost)
 COL_COST = {"wide": 3.0}
