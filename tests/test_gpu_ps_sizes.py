@@ -187,14 +187,15 @@ def test_a_relation_number_below_zero_shares_an_entity_key():
 
 @pytest.mark.parametrize("K,L,W", [(3000, 4, 5), (200_000, 2, 256), (200_000, 2, 257), (100_000, 1, 2048)])
 def test_statistics_at_the_sizes_where_workgroups_are_added(K, L, W):
-    """512 keys: one workgroup counts a call's statistics; 8,192: localize and owner check their keys themselves; more than
+    """512 keys: one workgroup counts a call's statistics; 8,192: localize and owner check their keys themselves, and up to 32
+    workgroups are counted on one word, more on 16; 131,072: the most workgroups; more than
     256 nodes: pairs by stamps.  Owners are spread by localize calls first; some calls name few destinations many times."""
     import torch
     from oracle.oracle import Oracle
     from paper_2002_00655_amd import ps as P
     rng = np.random.default_rng(W)
     orc, srv = Oracle("f32", K, L, W), P.ParameterServer(K, L, W)
-    for n in (1, 256, 257, 511, 512, 513, 2047, 2048, 2049, 8191, 8192, 8193, 30_000):
+    for n in (1, 256, 257, 511, 512, 513, 2047, 2048, 2049, 8191, 8192, 8193, 8449, 12_288, 30_000, 131_073):
         for same in (False, True):
             print(f"case K={K} W={W} n={n} same={same}", flush=True)
             keys = rng.integers(0, K, size=n) if not same else rng.integers(0, 3, size=n) * (K // 3)
