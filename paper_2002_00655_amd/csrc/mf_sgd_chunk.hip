@@ -9,19 +9,18 @@
 //     e_t = v_t - <w_t, h_{t-1}>,   h_t = c h_{t-1} + lr e_t w_t,   w_t' = c w_t + lr e_t h_{t-1}
 // (c = 1 - lr lambda) is affine in h, so for a group of T consecutive entries of a column
 // (distinct rows w_0 .. w_{T-1}, all final when the group starts) it can be regrouped:
-//   1. X = [w_0; ...; w_{T-1}; h]  (16 x r with T = 15),  G = X X^T  - one dense 16x16xr
-//      product (matrix cores); G[s][15] = <w_s, h> are the T inner products with the
-//      incoming h, G[s][t] = <w_s, w_t>;
+//   1. X = [w_0; ...; w_{T-1}]  (16 x r with T = 15, the last row zero),  G = X X^T  - one dense 16x16xr
+//      product (matrix cores), which needs nothing of h: G[s][t] = <w_s, w_t>;
 //   2. with p_s = <w_s, h> for the incoming h, the errors solve a lower-triangular system,
 //      e_t = v_t - c^t p_t - sum_(u<t) lr c^(t-1-u) G[t][u] e_u, which in the scaled unknowns
 //      e_t c^(-t) loses its powers of c: one dependent vector instruction per entry instead
 //      of a length-r reduction;
-//   3. all new rows are one more dense product X' = C X with the lower-triangular 16x16
-//      coefficient matrix  C[t][t] = c,  C[t][s<t] = lr^2 e_t e_s c^(t-1-s),
-//      C[t][15] = lr e_t c^t,  C[15][s] = lr e_s c^(T-1-s),  C[15][15] = c^T.
+//   3. with the errors known, w_t' and h_t are the recursion itself, component by component: a few multiply-adds per
+//      entry, every lane its components.  (As a dense product X' = X + (C - I) X with a lower-triangular coefficient
+//      matrix they cost another 28 matrix instructions at rank 100, 35 reads of LDS for its operands and the coefficients:
+//      3,400 cycles of a group's 8,900 under full load, now 1,900 of 7,600.)
 // c is never rounded to fp32 on its own (that would bias every update of a row the same
-// way): products with c are formed as x - (lr lambda) x, and the dense product is taken
-// as X' = X + (C - I) X with c - 1 and c^T - 1 computed in double.
+// way): products with c are formed as x - (lr lambda) x, and c^T - 1 is computed in double.
 // Dependencies between columns are unchanged: a row with several entries in the block is
 // ordered by its ticket, and a group starts when the rows of all its entries are final.
 // Groups are cut by the data alone (15 entries, the end of the column, or just before an
@@ -63,6 +62,7 @@ typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 
 #define CH 15                    // entries per group (the 16th row of X is the column's row)
 #define AUX_SC1 16               // cache policy of a buffer access: agent scope
+#define DPAPS_PAST_END 0x7F000000   // an offset past the end of any buffer of factors, also with a row's offset added (both below 2^31)
 
 // x, which is the same in all lanes, as a scalar
 __device__ __forceinline__ int64_t uniform_i64(int64_t x) {
@@ -118,6 +118,56 @@ __device__ __forceinline__ void solve_last(const float &acc, float (&hs)[NV], co
 // in front of the first step: a DPP operand must also keep five wait states from a write of the execution mask
 __device__ __forceinline__ void solve_first() { __asm__ volatile("s_nop 4"); }
 
+// NV (1 or 2) neighbouring floats of LDS
+template <int NV>
+__device__ __forceinline__ void lds_get(const float *p, float (&x)[NV]) {
+    if constexpr (NV == 2) { const f32x2 v = *reinterpret_cast<const f32x2 *>(p); x[0] = v[0]; x[1] = v[1]; }
+    else x[0] = *p;
+}
+template <int NV>
+__device__ __forceinline__ void lds_put(float *p, const float (&x)[NV]) {
+    if constexpr (NV == 2) *reinterpret_cast<f32x2 *>(p) = f32x2{x[0], x[1]};
+    else *p = x[0];
+}
+// this lane's components of a row to the store, both in one piece (WIDE: where rows start on 8 bytes) or each by itself
+template <int NV, bool WIDE, int AUX>
+__device__ __forceinline__ void put_row(const __amdgpu_buffer_rsrc_t buf, const float (&x)[NV], const int (&off)[NV]) {
+    if constexpr (NV == 2 && WIDE) __builtin_amdgcn_raw_buffer_store_b64(u32x2{__float_as_uint(x[0]), __float_as_uint(x[1])}, buf, off[0], 0, AUX);
+    else
+#pragma unroll
+        for (int cc = 0; cc < NV; ++cc) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(x[cc]), buf, off[cc], 0, AUX);
+}
+
+// ... and from the store, of the row that starts at row_off
+template <int NV, bool WIDE>
+__device__ __forceinline__ void get_row(const __amdgpu_buffer_rsrc_t buf, float (&x)[NV], int row_off, const int (&voff)[NV]) {
+    if constexpr (NV == 2 && WIDE) {
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(buf, row_off + voff[0], 0, 0);
+        const uint32_t v0 = v[0], v1 = v[1];
+        x[0] = __uint_as_float(v0); x[1] = __uint_as_float(v1);
+    } else
+#pragma unroll
+        for (int cc = 0; cc < NV; ++cc) x[cc] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, row_off + voff[cc], 0, 0));
+}
+
+// The new rows of a group from entry T on, to the store, and the column's factor along with them (scaled, after entry T
+// h_t = h c^(-T-1)); f, g: lane t of every row of 16 lanes has lr e_t c^t and lr e_t c^(-t-1); off: lane t has where row t starts.
+template <int T, int NV, bool WIDE>
+__device__ __forceinline__ void new_rows(const __amdgpu_buffer_rsrc_t wbuf, const float (&w)[CH][NV], float (&h_t)[NV], float f, float g, float delta,
+                                         const int (&voff)[NV], int off) {
+    const int row_off = rl_i(off, T);
+    float w_n[NV];
+    int to[NV];
+#pragma unroll
+    for (int cc = 0; cc < NV; ++cc) {
+        w_n[cc] = __builtin_fmaf(row_bcast_lane<T>(f), h_t[cc], __builtin_fmaf(-delta, w[T][cc], w[T][cc]));
+        h_t[cc] = __builtin_fmaf(row_bcast_lane<T>(g), w[T][cc], h_t[cc]);
+        to[cc] = row_off + voff[cc];
+    }
+    put_row<NV, WIDE, 0>(wbuf, w_n, to);
+    if constexpr (T + 1 < CH) new_rows<T + 1, NV, WIDE>(wbuf, w, h_t, f, g, delta, voff, off);
+}
+
 // NT = number of 16-component tiles of a factor row (rank <= 16 NT); A4: the rank is a multiple of 4,
 // so every row starts on a 16-byte boundary and is read in 16-byte pieces
 // (otherwise in 8-byte pieces where the rank is even, in 4-byte pieces where it is odd)
@@ -143,8 +193,8 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
             if (stopped != 0) return;
         }
     }
-    constexpr int RS = 16 * NT + 4;          // row stride of the staging area in floats (conflict-free for both read patterns)
-    constexpr int NV = (NT + 3) / 4;         // 64-component slices of a row
+    constexpr int RS = 16 * NT + 4;          // row stride of the staging area in floats (conflict-free for the accesses by rows and by tiles)
+    constexpr int NV = (NT + 3) / 4;         // components of a row per lane: NV neighbouring ones in the first part, 64 apart in the others
     // Called in a loop (AGENT_H): the thread's number, the rank and the step sizes pass through empty asm
     // statements, so that what depends on them - the table of powers of c, lane offsets - is not computed ahead
     // of the loop and held in registers all the way through it.
@@ -364,8 +414,8 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
             auto gs = [&](int gi) { return rl_i(gs_win, (gi < ng ? gi : ng) - gw); };   // start of group gi (the run's length past the last)
 
             // Read-ahead in two stages.  meta_load: the per-entry data of a group, entry pp + l into lane l.
-            // plan: whether all rows of the group are final, and their gather, straight into the layout of
-            // the dense products - lane (n16, hi) holds components 16 j + 4 hi .. + 3 of row n16 in xp[j].
+            // plan: whether all rows of the group are final, and their gather, row by row, a lane its NV neighbouring
+            // components (zero past the rank and for rows without an entry).
             // (Always executed, with positions clamped into the run: a load that is only issued on some
             // paths makes the compiler copy its result into the loop's registers right away, which waits.)
             int mq_row = 0, mq_info = (int)INFO_NONE;
@@ -375,38 +425,27 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
                 q = q < s1 ? q : s1 - 1;
                 mq_row = a.e_row[q]; mq_val = a.e_val[q]; mq_info = (int)a.e_info[q];
             };
-            int pf_row = 0, pf_info = (int)INFO_NONE, pf_n = 0;
+            int pf_off = DPAPS_PAST_END, pf_info = (int)INFO_NONE, pf_n = 0;   // where the row starts in the block's (bytes; no entry: past the end)
             float pf_val = 0.0f;
             bool pf_ready = false;
-            f32x4 xp[NT];
-            auto gather = [&](int n16, int hi) {
-                const int rid = bperm_i(pf_row, n16);
-                // byte offset of this lane's first piece; no entry: past the end, reads as zero
-                const uint32_t goff = n16 < pf_n ? (uint32_t)((rid - (int)blk_r0) * L + 4 * hi) * 4u : wspan;
+            float wn[CH][NV];
+            // (A row in one access: fewer lines are looked up than in accesses of a tile of every row, 64 bytes each wherever they
+            // start.  100k x 10k, rank 50: an epoch with its loss 6.91 ms that way, 6.68 this; rank 100 the same both ways.)
+            auto gather = [&](int ln) {
+                int voff[NV];                              // this lane's components, past the end where they do not exist
 #pragma unroll
-                for (int j = 0; j < NT; ++j) {
-                    if constexpr (A4) {
-                        // may run past the row's end (into the next row, or past the buffer's end)
-                        xp[j] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(wbuf, (int)goff + 64 * j, 0, 0));
-                    } else if (even_rank) {
-                        // rows start on 8-byte boundaries: two pieces of two components (both exist or neither)
+                for (int cc = 0; cc < NV; ++cc) voff[cc] = NV * ln + cc < L ? (NV * ln + cc) * 4 : DPAPS_PAST_END;
+                if (NV == 1 || A4 || even_rank) {
 #pragma unroll
-                        for (int q = 0; q < 4; q += 2) {
-                            const u32x2 pr = __builtin_amdgcn_raw_buffer_load_b64(
-                                wbuf, (16 * j + 4 * hi + q < L ? (int)goff : (int)wspan) + 64 * j + 4 * q, 0, 0);
-                            const uint32_t p0 = pr[0], p1 = pr[1];
-                            xp[j][q] = __uint_as_float(p0); xp[j][q + 1] = __uint_as_float(p1);
-                        }
-                    } else {
+                    for (int t = 0; t < CH; ++t) get_row<NV, true>(wbuf, wn[t], rl_i(pf_off, t), voff);
+                } else {
 #pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            xp[j][q] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
-                                wbuf, (16 * j + 4 * hi + q < L ? (int)goff : (int)wspan) + 64 * j + 4 * q, 0, 0));
-                    }
+                    for (int t = 0; t < CH; ++t) get_row<NV, false>(wbuf, wn[t], rl_i(pf_off, t), voff);
                 }
             };
-            auto plan = [&](int n, int n16, int hi) {     // the group of n entries whose data meta_load has fetched
-                pf_row = mq_row; pf_val = mq_val;
+            auto plan = [&](int n, int ln) {              // the group of n entries whose data meta_load has fetched
+                pf_off = lane < n ? (mq_row - (int)blk_r0) * L * 4 : DPAPS_PAST_END;
+                pf_val = mq_val;
                 pf_info = lane < n ? mq_info : (int)INFO_NONE;
                 pf_n = n;
                 const uint32_t slot = (uint32_t)pf_info & 0xFFFFu, seq = ((uint32_t)pf_info >> 16) & 0x7FFFu;
@@ -414,12 +453,12 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
                 if (lane < n && slot != INFO_SINGLE) ready = ticket_read(&ticket[slot]) == seq;
                 pf_ready = __ballot(ready) == ~0ull;      // all rows final now, before their loads are issued
                 __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                gather(n16, hi);
+                gather(ln);
             };
 
             int gi = mb;                                  // this wavefront's groups: mb, mb + T, ...
             meta_load(s0 + gs(gi));
-            plan(gs(gi + 1) - gs(gi), n16_, hi_);
+            plan(gs(gi + 1) - gs(gi), lane);
             meta_load(s0 + gs(gi + T));
             // everything asked for so far has arrived before the loop is entered, so that inside the loop
             // the read-ahead only ever has to wait for loads that were issued a whole group earlier
@@ -430,7 +469,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
                     const int q = gw + lane;
                     gs_win = a.gstart[gb + (q <= ng ? q : ng)];
                 }
-                int c_row = pf_row, c_info = pf_info;
+                int c_off = pf_off, c_info = pf_info;
                 float c_val = pf_val;
                 const int k = pf_n;                        // entries of this group
                 // The lane's coordinates once more, opaque to the compiler: everything derived from them
@@ -459,23 +498,22 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
                     }
                     __builtin_amdgcn_s_setprio(2);
                     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-                    gather(n16, hi);                      // same group, rows as they are now
+                    gather(ln);                           // same group, rows as they are now
                     // waited for here, on the rare path, so that where the paths join the common one is not
                     // made to wait for everything it has in flight
                     __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
                 }
-                // X: rows 0 .. 14 from the read-ahead (components past the rank are zero) go to the staging
-                // area; both dense products read X from there, so the registers of the read-ahead are free
-                // again at once
-                // (the first product and the inner products with h take them from the registers they are in)
+                // X: rows 0 .. 14 from the read-ahead go to the staging area (row 15 stays zero), where the registers of the
+                // read-ahead are free again, and come back in the layout of the dense product: lane (n16, hi) has
+                // components 16 j + 4 hi .. + 3 of row n16 in xp[j]
+                if (NV * ln < 16 * NT) {
 #pragma unroll
-                for (int q = 0; q < 4; ++q)
-                    if (16 * (NT - 1) + 4 * hi + q >= L) xp[NT - 1][q] = 0.0f;
-                if (n16 < 15) {
-#pragma unroll
-                    for (int j = 0; j < NT; ++j) *reinterpret_cast<f32x4 *>(&stg[n16 * RS + 16 * j + 4 * hi]) = xp[j];
+                    for (int t = 0; t < CH; ++t) lds_put<NV>(&stg[t * RS + NV * ln], wn[t]);
                 }
-                // ---- <w_s, w_t>: G = X X^T (row 15 of X is an old copy of h here; its products are not used)
+                f32x4 xp[NT];
+#pragma unroll
+                for (int j = 0; j < NT; ++j) xp[j] = *reinterpret_cast<const f32x4 *>(&stg[n16 * RS + 16 * j + 4 * hi]);
+                // ---- <w_s, w_t>: G = X X^T
                 f32x4 gm = {0.0f, 0.0f, 0.0f, 0.0f}, gm2 = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
                 for (int j = 0; j < NT; ++j) {
@@ -503,7 +541,9 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
                 // scaled: v_t c^(-t) = v_t + (c^(-t) - 1) v_t
                 const float v_row = bperm_f(c_val, n16);
                 float vs = __builtin_fmaf(v_row, cim1[n16], v_row);
-                float e_vec = 0.0f;                        // e_t in every lane with n16 == t
+                float e_vec = 0.0f, eps = 0.0f;            // e_t and e_t c^(-t) in every lane with n16 == t
+                float ho[NV];                              // h as it is now, lane l its components NV l .. (lanes past the row's 16 NT floats: any)
+                float wv[CH][NV];                          // the rows' components, likewise
                 {
                     // table entries for the new h, read before the wait as well
                     float cpm1_k = cpm1[k];
@@ -518,17 +558,11 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
 
                     // ---- the part that needs h as the previous group left it --------------------------------
                     f32x4 hq[NT];                          // h in quarters, for p_s = <w_s, h>
-                    float ho[NV];                          // h as it is now, lane l its components l, l + 64 (lanes past the row's 16 NT floats: any)
-                    int ck[NV];
-#pragma unroll
-                    for (int cc = 0; cc < NV; ++cc) ck[cc] = ln + 64 * cc < 16 * NT ? ln + 64 * cc : 0;
-                    // the rows' components for the new h further down (lane l: components l, l + 64 of every row)
-                    float wv[CH][NV];
+                    const int ck = NV * ln < 16 * NT ? NV * ln : 0;
+                    // the rows' components for the new h further down
                     if constexpr (RICH) {
 #pragma unroll
-                        for (int s = 0; s < CH; ++s)
-#pragma unroll
-                            for (int cc = 0; cc < NV; ++cc) wv[s][cc] = stg[s * RS + ck[cc]];
+                        for (int s = 0; s < CH; ++s) lds_get<NV>(&stg[s * RS + ck], wv[s]);
 #pragma unroll
                         for (int s = 0; s < CH; ++s)
 #pragma unroll
@@ -547,8 +581,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
                     __builtin_amdgcn_s_setprio(3);
 #pragma unroll
                     for (int j = 0; j < NT; ++j) hq[j] = *reinterpret_cast<const f32x4 *>(&hsh[16 * j + 4 * hi]);
-#pragma unroll
-                    for (int cc = 0; cc < NV; ++cc) ho[cc] = hsh[ck[cc]];
+                    lds_get<NV>(&hsh[ck], ho);
                     __builtin_amdgcn_sched_barrier(0);      // all of h asked for before the first product waits for its piece
                     float pq[4] = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
@@ -559,9 +592,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
                     // (with fewer registers they are asked for now, so that they arrive while the errors are being computed)
                     if constexpr (!RICH) {
 #pragma unroll
-                        for (int s = 0; s < CH; ++s)
-#pragma unroll
-                            for (int cc = 0; cc < NV; ++cc) wv[s][cc] = stg[s * RS + ck[cc]];
+                        for (int s = 0; s < CH; ++s) lds_get<NV>(&stg[s * RS + ck], wv[s]);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                     float p = (pq[0] + pq[1]) + (pq[2] + pq[3]);
@@ -602,105 +633,47 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
                     for (int cc = 0; cc < NV; ++cc) hn[cc] = __builtin_fmaf(lrck, hs[cc], hbase[cc]);
                     // the new h is complete: into LDS for the next group, which may start at once
                     {
-#pragma unroll
-                        for (int cc = 0; cc < NV; ++cc)
-                            if (ln + 64 * cc < L) hsh[ln + 64 * cc] = hn[cc];
+                        if (NV * ln < L) lds_put<NV>(&hsh[NV * ln], hn);    // (components past the rank stay zero)
                         compiler_fence();
                         ticket_write(hsq, (uint32_t)gi + 1u);
                         compiler_fence();
                         // to memory as the run's last group leaves it (an offset past the end writes nothing)
+                        int off[NV];
 #pragma unroll
-                        for (int cc = 0; cc < NV; ++cc) {
-                            const int off = (int)(ln + 64 * cc < L && gi + 1 == ng ? hoff + (uint32_t)(ln + 64 * cc) * 4u : hspan);
-                            if constexpr (AGENT_H) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(hn[cc]), hbuf, off, 0, AUX_SC1);
-                            else __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(hn[cc]), hbuf, off, 0, 0);
-                        }
+                        for (int cc = 0; cc < NV; ++cc) off[cc] = (int)(NV * ln + cc < L && gi + 1 == ng ? hoff + (uint32_t)(NV * ln + cc) * 4u : hspan);
+                        put_row<NV, A4, AGENT_H ? AUX_SC1 : 0>(hbuf, hn, off);
                         __builtin_amdgcn_s_setprio(2);
                     }
                     __builtin_amdgcn_sched_barrier(0);
                     // e_t = eps_t c^t in every lane with n16 == t, for the new rows below
                     e_vec = __builtin_fmaf(acc, cpm1_t, acc);
-                    // this wavefront's copy of h as it was (row 15 of X), for the new rows below
-#pragma unroll
-                    for (int cc = 0; cc < NV; ++cc)
-                        if (ln + 64 * cc < 16 * NT) stg[15 * RS + ln + 64 * cc] = ho[cc];
+                    eps = acc;
                 }
                 // read ahead: the rows of this wavefront's next group, the per-entry data of the one after (not
                 // earlier: the registers they arrive in are needed by the part above)
                 {
                     const int p1 = gs(gi + T), p2 = gs(gi + T + 1);
-                    plan(p2 - p1, n16, hi);
+                    plan(p2 - p1, ln);
                     meta_load(s0 + gs(gi + 2 * T));
                 }
 
-                // ---- the new rows: X' = X + (C - I) X, tile by tile; rows 0 .. k-1 go to the store ----------
-                // The product is formed transposed (X'^T = X^T (C - I)^T + X^T), which leaves lane (n16, hi) with
-                // components 16 tile + 4 hi .. + 3 of row n16 - the layout the rows were gathered in - so a row
-                // goes to the store in 16-byte pieces.  Byte offset of the lane's piece of tile 0 in the block's
-                // row factors (past the end for rows without an entry, row 15 among them):
-                const uint32_t dst = n16 < k ? (uint32_t)((bperm_i(c_row, n16) - (int)blk_r0) * L + 4 * hi) * 4u : wspan;
-                float ca[4];                               // (C - I)[t = n16][s = 4 hi + v]; row 15 is not needed any more
+                // ---- the new rows, entry by entry; rows 0 .. k-1 go to the store ----------------------------
+                // With the errors known, w_t' = c w_t + lr e_t h_(t-1) and h_t = c h_(t-1) + lr e_t w_t need no sum over
+                // components: a lane has its components of h and of every row, three multiply-adds per entry and
+                // component with h scaled by c^(-t), whose factors the instructions fetch from lane t themselves, and a row
+                // leaves in one piece.  (All 15 always, so that the number of stores in flight is known where the
+                // rows fetched meanwhile are waited for; offsets past the end write nothing.)
                 {
-                    // (the exchanges and the table reads all first, then the arithmetic: one wait for LDS, not eight)
-                    float es_all[4], cp[4];
+                    const float g_vec = -nlrc * eps, f_vec = (lr * e_vec) * cpow[n16];
+                    float h_t[NV];
+                    int voff[NV];                          // past the end for components that do not exist
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) es_all[v] = bperm_f(e_vec, 4 * hi + v);   // lane s (< 16) holds e_s (all lanes take part in the exchange)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int s = 4 * hi + v, pw = s == 15 ? n16 : n16 - 1 - s;
-                        cp[v] = cpow[pw > 0 ? pw : 0];
+                    for (int cc = 0; cc < NV; ++cc) {
+                        h_t[cc] = ho[cc];
+                        voff[cc] = NV * ln + cc < L ? (NV * ln + cc) * 4 : DPAPS_PAST_END;
                     }
-                    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        const int s = 4 * hi + v, t = n16;
-                        const float es = s < k ? es_all[v] : 0.0f;
-                        // C[t][s<t] = lr^2 e_t e_s c^(t-1-s),  C[t][t] - 1 = -lr lambda,  C[t][15] = lr e_t c^t
-                        float x = 0.0f;
-                        if (s < t) x = (lr * e_vec) * (lr * es) * cp[v];
-                        if (s == t) x = -delta;
-                        if (s == 15) x = lr * e_vec * cp[v];
-                        ca[v] = t < 15 ? x : 0.0f;
-                    }
-                }
-                // all of X is asked for (both layouts) before the first product waits for its operands: a tile's
-                // four matrix instructions depend on each other, and seven trips to LDS in between would double
-                // the time of this part
-                float xn[NT][4];
-                f32x4 xa[NT];
-#pragma unroll
-                for (int tile = 0; tile < NT; ++tile) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) xn[tile][v] = stg[(4 * hi + v) * RS + 16 * tile + n16];
-                    xa[tile] = *reinterpret_cast<const f32x4 *>(&stg[n16 * RS + 16 * tile + 4 * hi]);   // the X of X + (C - I) X
-                }
-                __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                for (int tile = 0; tile < NT; ++tile) {
-                    f32x4 acc = xa[tile];
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(xn[tile][v], ca[v], acc, 0, 0, 0);
-                    if constexpr (A4) {
-                        const bool comp = tile < NT - 1 || 16 * tile + 4 * hi < L;    // the piece exists (the rank is a multiple of 4)
-                        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, acc), wbuf, (int)(comp ? dst : wspan) + 64 * tile, 0, 0);
-                    } else {
-                        // (element by element into scalars first: a bit cast applied to a vector element directly
-                        // has been seen to pick element 0 every time)
-                        const float r0 = acc[0], r1 = acc[1], r2 = acc[2], r3 = acc[3];
-                        const float rr[4] = {r0, r1, r2, r3};
-                        if (even_rank) {
-#pragma unroll
-                            for (int q = 0; q < 4; q += 2) {
-                                const u32x2 pr = {__float_as_uint(rr[q]), __float_as_uint(rr[q + 1])};
-                                __builtin_amdgcn_raw_buffer_store_b64(pr, wbuf, (int)(16 * tile + 4 * hi + q < L ? dst : wspan) + 64 * tile + 4 * q, 0, 0);
-                            }
-                        } else {
-#pragma unroll
-                            for (int q = 0; q < 4; ++q)
-                                __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(rr[q]), wbuf,
-                                                                      (int)(16 * tile + 4 * hi + q < L ? dst : wspan) + 64 * tile + 4 * q, 0, 0);
-                        }
-                    }
+                    if (NV == 1 || A4 || even_rank) new_rows<0, NV, true>(wbuf, wv, h_t, f_vec, g_vec, delta, voff, c_off);
+                    else new_rows<0, NV, false>(wbuf, wv, h_t, f_vec, g_vec, delta, voff, c_off);
                 }
                 // ---- hand the rows on: the stores must have completed before the tickets move ---------
                 {

@@ -1,0 +1,35 @@
+"""Long column runs in groups of up to 15 entries, at ranks around the edges of how a group's rows are gathered and stored:
+one or two neighbouring components per lane, rows that start on 4, 8 or 16 bytes, a last tile with one component and a full
+one; runs shorter than a group, of whole groups and one more; against the sequential fp32 oracle."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("waves", [16, 12])
+@pytest.mark.parametrize("rank", [2, 3, 49, 62, 63, 64, 65, 66, 68, 97, 98, 99, 112, 126, 127, 128])
+def test_group_rows_at_edges_of_the_rank(rank, waves):
+    from paper_2002_00655_amd import workloads as wl
+    from _util import compare_state, gpu_epochs, oracle_epochs
+    from oracle.oracle import mf_block_ratings
+    from paper_2002_00655_amd.ps import OPT_MF_GROUPED, OPT_MF_HEAVY_LEN, OPT_MF_WAVES
+    rng = np.random.default_rng(rank)
+    w = wl.make_mf("tiny", scale=0.2, seed=3, rank=rank)
+    # columns of 1, 14, 15, 16, 29, 30, 31 and 46 entries and a repeated cell among what is there
+    rows, cols = [], []
+    for c, count in enumerate((1, 14, 15, 16, 29, 30, 31, 46)):
+        rows.append(rng.choice(w.m, count, replace=False)); cols.append(np.full(count, c))
+    keep = w.cols >= 8
+    w.rows = np.concatenate([w.rows[keep], *rows, rows[7][:3]]).astype(np.int32)
+    w.cols = np.concatenate([w.cols[keep], *cols, cols[7][:3]]).astype(np.int32)
+    w.vals = rng.standard_normal(w.rows.size).astype(np.float32)
+    rb, cb = np.array([0, 33, w.m], np.int64), np.array([0, 8, w.n], np.int64)
+    blocked = mf_block_ratings(w.m, w.n, w.rows, w.cols, w.vals, rb, cb)
+    sched = wl.cyclic_schedule(2)
+    print(f"case rank={rank} waves={waves} nnz={w.rows.size}", flush=True)
+    orc = oracle_epochs("f32", w, rb, cb, blocked, sched, epochs=2)
+    srv = gpu_epochs(w, rb, cb, blocked, sched, epochs=2, options=[(OPT_MF_WAVES, waves), (OPT_MF_GROUPED, 1), (OPT_MF_HEAVY_LEN, 4)])
+    # a step rounds each component a few times at its size (below 2): some 40 entries per row and column and two epochs of
+    # them stay within 1e-5, the tolerance of the other comparisons of the two kernels
+    compare_state(orc, srv, exact=False, atol=1e-5)
