@@ -315,41 +315,32 @@ __global__ __launch_bounds__(1024) void k_mf_sgd(SgdArgs a) {
 // ---------------------------------------------------------------------------
 // training error
 // ---------------------------------------------------------------------------
-// Products and sums in double.  What bounds it is the way of the factor rows to the compute units: 2 rows of 4 L
-// bytes per entry, far more than the entries themselves.  So
-// - 16 lanes take an entry, 4 entries a wavefront at a time, SSE_AHEAD times as many in flight: a lane holds the pieces
-//   j, j + 16, ... of both rows (V numbers each: 16 bytes where the rank is a multiple of 4, 8 where it is even), and the
-//   16 partial sums are added with four lane exchanges inside the vector unit;
+// Products and sums in double.  What bounds it is the way of the factor rows to the compute units - 2 rows of 4 L bytes per
+// entry, far more than the entries themselves - and the instructions on them.  So
+// - 8 lanes take an entry, 8 entries a wavefront at a time, SSE_AHEAD times as many in flight: a lane holds the pieces
+//   j, j + 8, ... of both rows (V numbers each: 16 bytes where the rank is a multiple of 4, 8 where it is even), and the
+//   8 partial sums are added with three lane exchanges inside the vector unit;
+// - the 8 lanes go through neighbouring entries one after the other, and most of those are of one column: its factor is read,
+//   and widened to double, where the column changes only;
 // - the entries come block by block, row-block major, and the workgroups that share a cache (every eighth: one compute
 //   die) go through one eighth of them side by side, so that the row factors of the row blocks under way stay in
-//   that cache and a column's factor is read by neighbours.
-// 480,189 x 17,770, 100M entries, rank 100: 4.7 ms (80 GB of factor rows asked for, 17 TB/s out of the caches), with one
-// wavefront per entry 19.2 ms; 2M x 200k, 100M entries: 7.0 ms, before 19.5; 4 entries ahead instead of 2: 5.0 and 6.9.
-constexpr int SSE_BLOCKS = 2048;          // at most: 8 wavefronts per vector unit; a multiple of the dies
+//   that cache.
+// 480,189 x 17,770, 100M entries, rank 100: 3.1 ms, 2M x 200k with as many: 4.6 ms, 100k x 10k, 10M entries, rank 50: 0.29 ms;
+// with 16 lanes per entry, entries of a column side by side and both rows read for each: 4.6, 7.0 and 0.36.
+// Two wavefronts per vector unit (SSE_BLOCKS): what matters is that those of a die are close to each other in the entries.
+// With 4: 3.1 and 5.9 ms; with 8, of which half start when the first are through: 3.1 and 6.3; with 1: 4.7 and 5.3; 1.5: 4.1 and 5.7.
+// A wavefront's batch longer than 64 entries (the column's factor is read anew in every batch): 256 3.2 and 7.5.
+constexpr int SSE_BLOCKS = 512;           // at most; a multiple of the dies
 constexpr int SSE_DIES = 8;
-constexpr int SSE_AHEAD = 2;
 // Workgroups for nnz entries: no more than have a batch of 64 for each of their 4 wavefronts.  (Which batch a wavefront
 // takes and the order of the partial sums are those of the full number; workgroups without a batch only add zeros, and
-// their launch and the way of their sums to the host: 300 entries 39.5 us, 41.2 with 2,048 workgroups.)
+// their launch and the way of their sums to the host.)
 static int sse_blocks(int64_t nnz) {
     const int64_t share = ((nnz + 63) / 64 + SSE_DIES - 1) / SSE_DIES;
     return (int)std::min<int64_t>(SSE_BLOCKS, SSE_DIES * std::max<int64_t>((share + 3) / 4, 1));
 }
 
-template <int V> struct SsePiece;
-template <> struct SsePiece<4> { typedef float4 type; };
-template <> struct SsePiece<2> { typedef float2 type; };
-template <> struct SsePiece<1> { typedef float type; };
-__device__ __forceinline__ void sse_mul_add(const float4 &x, const float4 &y, double &d) {
-    d = fma((double)x.x, (double)y.x, d); d = fma((double)x.y, (double)y.y, d);
-    d = fma((double)x.z, (double)y.z, d); d = fma((double)x.w, (double)y.w, d);
-}
-__device__ __forceinline__ void sse_mul_add(const float2 &x, const float2 &y, double &d) {
-    d = fma((double)x.x, (double)y.x, d); d = fma((double)x.y, (double)y.y, d);
-}
-__device__ __forceinline__ void sse_mul_add(const float &x, const float &y, double &d) { d = fma((double)x, (double)y, d); }
-
-// x of another lane of the same 16, by a data-parallel move
+// x of another lane of the same 8, by a data-parallel move
 template <int CTRL>
 __device__ __forceinline__ double sse_add_dpp(double x) {
     const uint64_t b = __builtin_bit_cast(uint64_t, x);
@@ -358,12 +349,12 @@ __device__ __forceinline__ double sse_add_dpp(double x) {
     return x + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// NR: pieces of a row per lane (ceil(ceil(L / V) / 16); V = 1: at least that), 0: any number, in a loop
+// NR: pieces of a row per lane (ceil(ceil(L / V) / 8); V = 1: at least that), 0: any number, in a loop
 template <int V, int NR>
 __global__ __launch_bounds__(256) void k_mf_sse(const int32_t *rows, const int32_t *cols, const float *vals, int64_t nnz,
                                                 const float *val, int64_t m, int32_t L, double *partial) {
-    typedef typename SsePiece<V>::type Piece;
-    const int lane = threadIdx.x & 63, j = lane & 15, grp = lane >> 4;
+    typedef float Piece __attribute__((ext_vector_type(V)));
+    const int lane = threadIdx.x & 63, j = lane & 7, first = lane & ~7;
     const int pieces = L / V;                               // (V divides the rank)
     // batches of 64 entries: this die's share, its wavefronts side by side
     const int64_t batches = (nnz + 63) / 64, share = (batches + SSE_DIES - 1) / SSE_DIES;
@@ -372,66 +363,76 @@ __global__ __launch_bounds__(256) void k_mf_sse(const int32_t *rows, const int32
     const int64_t step = (int64_t)(gridDim.x / SSE_DIES) * (blockDim.x >> 6);
     double acc = 0.0;
     for (int64_t b = die * share + (int64_t)(blockIdx.x / SSE_DIES) * (blockDim.x >> 6) + (threadIdx.x >> 6); b < b1; b += step) {
-        const int64_t p = b * 64 + lane;
+        const int64_t p = b * 64 + lane, p0 = b * 64 + first;                  // the 8 lanes' 8 entries start at p0
         const bool valid = p < nnz;
         const int32_t row = valid ? rows[p] : 0, col = valid ? cols[p] : 0;
         const float v = valid ? vals[p] : 0.0f;
-        for (int u0 = 0; u0 < 16; u0 += SSE_AHEAD) {        // entries 4 u + grp
-            if constexpr (NR > 0) {
-                Piece w[SSE_AHEAD][NR], h[SSE_AHEAD][NR];
+        if constexpr (NR > 0) {
+            constexpr int AHEAD = NR * V <= 16 ? 2 : 1;
+            auto in = [&](int r) { return (V > 1 && r + 1 < NR) || j + 8 * r < pieces; };   // (lanes past the row's end read its first piece and count it as zero)
+            int32_t last = -1;                              // the column whose factor is in h64
+            double h64[NR * V];
 #pragma unroll
-                for (int q = 0; q < SSE_AHEAD; ++q) {
-                    const int src = 4 * (u0 + q) + grp;
-                    const Piece *pw = reinterpret_cast<const Piece *>(val + (int64_t)__shfl(row, src) * L);
-                    const Piece *ph = reinterpret_cast<const Piece *>(val + (m + __shfl(col, src)) * (int64_t)L);
+            for (int r = 0; r < NR * V; ++r) h64[r] = 0.0;
+#pragma unroll 1
+            for (int u0 = 0; u0 < 8; u0 += AHEAD) {
+                Piece w[AHEAD][NR], h[AHEAD][NR];
+                bool fresh[AHEAD];
 #pragma unroll
-                    for (int r = 0; r < NR; ++r) {
-                        // (lanes past the row's end read its first piece and count it as zero)
-                        const bool in = (V > 1 && r + 1 < NR) || j + 16 * r < pieces;
-                        w[q][r] = pw[in ? j + 16 * r : 0];
-                        h[q][r] = ph[in ? j + 16 * r : 0];
+                for (int q = 0; q < AHEAD; ++q) {
+                    const int32_t c = __shfl(col, first + u0 + q);
+                    const Piece *pw = reinterpret_cast<const Piece *>(val + (int64_t)__shfl(row, first + u0 + q) * L);
+#pragma unroll
+                    for (int r = 0; r < NR; ++r) w[q][r] = pw[in(r) ? j + 8 * r : 0];
+                    fresh[q] = c != last;
+                    last = c;
+                    if (fresh[q]) {
+                        const Piece *ph = reinterpret_cast<const Piece *>(val + (m + c) * (int64_t)L);
+#pragma unroll
+                        for (int r = 0; r < NR; ++r) h[q][r] = ph[in(r) ? j + 8 * r : 0];
                     }
                 }
 #pragma unroll
-                for (int q = 0; q < SSE_AHEAD; ++q) {
+                for (int q = 0; q < AHEAD; ++q) {
+                    if (fresh[q]) {
+#pragma unroll
+                        for (int r = 0; r < NR; ++r)
+#pragma unroll
+                            for (int i = 0; i < V; ++i) h64[r * V + i] = (double)(in(r) ? h[q][r][i] : 0.0f);
+                    }
                     double d = 0.0;
 #pragma unroll
-                    for (int r = 0; r < NR; ++r) {
-                        double t = d;
-                        sse_mul_add(w[q][r], h[q][r], t);
-                        d = (V > 1 && r + 1 < NR) || j + 16 * r < pieces ? t : d;
-                    }
+                    for (int r = 0; r < NR; ++r)
+#pragma unroll
+                        for (int i = 0; i < V; ++i) d = fma((double)(in(r) ? w[q][r][i] : 0.0f), h64[r * V + i], d);
                     d = sse_add_dpp<0xB1>(d);               // quad_perm [1,0,3,2]: pairs
                     d = sse_add_dpp<0x4E>(d);               // quad_perm [2,3,0,1]: quads
                     d = sse_add_dpp<0x141>(d);              // row_half_mirror: 8 lanes
-                    d = sse_add_dpp<0x140>(d);              // row_mirror: 16 lanes
-                    const int src = 4 * (u0 + q) + grp;
-                    const double e = (double)__shfl(v, src) - d;
-                    acc += b * 64 + src < nnz ? e * e : 0.0;
+                    const double e = (double)__shfl(v, first + u0 + q) - d;
+                    acc += p0 + u0 + q < nnz ? e * e : 0.0;
                 }
-            } else {
-                for (int q = 0; q < SSE_AHEAD; ++q) {
-                    const int src = 4 * (u0 + q) + grp;
-                    const Piece *pw = reinterpret_cast<const Piece *>(val + (int64_t)__shfl(row, src) * L);
-                    const Piece *ph = reinterpret_cast<const Piece *>(val + (m + __shfl(col, src)) * (int64_t)L);
-                    double d = 0.0;
-                    for (int k = j; k < pieces; k += 16) sse_mul_add(pw[k], ph[k], d);
-                    d = sse_add_dpp<0xB1>(d);
-                    d = sse_add_dpp<0x4E>(d);
-                    d = sse_add_dpp<0x141>(d);
-                    d = sse_add_dpp<0x140>(d);
-                    const double e = (double)__shfl(v, src) - d;
-                    acc += b * 64 + src < nnz ? e * e : 0.0;
-                }
+            }
+        } else {
+            for (int u = 0; u < 8; ++u) {
+                const float *pw = val + (int64_t)__shfl(row, first + u) * L, *ph = val + (m + __shfl(col, first + u)) * (int64_t)L;
+                double d = 0.0;
+                for (int k = j; k < pieces; k += 8)
+#pragma unroll
+                    for (int i = 0; i < V; ++i) d = fma((double)pw[k * V + i], (double)ph[k * V + i], d);
+                d = sse_add_dpp<0xB1>(d);
+                d = sse_add_dpp<0x4E>(d);
+                d = sse_add_dpp<0x141>(d);
+                const double e = (double)__shfl(v, first + u) - d;
+                acc += p0 + u < nnz ? e * e : 0.0;
             }
         }
     }
-    __shared__ double s[16];                                // the 4 entries of 4 wavefronts
-    if (j == 0) s[threadIdx.x >> 4] = acc;
+    __shared__ double s[32];                                // the 8 entries of 4 wavefronts
+    if (j == 0) s[threadIdx.x >> 3] = acc;
     __syncthreads();
     if (threadIdx.x == 0) {
         double t = 0.0;
-        for (int i = 0; i < 16; ++i) t += s[i];
+        for (int i = 0; i < 32; ++i) t += s[i];
         partial[blockIdx.x] = t;
     }
 }
@@ -763,23 +764,33 @@ extern "C" int mf_train_sse(ps_handle ps, double *sse_host_out, void *stream) {
     double *partial = (double *)ps->ws;
 #define MF_SSE(V, NR) k_mf_sse<V, NR><<<blocks, 256, 0, st>>>(f.row, f.col, f.val, f.nnz, ps->val, f.m, L, partial)
     if (L % 4 == 0) {
-        switch ((L / 4 + 15) / 16) {
+        switch ((L / 4 + 7) / 8) {
         case 1: MF_SSE(4, 1); break;
         case 2: MF_SSE(4, 2); break;
         case 3: MF_SSE(4, 3); break;
-        default: MF_SSE(4, 4); break;
+        case 4: MF_SSE(4, 4); break;
+        case 5: MF_SSE(4, 5); break;
+        case 6: MF_SSE(4, 6); break;
+        case 7: MF_SSE(4, 7); break;
+        case 8: MF_SSE(4, 8); break;
+        default: MF_SSE(4, 0); break;
         }
     } else if (L % 2 == 0) {
-        switch ((L / 2 + 15) / 16) {
+        switch ((L / 2 + 7) / 8) {
         case 1: MF_SSE(2, 1); break;
         case 2: MF_SSE(2, 2); break;
         case 3: MF_SSE(2, 3); break;
         case 4: MF_SSE(2, 4); break;
+        case 5: MF_SSE(2, 5); break;
+        case 6: MF_SSE(2, 6); break;
+        case 7: MF_SSE(2, 7); break;
+        case 8: MF_SSE(2, 8); break;
         default: MF_SSE(2, 0); break;
         }
-    } else if (L <= 32) MF_SSE(1, 2);
-    else if (L <= 64) MF_SSE(1, 4);
-    else if (L <= 128) MF_SSE(1, 8);
+    } else if (L <= 16) MF_SSE(1, 2);
+    else if (L <= 32) MF_SSE(1, 4);
+    else if (L <= 64) MF_SSE(1, 8);
+    else if (L <= 128) MF_SSE(1, 16);
     else MF_SSE(1, 0);
 #undef MF_SSE
     PS_HIP(ps, hipGetLastError());
