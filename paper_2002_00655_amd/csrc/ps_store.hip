@@ -8,6 +8,7 @@
 #include <cstring>
 #include <mutex>
 #include <new>
+#include <type_traits>
 
 // ---------------------------------------------------------------------------
 // host helpers
@@ -418,6 +419,13 @@ __device__ __forceinline__ uint64_t readlane_u64(uint64_t x, int l) {
     return ((uint64_t)hi << 32) | lo;
 }
 
+// x, which is the same in all lanes, as a scalar
+__device__ __forceinline__ uint64_t uniform_u64(uint64_t x) {
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)x);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(x >> 32));
+    return ((uint64_t)hi << 32) | lo;
+}
+
 constexpr uint64_t NOKEY = ~0ull;                                      // no key looks like this
 
 // Of one range of cnt sorted positions, lane t holding position t's key (mk), the key before it (before) and where its
@@ -531,6 +539,126 @@ __global__ __launch_bounds__(64) void k_push_tiny(RouteArgs route, const int64_t
     const uint64_t mk = ((uint64_t)hi << 32) | lo;
     const uint64_t up = __shfl_up(mk, 1);
     push_range(n, 0, PUSH_RANGE, 0, mk, lane > 0 && lane < n ? up : NOKEY, mp, NOKEY, NOKEY, 0, blockIdx.x * 64 + lane, L, deltas, val, (float *)nullptr);
+}
+
+// A push of up to FEW_KEYS keys in one launch, without a sort: the sums are those of k_push_ranges and k_push_join, bit for
+// bit, and what they need of a key's place in the order is counted.  Every workgroup checks all keys and has them in LDS.  A
+// wavefront takes a position: it compares the position's key with all keys, and if no position before it has the same, the number
+// of smaller keys is where the key's terms start among the sorted ones - so where its ranges of 64 begin - and the positions
+// with the same key are its terms, in order.  A key of more than FEW_OWN ranges is worked on by the whole workgroup, a
+// range per wavefront, its sums in LDS.  The first route.blocks workgroups count the statistics.
+// Bound by a launch and two trips to memory behind each other (keys, rows), above 1,024 keys by the comparisons.  A push of 333 keys of
+// 100 values on 256 nodes: 7.6 us, sorted and added in three launches 16.8; 2,048 keys 13.3 and 27.3, all of them one key 28.2 and 33.1,
+// of 20 keys 17.2 and 32.0 (78 with a workgroup's positions side by side).
+constexpr int FEW_THREADS = 1024, FEW_WAVES = FEW_THREADS / 64, FEW_OWN = 2, FEW_RANGES = (int)FEW_KEYS / PUSH_RANGE + 1;
+template <class Piece>
+__global__ __launch_bounds__(FEW_THREADS) void k_push_few(RouteArgs route, const int64_t *keys, int n, int32_t P, const Piece *deltas, Piece *val,
+                                                          int64_t K, int32_t *err) {
+    constexpr size_t SUMS = (size_t)FEW_KEYS * 8, FEW_LDS = SUMS + (size_t)FEW_RANGES * 64 * sizeof(Piece);
+    __shared__ __attribute__((aligned(16))) unsigned char mem[FEW_LDS > sizeof(RouteLds) ? FEW_LDS : sizeof(RouteLds)];
+    __shared__ uint32_t many;                                          // which wavefronts' keys the whole workgroup works on,
+    __shared__ u64 many_mask[FEW_WAVES][FEW_KEYS / 64], many_key[FEW_WAVES];   // and what they found of them
+    __shared__ int many_start[FEW_WAVES], many_count[FEW_WAVES];
+    const bool counts = (int)blockIdx.x < route.blocks;
+    uint64_t *lk = reinterpret_cast<uint64_t *>(mem);
+    Piece *sums = reinterpret_cast<Piece *>(mem + SUMS);
+    if (threadIdx.x == 0) many = 0;
+    if (few_keys_off<2>(keys, n, K, err, [&](int64_t p, int64_t k) { lk[p] = (uint64_t)k; })) return;
+    if (counts) {
+        __syncthreads();                                               // (the keys in LDS are not needed here)
+        if (blockIdx.y == 0) route_access_block(route, *reinterpret_cast<RouteLds *>(mem), blockIdx.x);
+        return;
+    }
+    constexpr int UN = sizeof(Piece) == 16 ? 16 : 32;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), chunks = (n + 63) / 64;
+    // (the positions dealt out to the workgroups in turn, shifted from turn to turn: frequent keys are first named by the first
+    // positions, or at equal distances, and a workgroup takes its own one after the other)
+    const int groups = (int)(gridDim.x - (unsigned)route.blocks), mine = wave * groups + ((int)(blockIdx.x - (unsigned)route.blocks) + 5 * wave) % groups;
+    const int c = blockIdx.y * 64 + lane;
+    const bool in = c < P;
+    u64 mask = 0;                                                      // lane i: which of the positions 64 i .. have the key
+    int start = 0, count = 0;                                          // its terms among the sorted ones: the first, how many
+    uint64_t key = 0;
+    // position p's key; false if a position before p has it, or there is no position p
+    auto look = [&](int p) {
+        mask = 0; start = 0; count = 0;
+        if (p >= n) return false;
+        key = uniform_u64(lk[p]);
+        for (int i = 0; i < chunks; ++i) {
+            const bool there = 64 * i + lane < n;
+            const uint64_t k = there ? lk[64 * i + lane] : NOKEY;
+            const u64 same = __ballot(there && k == key);
+            if (64 * i <= p && (64 * i + 63 < p ? same : same & ((1ull << (p & 63)) - 1ull)) != 0) return false;
+            start += __popcll(__ballot(there && k < key));
+            count += __popcll(same);
+            mask = lane == i ? same : mask;
+        }
+        return true;
+    };
+    // the sum of the key's terms [lo, hi), one after the other, onto the stored value (STORED) or zero
+    auto sum = [&](int lo, int hi, auto stored) {
+        Piece v = {};
+        if constexpr (decltype(stored)::value)
+            if (in) v = val[(int64_t)key * P + c];
+        int at = 0, seen = 0;                                          // the positions from 64 at on, `seen` terms are before those
+        u64 m = readlane_u64(mask, 0);
+        while (seen + __popcll(m) <= lo) { seen += __popcll(m); m = readlane_u64(mask, ++at); }
+        for (; seen < lo; ++seen) m &= m - 1ull;
+        while (lo < hi) {
+            Piece d[UN];
+            int got = 0;
+#pragma unroll
+            for (int u = 0; u < UN; ++u) {
+                d[u] = Piece{};
+                if (lo + u < hi) {
+                    while (m == 0) m = readlane_u64(mask, ++at);
+                    const int p = 64 * at + __ffsll((long long)m) - 1;
+                    m &= m - 1ull;
+                    if (in) d[u] = deltas[(int64_t)p * P + c];
+                    ++got;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < UN; ++u)
+                if (u < got) v = v + d[u];
+            lo += got;
+        }
+        return v;
+    };
+    constexpr std::integral_constant<bool, true> onto_stored{};
+    constexpr std::integral_constant<bool, false> onto_zero{};
+    // range r of the key's terms ends before term
+    auto end_of = [&](int r) { const int e = (start / PUSH_RANGE + r + 1) * PUSH_RANGE - start; return e < count ? e : count; };
+    if (look(mine)) {
+        const int ranges = (start + count - 1) / PUSH_RANGE - start / PUSH_RANGE + 1;
+        if (ranges <= FEW_OWN) {
+            Piece v = sum(0, end_of(0), onto_stored);
+            for (int r = 1; r < ranges; ++r) v = v + sum(end_of(r - 1), end_of(r), onto_zero);
+            if (in) val[(int64_t)key * P + c] = v;
+        } else {
+            if (lane < (int)FEW_KEYS / 64) many_mask[wave][lane] = mask;
+            if (lane == 0) { many_key[wave] = key; many_start[wave] = start; many_count[wave] = count; atomicOr(&many, 1u << wave); }
+        }
+    }
+    __syncthreads();
+    uint32_t left = (uint32_t)__builtin_amdgcn_readfirstlane((int)many);
+    while (left != 0) {
+        const int w = __ffs((int)left) - 1;
+        left &= left - 1u;
+        mask = lane < (int)FEW_KEYS / 64 ? many_mask[w][lane] : 0;
+        key = uniform_u64(many_key[w]);
+        start = __builtin_amdgcn_readfirstlane(many_start[w]);
+        count = __builtin_amdgcn_readfirstlane(many_count[w]);
+        const int ranges = (start + count - 1) / PUSH_RANGE - start / PUSH_RANGE + 1;
+        for (int r = wave; r < ranges; r += FEW_WAVES) sums[r * 64 + lane] = r == 0 ? sum(0, end_of(0), onto_stored) : sum(end_of(r - 1), end_of(r), onto_zero);
+        __syncthreads();
+        if (wave == 0 && in) {
+            Piece v = sums[lane];
+            for (int r = 1; r < ranges; ++r) v = v + sums[r * 64 + lane];
+            val[(int64_t)key * P + c] = v;
+        }
+        __syncthreads();                                               // the sums' place is used again
+    }
 }
 
 // Second kernel: the wavefront of the range in which a key's terms start and do not end adds the partial sums
@@ -820,6 +948,22 @@ static int push_width(int32_t L, const float *deltas) {
     if (L > 64 && L % 2 == 0 && ((uintptr_t)deltas & 7) == 0) return 2;
     return 1;
 }
+static int push_few(dpaps_ps *ps, RouteArgs stats, const int64_t *keys, int64_t n, const float *deltas, hipStream_t st) {
+    if (stats.blocks) stats.blocks = 1;                // (its threads take all keys in one go)
+    const int width = push_width(ps->L, deltas);
+    const int32_t P = ps->L / width;
+    const dim3 grid((unsigned)stats.blocks + grid_for(n, FEW_WAVES), (unsigned)((P + 63) / 64));
+#define FEW(PIECE)                                                                                                                       \
+    k_push_few<PIECE><<<grid, FEW_THREADS, 0, st>>>(stats, keys, (int)n, P, reinterpret_cast<const PIECE *>(deltas), reinterpret_cast<PIECE *>(ps->val), ps->K, ps->err)
+    if (width == 4) FEW(f32x4); else if (width == 2) FEW(f32x2); else FEW(float);
+#undef FEW
+    PS_HIP(ps, hipGetLastError());
+    return PS_OK;
+}
+// A push whose sums need no sorted pairs: one launch.
+static int push_at_once(dpaps_ps *ps, const RouteArgs &stats, const int64_t *keys, int64_t n, const float *deltas, hipStream_t st) {
+    return n <= PUSH_RANGE ? push_tiny(ps, stats, keys, n, deltas, st) : push_few(ps, stats, keys, n, deltas, st);
+}
 // stats: an access to be counted along with the sums; done: what has been added already
 static int push_add(dpaps_ps *ps, int64_t n, const float *deltas, const RouteArgs &stats, const PushDone &done, hipStream_t st) {
     if (n != ps->push_sorted_n || !ps->push_base) { ps->last_error = "push: the sums do not follow their sort"; return PS_EINVAL; }
@@ -867,23 +1011,24 @@ int dpaps_push_add_step(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64
                     done, st);
 }
 
-// The same for a step of at most dpaps_few_keys() keys, checked: the sort and the sums.
+// The same for a step of at most dpaps_few_keys() keys: one launch, unless its terms are to be added strictly in order or
+// its accesses are counted one after the other.
 int64_t dpaps_few_keys() { return FEW_KEYS; }
 int dpaps_push_few_step(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, const float *deltas, hipStream_t st) {
-    if (n > PUSH_RANGE || ps->opt_push_sequential || ps->loc) {
+    if (ps->opt_push_sequential || ps->loc) {
         const int rc = dpaps_push_sort(ps, keys, n, st);
         return rc ? rc : dpaps_push_add_step(ps, worker, keys, n, deltas, PushDone{}, st);
     }
     const RouteArgs a = route_args(ps, worker, keys, n, PS_STAT_PULL_LOCAL, PS_STAT_PULL_REMOTE, PS_STAT_PUSH_LOCAL, PS_STAT_PUSH_REMOTE, st);
-    return push_tiny(ps, a, keys, n, deltas, st);
+    return push_at_once(ps, a, keys, n, deltas, st);
 }
 
 // One push call with its scratch in `base` (NULL: the handle's own, which grows): the keys checked by the sort's first
 // kernel, the sums with the statistics beside them.
 static int push_call(dpaps_ps *ps, void *base, int32_t worker, const int64_t *keys, int64_t n, const float *deltas, hipStream_t st) {
-    const bool tiny = n <= PUSH_RANGE && !ps->opt_push_sequential;
+    const bool at_once = n <= FEW_KEYS && !ps->opt_push_sequential;
     int rc;
-    if (!tiny) {
+    if (!at_once) {
         if (!base) {
             rc = dpaps_ws_reserve(ps, push_layout(ps, n).bytes);
             if (rc) return rc;
@@ -893,7 +1038,7 @@ static int push_call(dpaps_ps *ps, void *base, int32_t worker, const int64_t *ke
         if (rc) return rc;
     }
     const RouteArgs a = route_args(ps, worker, keys, n, PS_STAT_PUSH_LOCAL, PS_STAT_PUSH_REMOTE, -1, -1, st);
-    rc = tiny ? push_tiny(ps, a, keys, n, deltas, st) : push_add(ps, n, deltas, a, PushDone{}, st);
+    rc = at_once ? push_at_once(ps, a, keys, n, deltas, st) : push_add(ps, n, deltas, a, PushDone{}, st);
     return rc ? rc : cache_replies(ps, worker, keys, n, st);
 }
 

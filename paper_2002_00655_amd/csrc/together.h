@@ -9,20 +9,25 @@
 // Whether a call of few keys is to do nothing: a key is out of range, or the flag is set.  Every workgroup of the call's
 // one kernel looks at all of the keys before it does anything else, so that a bad call changes nothing, and no thread
 // leaves before all have looked.  Sets the error; the same in all threads.
-// AHEAD: keys of a thread whose reads are on their way together.
+// AHEAD: keys of a thread whose reads are on their way together.  keep(p, k): called for every key as it is read.
 constexpr int64_t FEW_KEYS = 2048;
-template <int AHEAD = 1>
-__device__ __forceinline__ bool few_keys_off(const int64_t *keys, int64_t n, int64_t K, int32_t *err) {
+template <int AHEAD, class Keep>
+__device__ __forceinline__ bool few_keys_off(const int64_t *keys, int64_t n, int64_t K, int32_t *err, Keep keep) {
     const bool was_off = *(volatile const int32_t *)err != 0;
     bool off = was_off;
 #pragma unroll AHEAD
     for (int64_t p = threadIdx.x; p < n; p += blockDim.x) {
         const int64_t k = keys[p];
+        keep(p, k);
         off |= k < 0 || k >= K;
     }
     const bool any = __syncthreads_or(off ? 1 : 0) != 0;
     if (any && threadIdx.x == 0 && !was_off) atomicExch(err, PS_EKEY);     // (an error that stands already is kept)
     return any;
+}
+template <int AHEAD = 1>
+__device__ __forceinline__ bool few_keys_off(const int64_t *keys, int64_t n, int64_t K, int32_t *err) {
+    return few_keys_off<AHEAD>(keys, n, K, err, [](int64_t, int64_t) {});
 }
 
 // One thread's look at the flag, for the whole workgroup: what stands in `word` (in LDS) after the next barrier holds for all.
