@@ -16,6 +16,8 @@
 #include "common.h"
 #include "kge_slots.h"
 #include "mf_device.h"
+#include "route.h"
+#include "together.h"
 
 #include <algorithm>
 #include <type_traits>
@@ -56,6 +58,35 @@ template <bool EXACT>
 __device__ __forceinline__ Upd adagrad(float g, float G, float lr, float eps) {
     if constexpr (EXACT) return {-lr * g / (float)sqrt((double)(G + g * g + eps)), g * g};
     else return {(-lr * g) * __builtin_amdgcn_rsqf(G + g * g + eps), g * g};
+}
+
+// dloss/dscore of one scored triple: -label sigmoid(-label score), written so that nothing overflows; EXACT: the
+// exponential in double and rounded to float, as a sequential fp32 program has it
+template <bool EXACT>
+__device__ __forceinline__ float dloss(float label, float sc) {
+    const float z = -label * sc;
+    const float na = z >= 0.0f ? -z : z;                             // -|z|
+    float ex;
+    if constexpr (EXACT) ex = (float)exp((double)na);
+    else ex = __builtin_amdgcn_exp2f(na * 1.44269504088896340736f);   // the hardware's 2^x, good to one unit in the last place
+    const float sig = z >= 0.0f ? 1.0f / (1.0f + ex) : ex / (1.0f + ex);
+    return -label * sig;
+}
+// the losses of a data point's scored triples, added in their order (lane t: triple t, t < per; the positive one is triple 0);
+// the same in all lanes
+__device__ __forceinline__ double loss_of(float score, int per) {
+    const float label = (threadIdx.x & 63) == 0 ? 1.0f : -1.0f;
+    const float z = -label * score;
+    const double en = exp((double)(z >= 0.0f ? -z : z));
+    const double ls = z >= 0.0f ? (double)z + log1p(en) : log1p(en);
+    double sum = 0.0;
+    for (int i = 0; i < per; ++i) {
+        const uint64_t bits = __builtin_bit_cast(uint64_t, ls);
+        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bits, i);
+        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(bits >> 32), i);
+        sum += __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+    }
+    return sum;
 }
 
 // One wavefront per data point - a positive triple and its negatives (Appendix A: the negatives are derived from
@@ -138,21 +169,10 @@ __global__ __launch_bounds__(256) void k_kge_group(KgeBatch t, int32_t D, float 
         const float sc = total(term);
         score = lane == 0 ? sc : score;
     }
-    // dloss/dscore of one scored triple (the same value in every lane): -label sigmoid(-label score), written so that
-    // nothing overflows; EXACT: the exponential in double and rounded to float, as a sequential fp32 program has it
-    auto dloss = [](float label, float sc) {
-        const float z = -label * sc;
-        const float na = z >= 0.0f ? -z : z;                         // -|z|
-        float ex;
-        if constexpr (EXACT) ex = (float)exp((double)na);
-        else ex = __builtin_amdgcn_exp2f(na * 1.44269504088896340736f);   // the hardware's 2^x, good to one unit in the last place
-        const float sig = z >= 0.0f ? 1.0f / (1.0f + ex) : ex / (1.0f + ex);
-        return -label * sig;
-    };
     // the gradients of the subject's, the relation's and the object's slot, started by the positive triple
     float gs[NC][2], gr[NC][2], go[NC][2];
     {
-        const float dl = dloss(1.0f, rl_f(score, 0));
+        const float dl = dloss<EXACT>(1.0f, rl_f(score, 0));
 #pragma unroll
         for (int c = 0; c < NC; ++c) {
             gs[c][0] = 0.0f + dl * (rr[c] * orl[c] + ri[c] * oi[c]); gs[c][1] = 0.0f + dl * (rr[c] * oi[c] - ri[c] * orl[c]);
@@ -200,7 +220,7 @@ __global__ __launch_bounds__(256) void k_kge_group(KgeBatch t, int32_t D, float 
                 const bool alone = flag[q] != done.id;                 // (the same in all lanes)
                 float *un = alone ? store + kq[q] * L : u0 + (int64_t)(slot0 + j0 + q) * L;
                 score = lane == slot0 - 2 + j0 + q ? sc[q] : score;
-                const float dl = dloss(-1.0f, sc[q]);
+                const float dl = dloss<EXACT>(-1.0f, sc[q]);
 #pragma unroll
                 for (int c = 0; c < NC; ++c) {
                     const uint32_t k = (uint32_t)lane + 64u * c;
@@ -224,20 +244,10 @@ __global__ __launch_bounds__(256) void k_kge_group(KgeBatch t, int32_t D, float 
     };
     negatives(std::false_type{}, t.neg_subj, ns, 3);
     negatives(std::true_type{}, t.neg_obj, no, 3 + ns);
-    // the losses of all scored triples at once (lane t: triple t; the positive one is triple 0)
-    {
-        const float label = lane == 0 ? 1.0f : -1.0f;
-        const float z = -label * score;
-        const double en = exp((double)(z >= 0.0f ? -z : z));
-        const double ls = z >= 0.0f ? (double)z + log1p(en) : log1p(en);
-        double loss_sum = 0.0;
-        for (int i = 0; i < 1 + ns + no; ++i) {
-            const uint64_t bits = __builtin_bit_cast(uint64_t, ls);
-            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)bits, i);
-            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(bits >> 32), i);
-            loss_sum += __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
-        }
-        if (lane == 0) loss[b] = loss_sum;
+    // the losses of all scored triples at once, if anybody asks for them
+    if (loss) {
+        const double sum = loss_of(score, 1 + ns + no);
+        if (lane == 0) loss[b] = sum;
     }
     // subject, relation, object: one AdaGrad step each on the summed gradient, with the accumulators as pulled
 #pragma unroll
@@ -255,6 +265,111 @@ __global__ __launch_bounds__(256) void k_kge_group(KgeBatch t, int32_t D, float 
             (u0 + 2 * L + ft)[k] = uo.dt; (u0 + 2 * L + fg)[k] = uo.dg;
         }
     }
+}
+
+// A step of so few data points that their slots fit side by side in one workgroup's LDS: all of it in one launch - the keys
+// checked, every slot's row read once, a wavefront per scored triple for the scores and one per slot for gradient, AdaGrad step and
+// sum, each slot's terms in the order of the other path.  A second workgroup counts the statistics.
+// Bound by a launch and two trips to memory, keys and rows.  A data point with 5 + 5 negatives, dim 100, and its
+// rows read back: 19.7 us, 23.2 with the update rows and the push in launches of their own (11 + 6 us), which is what the host takes now.
+// LDS: the keys, the rows as pulled, the update rows, and the derivatives of the scored triples' losses.
+constexpr int KGE_FEW_SLOTS = 64, KGE_FEW_THREADS = 1024, KGE_FEW_LDS = 128 << 10;
+static size_t kge_few_lds(int64_t slots, int32_t L) { return (size_t)slots * 2 * L * 4 > sizeof(RouteLds) ? (size_t)slots * 2 * L * 4 : sizeof(RouteLds); }
+__global__ __launch_bounds__(KGE_FEW_THREADS) void k_kge_few(RouteArgs route, KgeBatch t, int32_t D, float lr, float eps, float *store, int64_t K, double *loss,
+                                                             int32_t *err) {
+    extern __shared__ __attribute__((aligned(16))) float mem[];
+    __shared__ int64_t key[KGE_FEW_SLOTS];
+    __shared__ float score[KGE_FEW_SLOTS], dl[KGE_FEW_SLOTS];
+    const int ns = t.ns, no = t.no, rows = 3 + ns + no, per = 1 + ns + no, slots = (int)t.batch * rows, L = 4 * D;
+    if ((int)threadIdx.x < slots) key[threadIdx.x] = slot_key(t, (int)threadIdx.x / rows, (int)threadIdx.x % rows);
+    __syncthreads();
+    if (few_keys_off(key, slots, K, err)) return;
+    if (blockIdx.x > 0) {
+        route.keys = key;
+        route_access_block(route, *reinterpret_cast<RouteLds *>(mem), 0);
+        return;
+    }
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), waves = blockDim.x >> 6;
+    float *const val = mem, *const upd = mem + (size_t)slots * L;
+    for (int j = wave; j < slots; j += waves) {
+        const float *from = store + key[j] * L;
+        for (int k = lane; k < L; k += 64) val[j * L + k] = from[k];
+    }
+    __syncthreads();
+    // the score of triple i of data point b (0: the positive one, then the subject and the object negatives) - its subject's, relation's and
+    // object's slots - and the derivative of its loss
+    for (int i = wave; i < (int)t.batch * per; i += waves) {
+        const int b = i / per, q = i - b * per;
+        const float *base = val + b * rows * L, *n = base + (q + 2) * L;
+        const float *s = q >= 1 && q <= ns ? n : base, *r = base + L, *o = q > ns ? n : base + 2 * L;
+        float part = 0.0f;
+        for (int k = lane; k < D; k += 64)
+            part += s[k] * r[k] * o[k] + s[D + k] * r[k] * o[D + k] + s[k] * r[D + k] * o[D + k] - s[D + k] * r[D + k] * o[k];
+        const float sc = wave_sum(part), d = dloss<false>(q == 0 ? 1.0f : -1.0f, sc);
+        if (lane == 0) { score[i] = sc; dl[i] = d; }
+    }
+    __syncthreads();
+    // every slot's gradient, the terms of the triples it occurs in in their order, and its AdaGrad step with the accumulators as pulled
+    for (int j = wave; j < slots; j += waves) {
+        const int b = j / rows, jj = j - b * rows;
+        const float *base = val + b * rows * L, *s = base, *r = base + L, *o = base + 2 * L, *own = base + jj * L, *d = dl + b * per;
+        for (int k = lane; k < D; k += 64) {
+            const float sr = s[k], si = s[D + k], rr = r[k], ri = r[D + k], orl = o[k], oi = o[D + k];
+            float g0, g1;
+            if (jj == 0) {
+                g0 = 0.0f + d[0] * (rr * orl + ri * oi); g1 = 0.0f + d[0] * (rr * oi - ri * orl);
+                for (int q = 0; q < no; ++q) {
+                    const float *n = base + (3 + ns + q) * L;
+                    const float nr = n[k], ni = n[D + k], dq = d[1 + ns + q];
+                    g0 = g0 + dq * (rr * nr + ri * ni); g1 = g1 + dq * (rr * ni - ri * nr);
+                }
+            } else if (jj == 1) {
+                g0 = 0.0f + d[0] * (sr * orl + si * oi); g1 = 0.0f + d[0] * (sr * oi - si * orl);
+                for (int q = 0; q < ns; ++q) {
+                    const float *n = base + (3 + q) * L;
+                    const float nr = n[k], ni = n[D + k], dq = d[1 + q];
+                    g0 = g0 + dq * (nr * orl + ni * oi); g1 = g1 + dq * (nr * oi - ni * orl);
+                }
+                for (int q = 0; q < no; ++q) {
+                    const float *n = base + (3 + ns + q) * L;
+                    const float nr = n[k], ni = n[D + k], dq = d[1 + ns + q];
+                    g0 = g0 + dq * (sr * nr + si * ni); g1 = g1 + dq * (sr * ni - si * nr);
+                }
+            } else if (jj == 2) {
+                g0 = 0.0f + d[0] * (sr * rr - si * ri); g1 = 0.0f + d[0] * (si * rr + sr * ri);
+                for (int q = 0; q < ns; ++q) {
+                    const float *n = base + (3 + q) * L;
+                    const float nr = n[k], ni = n[D + k], dq = d[1 + q];
+                    g0 = g0 + dq * (nr * rr - ni * ri); g1 = g1 + dq * (ni * rr + nr * ri);
+                }
+            } else {
+                const float dq = d[jj - 2];
+                if (jj < 3 + ns) { g0 = 0.0f + dq * (rr * orl + ri * oi); g1 = 0.0f + dq * (rr * oi - ri * orl); }
+                else { g0 = 0.0f + dq * (sr * rr - si * ri); g1 = 0.0f + dq * (si * rr + sr * ri); }
+            }
+            const Upd u0 = adagrad<false>(g0, own[2 * D + k], lr, eps), u1 = adagrad<false>(g1, own[3 * D + k], lr, eps);
+            float *u = upd + j * L + k;
+            u[0] = u0.dt; u[D] = u1.dt; u[2 * D] = u0.dg; u[3 * D] = u1.dg;
+        }
+    }
+    __syncthreads();
+    // the push: the first slot that names a key adds the terms of all that do, in their order, onto the value
+    for (int j = wave; j < slots; j += waves) {
+        const int64_t kj = key[j];
+        const u64 same = __ballot(lane < slots && key[lane < slots ? lane : 0] == kj);
+        if ((same & ((1ull << j) - 1ull)) != 0) continue;
+        float *to = store + kj * L;
+        for (int k = lane; k < L; k += 64) {
+            float v = val[j * L + k];
+            for (u64 left = same; left != 0; left &= left - 1ull) v = v + upd[(__ffsll((long long)left) - 1) * L + k];
+            to[k] = v;
+        }
+    }
+    if (loss)
+        for (int b = wave; b < (int)t.batch; b += waves) {
+            const double sum = loss_of(lane < per ? score[b * per + lane] : 0.0f, per);
+            if (lane == 0) loss[b] = sum;
+        }
 }
 
 __global__ __launch_bounds__(256) void k_kge_loss_sum(const double *loss, int64_t n, double *out) {
@@ -365,11 +480,17 @@ extern "C" int kge_sgd_step(ps_handle ps, int32_t worker, int64_t num_entities, 
     double *loss = (double *)((char *)ps->kge_ws + off_loss);
     const KgeBatch t{subj, rel, obj, neg_subj, neg_obj, n_neg_subj, n_neg_obj, num_entities, batch};
     int rc;
-    if (rows <= dpaps_few_keys()) {
+    double *const wanted = loss_host_out ? loss : nullptr;            // the losses, if the caller asks for them
+    if (rows <= KGE_FEW_SLOTS && kge_few_lds(rows, ps->L) <= KGE_FEW_LDS && !ps->opt_kge_exact && !ps->opt_push_sequential && !ps->loc) {
+        static const hipError_t lds_set = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_kge_few), hipFuncAttributeMaxDynamicSharedMemorySize, KGE_FEW_LDS);
+        PS_HIP(ps, lds_set);
+        const RouteArgs a = dpaps_step_route(ps, worker, rows, st);
+        k_kge_few<<<1 + a.blocks, KGE_FEW_THREADS, kge_few_lds(rows, ps->L), st>>>(a, t, dim, lr, eps, ps->val, ps->K, wanted, ps->err);
+        PS_HIP(ps, hipGetLastError());
+    } else if (rows <= dpaps_few_keys()) {
         // Few slots: what costs is launches, and the two streams' waiting for each other.  The update rows' kernel checks
-        // and writes the keys, then the sort (none up to 64 slots) and the sums follow on the one stream: 2 to 4
-        // launches (one data point: 11 + 7 us of kernels, 23 us a step with its rows read back, 107 as below).
-        rc = launch_group(ps, t, dim, lr, eps, upd, ukeys, PushDone{}, loss, st);
+        // and writes the keys, then the sums follow on the one stream.
+        rc = launch_group(ps, t, dim, lr, eps, upd, ukeys, PushDone{}, wanted, st);
         if (rc) return rc;
         rc = dpaps_push_few_step(ps, worker, ukeys, rows, upd, st);
         if (rc) return rc;
@@ -390,7 +511,7 @@ extern "C" int kge_sgd_step(ps_handle ps, int32_t worker, int64_t num_entities, 
         rc = dpaps_push_sort(ps, ukeys, rows, bs);
         if (rc) return rc;
         PS_HIP(ps, hipEventRecord(ps->ev_sorted, bs));
-        rc = launch_group(ps, t, dim, lr, eps, upd, nullptr, done, loss, st);
+        rc = launch_group(ps, t, dim, lr, eps, upd, nullptr, done, wanted, st);
         if (rc) return rc;
         PS_HIP(ps, hipStreamWaitEvent(st, ps->ev_sorted, 0));
         rc = dpaps_push_add_step(ps, worker, ukeys, rows, upd, done, st);
@@ -552,7 +673,7 @@ extern "C" int kge_sgd_epoch(ps_handle ps, int64_t num_entities, int32_t dim, in
             PS_HIP(ps, hipEventRecord(ps->ev_sorted, bs));
             // first stream: the values
             if (in_place) PS_HIP(ps, hipStreamWaitEvent(vs, ps->ev_keys, 0));
-            rc = launch_group(ps, t, dim, lr, eps, upd, nullptr, done, loss, vs);
+            rc = launch_group(ps, t, dim, lr, eps, upd, nullptr, done, loss_host_out ? loss : nullptr, vs);
             if (rc) break;
             PS_HIP(ps, hipStreamWaitEvent(vs, ps->ev_sorted, 0));
             rc = dpaps_push_add(ps, nb * (3 + ns + no), upd, done, vs);
