@@ -143,7 +143,7 @@ struct dpaps_ps {
     void *handoff_ws = nullptr;       // column block states and the recorded order of mf_sgd_epoch_handoff (grows)
     size_t handoff_ws_bytes = 0;
     hipStream_t side_stream = nullptr;   // default priority: the localize calls and statistics of kge_sgd_epoch run here
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_sorted = nullptr, ev_added = nullptr, ev_keys = nullptr;
+    hipEvent_t ev_fork = nullptr, ev_join = nullptr, ev_sorted = nullptr, ev_added[2] = {nullptr, nullptr}, ev_keys = nullptr;
     std::string last_error;
 };
 
@@ -219,6 +219,8 @@ struct PushDone {
 int dpaps_route_pull_push(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, hipStream_t st);   // without the key check
 int dpaps_localize_checked(dpaps_ps *ps, const int64_t *keys, int64_t n, int32_t worker, hipStream_t st);
 int dpaps_push_sort(dpaps_ps *ps, const int64_t *keys, int64_t n, hipStream_t st);     // the two halves of a push of checked keys
+int dpaps_push_reserve_two(dpaps_ps *ps, int64_t most);
+int dpaps_push_sort_half(dpaps_ps *ps, int half, int64_t most, const int64_t *keys, int64_t n, hipStream_t st);
 int dpaps_push_add(dpaps_ps *ps, int64_t n, const float *deltas, const PushDone &done, hipStream_t st);
 int dpaps_push_add_step(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, const float *deltas, const PushDone &done, hipStream_t st);
 int64_t dpaps_few_keys();

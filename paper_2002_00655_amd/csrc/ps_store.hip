@@ -5,6 +5,7 @@
 #include "route.h"
 #include "together.h"
 
+#include <algorithm>
 #include <cstdio>
 #include <cstring>
 #include <mutex>
@@ -583,7 +584,8 @@ extern "C" int ps_destroy(ps_handle ps) {
     if (ps->ev_fork) (void)hipEventDestroy(ps->ev_fork);
     if (ps->ev_join) (void)hipEventDestroy(ps->ev_join);
     if (ps->ev_sorted) (void)hipEventDestroy(ps->ev_sorted);
-    if (ps->ev_added) (void)hipEventDestroy(ps->ev_added);
+    for (hipEvent_t e : ps->ev_added)
+        if (e) (void)hipEventDestroy(e);
     if (ps->ev_keys) (void)hipEventDestroy(ps->ev_keys);
     if (ps->d_tasks) (void)hipFree(ps->d_tasks);
     for (hipEvent_t e : ps->ev_pool) (void)hipEventDestroy(e);
@@ -606,7 +608,7 @@ int dpaps_side_stream(dpaps_ps *ps) {
         PS_HIP(ps, hipEventCreateWithFlags(&ps->ev_fork, hipEventDisableTiming));
         PS_HIP(ps, hipEventCreateWithFlags(&ps->ev_join, hipEventDisableTiming));
         PS_HIP(ps, hipEventCreateWithFlags(&ps->ev_sorted, hipEventDisableTiming));
-        PS_HIP(ps, hipEventCreateWithFlags(&ps->ev_added, hipEventDisableTiming));
+        for (hipEvent_t &e : ps->ev_added) PS_HIP(ps, hipEventCreateWithFlags(&e, hipEventDisableTiming));
         PS_HIP(ps, hipEventCreateWithFlags(&ps->ev_keys, hipEventDisableTiming));
     }
     return PS_OK;
@@ -721,6 +723,15 @@ static int push_sort_into(dpaps_ps *ps, void *base, const int64_t *keys, int64_t
 int dpaps_push_sort(dpaps_ps *ps, const int64_t *keys, int64_t n, hipStream_t st) {
     const int rc = dpaps_ws_reserve(ps, push_layout(ps, n).bytes);
     return rc ? rc : push_sort_into(ps, ps->ws, keys, n, false, st);
+}
+// The same for steps that sort ahead of the sums of the step before: scratch for two steps of up to n keys each, and the sort
+// into one of the two halves.  (Somewhat fewer keys can need more: the sort's tiles are smaller below 2^20.)
+static size_t push_half(const dpaps_ps *ps, int64_t most) {
+    return align_up(std::max(push_layout(ps, most).bytes, push_layout(ps, std::min<int64_t>(most, ((int64_t)1 << 20) - 1)).bytes));
+}
+int dpaps_push_reserve_two(dpaps_ps *ps, int64_t most) { return dpaps_ws_reserve(ps, 2 * push_half(ps, most)); }
+int dpaps_push_sort_half(dpaps_ps *ps, int half, int64_t most, const int64_t *keys, int64_t n, hipStream_t st) {
+    return push_sort_into(ps, (char *)ps->ws + (half ? push_half(ps, most) : 0), keys, n, false, st);
 }
 
 static int push_tiny(dpaps_ps *ps, const RouteArgs &stats, const int64_t *keys, int64_t n, const float *deltas, hipStream_t st) {
