@@ -24,6 +24,7 @@
 // A caller that has not checked its keys asks for it: the first kernel then sets the handle's error, which ends the rest.
 // Integer work only: the result is the same bit for bit whatever the scheduling.
 #include "common.h"
+#include "together.h"
 
 namespace {
 
@@ -38,20 +39,25 @@ __device__ __forceinline__ uint32_t digit_of(uint64_t key, int shift, uint32_t m
 template <int ITEMS, bool FIRST>
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_count(const int64_t *keys_in, const uint64_t *pk_in, int64_t n, int shift, int bits,
                                                              int64_t num_tiles, uint32_t *hist, int64_t check_below, int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
+    const int32_t stop = flag_ahead(err);
     __shared__ uint32_t cnt[1 << SORT_MAX_BITS];
     const int R = 1 << bits;
     const uint32_t mask = (uint32_t)R - 1u;
-    for (int i = threadIdx.x; i < R; i += SORT_THREADS) cnt[i] = 0;
-    __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * (SORT_THREADS * ITEMS);
+    uint64_t key[ITEMS];
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
         const int64_t q = base + (int64_t)r * SORT_THREADS + threadIdx.x;
-        if (q < n) {
-            const uint64_t k = FIRST ? (uint64_t)keys_in[q] : pk_in[q];
-            if (FIRST && check_below > 0 && k >= (uint64_t)check_below) atomicExch(err, PS_EKEY);
-            atomicAdd(&cnt[digit_of(k, shift, mask)], 1u);
+        key[r] = q < n ? (FIRST ? (uint64_t)keys_in[q] : pk_in[q]) : 0;
+    }
+    if (stop) return;
+    for (int i = threadIdx.x; i < R; i += SORT_THREADS) cnt[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        if (base + (int64_t)r * SORT_THREADS + threadIdx.x < n) {
+            if (FIRST && check_below > 0 && key[r] >= (uint64_t)check_below) atomicExch(err, PS_EKEY);
+            atomicAdd(&cnt[digit_of(key[r], shift, mask)], 1u);
         }
     }
     __syncthreads();
@@ -59,11 +65,12 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_count(const int64_t *keys
 }
 
 __global__ __launch_bounds__(256) void k_sort_rowsum(const uint32_t *hist, int64_t num_tiles, uint32_t *row_total, const int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
+    const int32_t stop = flag_ahead(err);
     __shared__ uint32_t s[256];
     const uint32_t *row = hist + (int64_t)blockIdx.x * num_tiles;
     uint32_t acc = 0;
     for (int64_t t = threadIdx.x; t < num_tiles; t += 256) acc += row[t];
+    if (stop) return;
     s[threadIdx.x] = acc;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
@@ -75,12 +82,13 @@ __global__ __launch_bounds__(256) void k_sort_rowsum(const uint32_t *hist, int64
 
 // hist[b][t] <- pairs in buckets below b + pairs of bucket b in tiles before t
 __global__ __launch_bounds__(256) void k_sort_scan(uint32_t *hist, int64_t num_tiles, const uint32_t *row_total, const int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
+    const int32_t stop = flag_ahead(err);
     __shared__ uint32_t s[256];
     __shared__ uint32_t carry;
     const int b = blockIdx.x;
     uint32_t acc = 0;
     for (int i = threadIdx.x; i < b; i += 256) acc += row_total[i];
+    if (stop) return;
     s[threadIdx.x] = acc;
     __syncthreads();
     for (int w = 128; w > 0; w >>= 1) {
@@ -114,13 +122,11 @@ template <int ITEMS, bool FIRST>
 __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(const int64_t *keys_in, const uint64_t *pk_in, const uint32_t *pp_in, int64_t n,
                                                                int shift, int bits, int64_t num_tiles, const uint32_t *hist, uint64_t *pk_out,
                                                                uint32_t *pp_out, const int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
+    const int32_t stop = flag_ahead(err);
     __shared__ uint32_t wh[SORT_WAVES][1 << SORT_MAX_BITS];
     const int R = 1 << bits;
     const uint32_t mask = (uint32_t)R - 1u;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    for (int i = threadIdx.x; i < SORT_WAVES * (1 << SORT_MAX_BITS); i += SORT_THREADS) (&wh[0][0])[i] = 0;
-    __syncthreads();
     // wavefront w takes the pairs [base + w * 64 * ITEMS, + 64 * ITEMS), 64 consecutive ones per round
     const int64_t base = (int64_t)blockIdx.x * (SORT_THREADS * ITEMS) + (int64_t)wave * 64 * ITEMS;
     uint64_t key[ITEMS];
@@ -129,12 +135,26 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(const int64_t *ke
 #pragma unroll
     for (int r = 0; r < ITEMS; ++r) {
         const int64_t q = base + r * 64 + lane;
-        const bool valid = q < n;
         key[r] = 0; pos[r] = 0;
-        if (valid) {
+        if (q < n) {
             key[r] = FIRST ? (uint64_t)keys_in[q] : pk_in[q];
             pos[r] = FIRST ? (uint32_t)q : pp_in[q];
         }
+    }
+    // where the tile's pairs of this thread's buckets go
+    constexpr int OWN = (1 << SORT_MAX_BITS) / SORT_THREADS;
+    uint32_t starts[OWN];
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+        const int b = threadIdx.x + i * SORT_THREADS;
+        starts[i] = b < R ? hist[(int64_t)b * num_tiles + blockIdx.x] : 0u;
+    }
+    if (stop) return;
+    for (int i = threadIdx.x; i < SORT_WAVES * (1 << SORT_MAX_BITS); i += SORT_THREADS) (&wh[0][0])[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ITEMS; ++r) {
+        const bool valid = base + r * 64 + lane < n;
         const uint32_t d = digit_of(key[r], shift, mask);
         uint64_t same = __ballot(valid);
         for (int b = 0; b < bits; ++b) {
@@ -154,8 +174,11 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(const int64_t *ke
     }
     __syncthreads();
     // a wavefront's counters become the offsets of its first pair of each bucket
-    for (int b = threadIdx.x; b < R; b += SORT_THREADS) {
-        uint32_t run = hist[(int64_t)b * num_tiles + blockIdx.x];
+#pragma unroll
+    for (int i = 0; i < OWN; ++i) {
+        const int b = threadIdx.x + i * SORT_THREADS;
+        if (b >= R) break;
+        uint32_t run = starts[i];
 #pragma unroll
         for (int w = 0; w < SORT_WAVES; ++w) {
             const uint32_t c = wh[w][b];
@@ -183,20 +206,25 @@ static_assert(2 * MID_THREADS >= 1 << SORT_MAX_BITS, "two buckets per thread");
 template <bool FIRST>
 __global__ __launch_bounds__(MID_THREADS) void k_sort_mid_count(const int64_t *keys_in, const uint64_t *pk_in, int64_t n, int shift, int bits,
                                                                 uint32_t *hist, int64_t check_below, int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
+    const int32_t stop = flag_ahead(err);
     __shared__ uint32_t cnt[1 << SORT_MAX_BITS];
     const int R = 1 << bits, tid = threadIdx.x;
     const uint32_t mask = (uint32_t)R - 1u;
-    for (int i = tid; i < R; i += MID_THREADS) cnt[i] = 0;
-    __syncthreads();
     const int64_t base = (int64_t)blockIdx.x * MID_TILE;
+    uint64_t key[MID_ITEMS];
 #pragma unroll
     for (int r = 0; r < MID_ITEMS; ++r) {
         const int64_t q = base + r * MID_THREADS + tid;
-        if (q < n) {
-            const uint64_t k = FIRST ? (uint64_t)keys_in[q] : pk_in[q];
-            if (FIRST && check_below > 0 && k >= (uint64_t)check_below) atomicExch(err, PS_EKEY);
-            atomicAdd(&cnt[digit_of(k, shift, mask)], 1u);
+        key[r] = q < n ? (FIRST ? (uint64_t)keys_in[q] : pk_in[q]) : 0;
+    }
+    if (stop) return;
+    for (int i = tid; i < R; i += MID_THREADS) cnt[i] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < MID_ITEMS; ++r) {
+        if (base + r * MID_THREADS + tid < n) {
+            if (FIRST && check_below > 0 && key[r] >= (uint64_t)check_below) atomicExch(err, PS_EKEY);
+            atomicAdd(&cnt[digit_of(key[r], shift, mask)], 1u);
         }
     }
     __syncthreads();
@@ -207,23 +235,11 @@ template <bool FIRST>
 __global__ __launch_bounds__(MID_THREADS) void k_sort_mid_scatter(const int64_t *keys_in, const uint64_t *pk_in, const uint32_t *pp_in, int64_t n,
                                                                   int shift, int bits, const uint32_t *hist, uint64_t *pk_out, uint32_t *pp_out,
                                                                   const int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
+    const int32_t stop = flag_ahead(err);
     __shared__ __attribute__((aligned(8))) uint32_t wh[MID_WAVES][1 << SORT_MAX_BITS];
     __shared__ uint32_t wave_sum[MID_WAVES];
     const int R = 1 << bits, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tile = blockIdx.x, tiles = gridDim.x;
     const uint32_t mask = (uint32_t)R - 1u;
-    // this thread's two buckets: pairs in all tiles, and in the tiles before this one
-    uint2 total = make_uint2(0u, 0u), before_tile = total;
-    if (2 * tid < R) {
-#pragma unroll 16
-        for (int t = 0; t < tiles; ++t) {
-            const uint2 v = *reinterpret_cast<const uint2 *>(&hist[(int64_t)t * R + 2 * tid]);
-            total.x += v.x; total.y += v.y;
-            if (t < tile) { before_tile.x += v.x; before_tile.y += v.y; }
-        }
-    }
-    for (int i = tid; i < MID_WAVES * (1 << SORT_MAX_BITS); i += MID_THREADS) (&wh[0][0])[i] = 0;
-    __syncthreads();
     const int64_t base = (int64_t)tile * MID_TILE + (int64_t)wave * 64 * MID_ITEMS;
     uint64_t key[MID_ITEMS];
     uint32_t pos[MID_ITEMS], rank[MID_ITEMS];
@@ -235,6 +251,21 @@ __global__ __launch_bounds__(MID_THREADS) void k_sort_mid_scatter(const int64_t 
         key[r] = valid ? (FIRST ? (uint64_t)keys_in[q] : pk_in[q]) : 0;
         pos[r] = valid ? (FIRST ? (uint32_t)q : pp_in[q]) : 0u;
     }
+    // this thread's two buckets: pairs in all tiles, and in the tiles before this one
+    uint2 total = make_uint2(0u, 0u), before_tile = total;
+    if (2 * tid < R) {
+#pragma unroll 16
+        for (int t = 0; t < tiles; ++t) {
+            const uint2 v = *reinterpret_cast<const uint2 *>(&hist[(int64_t)t * R + 2 * tid]);
+            total.x += v.x; total.y += v.y;
+            if (t < tile) { before_tile.x += v.x; before_tile.y += v.y; }
+        }
+    }
+    if (stop) return;
+    // (of the buckets only what the digit has)
+    for (int w = 0; w < MID_WAVES; ++w)
+        if (2 * tid < R) *reinterpret_cast<uint2 *>(&wh[w][2 * tid]) = make_uint2(0u, 0u);
+    __syncthreads();
 #pragma unroll
     for (int r = 0; r < MID_ITEMS; ++r) {
         const bool valid = base + r * 64 + lane < n;

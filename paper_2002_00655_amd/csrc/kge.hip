@@ -32,18 +32,19 @@ static inline unsigned grid_for(int64_t n, int block) { return (unsigned)((n + b
 __device__ __forceinline__ int64_t entity_key(const KgeBatch &t, int64_t b, int32_t j) { return slot_key(t, b, j == 0 ? 0 : j + 1); }
 __global__ void k_kge_keys(KgeBatch t, int64_t *keys, int64_t check_below, u64 *seen, uint32_t *shared, uint32_t id, KgeBatch ent, int64_t *ent_keys,
                            int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
+    const int32_t stop = flag_ahead(err);
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     const int32_t rows = 3 + t.ns + t.no;
     if (i < t.batch * rows) {
         const int64_t b = i / rows, k = slot_key(t, b, (int32_t)(i - b * rows));
+        if (stop) return;
         const bool bad = check_below > 0 && (k < 0 || k >= check_below);
         if (bad) atomicExch(err, PS_EKEY);
         keys[i] = k;
         if (seen && !bad) kge_mark_slot(t.num_entities, (uint32_t)i, (int32_t)(i - b * rows), k, seen, shared, id);
     }
     const int32_t ents = 2 + ent.ns + ent.no;
-    if (i < ent.batch * ents) {
+    if (stop == 0 && i < ent.batch * ents) {
         const int64_t b = i / ents;
         ent_keys[i] = entity_key(ent, b, (int32_t)(i - b * ents));
     }
@@ -110,12 +111,14 @@ __device__ __forceinline__ double loss_of(float score, int per) {
 template <int NC, bool EXACT>
 __global__ __launch_bounds__(256) void k_kge_group(KgeBatch t, int32_t D, float lr, float eps, float *store, float *__restrict__ upd,
                                                     int64_t *keys_out, int64_t num_keys, PushDone done, double *loss, int32_t *err) {
-    if (__hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) return;
+    const int32_t stop = __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int lane = threadIdx.x & 63;
     // the data point is the same for all lanes of a wavefront: said so, its keys and row addresses stay in scalar registers
     const int64_t b = (int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (b >= t.batch) return;
     const int32_t ns = t.ns, no = t.no;
+    const int64_t ks = t.subj[b], kr = t.num_entities + t.rel[b], ko = t.obj[b];
+    if (stop != 0) return;                                           // (looked at when the first keys have been asked for)
     constexpr int CH = NC <= 2 ? 5 : 1;                              // negatives whose rows are in flight together
     const int L = 4 * D, rows = 3 + ns + no;
     if (keys_out) {
@@ -131,7 +134,6 @@ __global__ __launch_bounds__(256) void k_kge_group(KgeBatch t, int32_t D, float 
         }
     }
     const uint32_t Du = (uint32_t)D;                                 // row addresses and field offsets are scalars, k the only lane offset
-    const int64_t ks = t.subj[b], kr = t.num_entities + t.rel[b], ko = t.obj[b];
     const float *vs = store + ks * L, *vr = store + kr * L, *vo = store + ko * L;
     float *u0 = upd + b * rows * L;
     // the sum of the lanes' terms: term[c] belongs to component lane + 64 c

@@ -56,9 +56,8 @@ __global__ void k_check_keys(const int64_t *keys, int64_t n, int64_t K, int32_t 
 }
 
 __global__ __launch_bounds__(256) void k_route_access(RouteArgs a, const int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
     __shared__ RouteLds l;
-    route_access_block(a, l, blockIdx.x);
+    route_access_block(a, l, blockIdx.x, flag_ahead(err));
 }
 
 // The replies of a pull or push have arrived: the requester's node knows the owner of every remote key it asked
@@ -78,7 +77,8 @@ __global__ void k_cache_replies(const int64_t *keys, int64_t n, int32_t worker, 
 __global__ __launch_bounds__(256) void k_localize(const int64_t *keys, int64_t n, int32_t worker, int32_t *owner, int64_t per_home, int32_t W,
                                                    uint32_t *named, uint32_t *stamp_pair, uint32_t call_id, u64 *stats,
                                                    int16_t *loc, int64_t K, bool few, int32_t *err) {
-    if (few ? few_keys_off<8>(keys, n, K, err) : *(volatile const int32_t *)err != 0) return;
+    const int32_t stop = few ? 0 : flag_ahead(err);
+    if (few && few_keys_off<8>(keys, n, K, err)) return;
     __shared__ RouteLds l;
     route_lds_init(l, W);
     const double inv_per_home = 1.0 / (double)per_home;
@@ -94,6 +94,7 @@ __global__ __launch_bounds__(256) void k_localize(const int64_t *keys, int64_t n
             active[u] = p < n;
             k[u] = active[u] ? keys[p] : 0;
         }
+        if (stop) return;
         // (a key that is seen to be the worker's already is left alone: a stale read only costs an exchange, and
         // a key mentioned a million times in one call does not turn into a million exchanges on one word)
 #pragma unroll
@@ -117,9 +118,11 @@ __global__ __launch_bounds__(256) void k_localize(const int64_t *keys, int64_t n
 }
 
 __global__ __launch_bounds__(256) void k_owner(const int64_t *keys, int64_t n, const int32_t *owner, int32_t *out, int64_t K, bool few, int32_t *err) {
-    if (few ? few_keys_off<8>(keys, n, K, err) : *(volatile const int32_t *)err != 0) return;
-    int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (p < n) out[p] = owner[keys[p]];
+    const int32_t stop = few ? 0 : flag_ahead(err);
+    const int64_t p = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t k = p < n ? keys[p] : 0;
+    if (few ? few_keys_off<8>(keys, n, K, err) : stop != 0) return;
+    if (p < n) out[p] = owner[k];
 }
 
 // Pieces of a row: built-in vectors (arrays of float4 structures end up in LDS and scratch memory).
@@ -142,9 +145,14 @@ template <class Piece, int AHEAD, bool STREAM>
 __global__ __launch_bounds__(256) void k_pull(RouteArgs route, const int64_t *keys, int64_t n, uint32_t P, double inv_P, const Piece *val, Piece *out,
                                               int64_t K, int32_t *err) {
     // (of a larger call the flag was set, or not, by the launch before)
-    if (n <= FEW_KEYS ? few_keys_off(keys, n, K, err) : *(volatile const int32_t *)err != 0) return;
+    const bool few = n <= FEW_KEYS;
+    const int32_t stop = few ? 0 : flag_ahead(err);
     __shared__ RouteLds l;
-    if ((int)blockIdx.x < route.blocks) { route_access_block(route, l, blockIdx.x); return; }
+    if ((int)blockIdx.x < route.blocks) {
+        if (few && few_keys_off(keys, n, K, err)) return;
+        route_access_block(route, l, blockIdx.x, stop);
+        return;
+    }
     const int64_t block = blockIdx.x - route.blocks;
     // the workgroup's first piece: row p0, piece c0 of it (quotients by way of 1 / P, rounded: the first in double and
     // put right, the others, of numbers up to P - 1 + 256 AHEAD - 1 - 3069 at most, with 8 pieces of 4 bytes ahead and rows of
@@ -161,6 +169,7 @@ __global__ __launch_bounds__(256) void k_pull(RouteArgs route, const int64_t *ke
         c[u] = t - row * P;
         key[u] = first + u * 256 + threadIdx.x < total ? keys[p0 + row] : 0;
     }
+    if (few ? few_keys_off(keys, n, K, err) : stop != 0) return;
     Piece x[AHEAD];
 #pragma unroll
     for (int u = 0; u < AHEAD; ++u) x[u] = val[key[u] * P + c[u]];
@@ -286,10 +295,10 @@ __device__ __forceinline__ void push_range(int cnt, int p0, int p1, u64 skips, u
 template <class Piece, int SPLIT>
 __global__ __launch_bounds__(256) void k_push_ranges(RouteArgs route, PushDone done, const uint64_t *skeys, const uint32_t *spos, int64_t n, int32_t P,
                                                       const Piece *deltas, Piece *val, Piece *part, const int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
+    const int32_t stop = flag_ahead(err);
     __shared__ RouteLds l;
     if ((int)blockIdx.x < route.blocks) {
-        if (blockIdx.y == 0) route_access_block(route, l, blockIdx.x);
+        if (blockIdx.y == 0) route_access_block(route, l, blockIdx.x, stop);
         return;
     }
     const int lane = threadIdx.x & 63;
@@ -303,6 +312,7 @@ __global__ __launch_bounds__(256) void k_push_ranges(RouteArgs route, PushDone d
     const uint64_t prevk = q0 > 0 ? skeys[q0 - 1] : NOKEY;
     const uint64_t nextk = q0 + cnt < n ? skeys[q0 + cnt] : NOKEY;
     const uint64_t before = lane > 0 && lane < cnt ? skeys[q0 + lane - 1] : NOKEY;
+    if (stop) return;
     u64 skips = 0;
     if (done.shared) skips = __ballot(lane < cnt && done.in_place((uint32_t)mp));
     push_range(cnt, p0, p0 + PUSH_RANGE / SPLIT, skips, mk, before, mp, prevk, nextk, r, blockIdx.y * 64 + lane, P, deltas, val, part);
@@ -313,11 +323,11 @@ __global__ __launch_bounds__(256) void k_push_ranges(RouteArgs route, PushDone d
 // last workgroup counts the statistics.
 __global__ __launch_bounds__(64) void k_push_tiny(RouteArgs route, const int64_t *keys, int n, int32_t L, const float *deltas, float *val, int64_t K,
                                                   int32_t *err) {
+    const int lane = threadIdx.x;
+    const uint64_t k = lane < n ? (uint64_t)keys[lane] : NOKEY;
     if (few_keys_off(keys, n, K, err)) return;
     __shared__ RouteLds l;
     if (route.blocks && blockIdx.x == gridDim.x - 1) { route_access_block(route, l, 0); return; }
-    const int lane = threadIdx.x;
-    const uint64_t k = lane < n ? (uint64_t)keys[lane] : NOKEY;
     int place = 0;
     for (int i = 0; i < n; ++i) {
         const uint64_t ki = readlane_u64(k, i);
@@ -460,13 +470,13 @@ __global__ __launch_bounds__(FEW_THREADS) void k_push_few(RouteArgs route, const
 constexpr int JOIN_AHEAD = 64;
 __global__ __launch_bounds__(256) void k_push_join(const uint64_t *skeys, int64_t n, int32_t L, const float *part, float *val,
                                                     const int32_t *err) {
-    if (*(volatile const int32_t *)err) return;
+    const int32_t stop = flag_ahead(err);
     const int lane = threadIdx.x & 63;
     const int64_t r = (int64_t)blockIdx.x * (blockDim.x >> 6) + __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);   // the same in all lanes: addresses in scalars
     const int64_t q1 = (r + 1) * PUSH_RANGE;
     if (q1 >= n) return;                                               // nothing follows this range
-    const uint64_t key = skeys[q1 - 1];
-    if (skeys[q1] != key) return;                                      // its last key ends here
+    const uint64_t key = skeys[q1 - 1], next = skeys[q1];
+    if (stop != 0 || next != key) return;                              // its last key ends here
     if (r > 0 && skeys[q1 - PUSH_RANGE] == key && skeys[q1 - PUSH_RANGE - 1] == key) return;   // it started earlier
     // m: how many of the following ranges begin with this key.  The keys are sorted, so those ranges follow one another:
     // 64 at a time are looked at, and where all of them do, 64 spread over what is left, until the first that does not.

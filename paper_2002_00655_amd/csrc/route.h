@@ -178,7 +178,8 @@ struct RouteArgs {
 };
 constexpr int ROUTE_AHEAD = 4;
 
-__device__ __forceinline__ void route_access_block(const RouteArgs &a, RouteLds &l, int block) {
+// stop: the handle's error flag, the same in all threads; looked at when the first keys are on their way.
+__device__ __forceinline__ void route_access_block(const RouteArgs &a, RouteLds &l, int block, int32_t stop = 0) {
     route_lds_init(l, a.W);
     const double inv_per_home = 1.0 / (double)a.per_home;
     const int64_t step = (int64_t)a.blocks * blockDim.x;
@@ -193,6 +194,7 @@ __device__ __forceinline__ void route_access_block(const RouteArgs &a, RouteLds 
             active[u] = p < a.n;
             k[u] = active[u] ? a.keys[p] : 0;
         }
+        if (stop) return;
 #pragma unroll
         for (int u = 0; u < ROUTE_AHEAD; ++u) o[u] = active[u] ? a.owner[k[u]] : 0;
 #pragma unroll
