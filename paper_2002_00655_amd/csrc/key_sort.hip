@@ -199,18 +199,19 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(const int64_t *ke
 }
 
 // ---- up to MID_MAX pairs: counters tile by tile, every workgroup of the scatter sums them itself -------------------
-constexpr int MID_THREADS = 512, MID_WAVES = MID_THREADS / 64, MID_ITEMS = 4, MID_TILE = MID_THREADS * MID_ITEMS, MID_MAX_TILES = 64;
-constexpr int64_t MID_MAX = (int64_t)MID_TILE * MID_MAX_TILES;
+// MID_ITEMS pairs per thread: 4, or 2 up to MID_SHORT pairs, where tiles are what there are too few of.
+constexpr int MID_THREADS = 512, MID_WAVES = MID_THREADS / 64, MID_MAX_TILES = 64;
+constexpr int64_t MID_MAX = (int64_t)MID_THREADS * 4 * MID_MAX_TILES, MID_SHORT = MID_MAX / 4;
 static_assert(2 * MID_THREADS >= 1 << SORT_MAX_BITS, "two buckets per thread");
 
-template <bool FIRST>
+template <int MID_ITEMS, bool FIRST>
 __global__ __launch_bounds__(MID_THREADS) void k_sort_mid_count(const int64_t *keys_in, const uint64_t *pk_in, int64_t n, int shift, int bits,
                                                                 uint32_t *hist, int64_t check_below, int32_t *err) {
     const int32_t stop = flag_ahead(err);
     __shared__ uint32_t cnt[1 << SORT_MAX_BITS];
     const int R = 1 << bits, tid = threadIdx.x;
     const uint32_t mask = (uint32_t)R - 1u;
-    const int64_t base = (int64_t)blockIdx.x * MID_TILE;
+    const int64_t base = (int64_t)blockIdx.x * (MID_THREADS * MID_ITEMS);
     uint64_t key[MID_ITEMS];
 #pragma unroll
     for (int r = 0; r < MID_ITEMS; ++r) {
@@ -231,7 +232,7 @@ __global__ __launch_bounds__(MID_THREADS) void k_sort_mid_count(const int64_t *k
     for (int i = tid; i < R; i += MID_THREADS) hist[(int64_t)blockIdx.x * R + i] = cnt[i];
 }
 
-template <bool FIRST>
+template <int MID_ITEMS, bool FIRST>
 __global__ __launch_bounds__(MID_THREADS) void k_sort_mid_scatter(const int64_t *keys_in, const uint64_t *pk_in, const uint32_t *pp_in, int64_t n,
                                                                   int shift, int bits, const uint32_t *hist, uint64_t *pk_out, uint32_t *pp_out,
                                                                   const int32_t *err) {
@@ -240,7 +241,7 @@ __global__ __launch_bounds__(MID_THREADS) void k_sort_mid_scatter(const int64_t 
     __shared__ uint32_t wave_sum[MID_WAVES];
     const int R = 1 << bits, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tile = blockIdx.x, tiles = gridDim.x;
     const uint32_t mask = (uint32_t)R - 1u;
-    const int64_t base = (int64_t)tile * MID_TILE + (int64_t)wave * 64 * MID_ITEMS;
+    const int64_t base = (int64_t)tile * (MID_THREADS * MID_ITEMS) + (int64_t)wave * 64 * MID_ITEMS;
     uint64_t key[MID_ITEMS];
     uint32_t pos[MID_ITEMS], rank[MID_ITEMS];
     const uint64_t below = (1ull << lane) - 1ull;
@@ -391,8 +392,8 @@ SortPlan sort_plan(int64_t n, int key_bits) {
     return p;
 }
 
-// ITEMS 0: up to MID_MAX pairs
-template <int ITEMS>
+// MID: up to MID_MAX pairs
+template <int ITEMS, bool MID>
 int sort_run(dpaps_ps *ps, const SortPlan &p, const int64_t *keys, int64_t n, int64_t check_below, uint64_t *skeys, uint32_t *spos, void *scratch,
              hipStream_t st) {
     uint64_t *alt_k = (uint64_t *)((char *)scratch + p.off_pk);
@@ -406,13 +407,14 @@ int sort_run(dpaps_ps *ps, const SortPlan &p, const int64_t *keys, int64_t n, in
     int shift = 0;
     for (int i = 0; i < p.passes; ++i) {
         const int bits = p.bits[i], R = 1 << bits;
-        if constexpr (ITEMS == 0) {
-            const unsigned mid = (unsigned)((n + MID_TILE - 1) / MID_TILE);
-            if (i == 0) k_sort_mid_count<true><<<mid, MID_THREADS, 0, st>>>(keys, nullptr, n, shift, bits, hist, check_below, ps->err);
-            else k_sort_mid_count<false><<<mid, MID_THREADS, 0, st>>>(nullptr, in_k, n, shift, bits, hist, 0, ps->err);
+        if constexpr (MID) {
+            constexpr int TILE = MID_THREADS * ITEMS;
+            const unsigned mid = (unsigned)((n + TILE - 1) / TILE);
+            if (i == 0) k_sort_mid_count<ITEMS, true><<<mid, MID_THREADS, 0, st>>>(keys, nullptr, n, shift, bits, hist, check_below, ps->err);
+            else k_sort_mid_count<ITEMS, false><<<mid, MID_THREADS, 0, st>>>(nullptr, in_k, n, shift, bits, hist, 0, ps->err);
             PS_HIP(ps, hipGetLastError());
-            if (i == 0) k_sort_mid_scatter<true><<<mid, MID_THREADS, 0, st>>>(keys, nullptr, nullptr, n, shift, bits, hist, out_k, out_p, ps->err);
-            else k_sort_mid_scatter<false><<<mid, MID_THREADS, 0, st>>>(nullptr, in_k, in_p, n, shift, bits, hist, out_k, out_p, ps->err);
+            if (i == 0) k_sort_mid_scatter<ITEMS, true><<<mid, MID_THREADS, 0, st>>>(keys, nullptr, nullptr, n, shift, bits, hist, out_k, out_p, ps->err);
+            else k_sort_mid_scatter<ITEMS, false><<<mid, MID_THREADS, 0, st>>>(nullptr, in_k, in_p, n, shift, bits, hist, out_k, out_p, ps->err);
             PS_HIP(ps, hipGetLastError());
         } else {
             if (i == 0) k_sort_count<ITEMS, true><<<tiles, SORT_THREADS, 0, st>>>(keys, nullptr, n, shift, bits, p.num_tiles, hist, check_below, ps->err);
@@ -458,6 +460,7 @@ int dpaps_sort_pairs(dpaps_ps *ps, const int64_t *keys, int64_t n, int key_bits,
         return PS_OK;
     }
     const SortPlan p = sort_plan(n, key_bits);
-    if (n <= MID_MAX) return sort_run<0>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
-    return p.items == 4 ? sort_run<4>(ps, p, keys, n, check_below, skeys, spos, scratch, st) : sort_run<16>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
+    if (n <= MID_SHORT) return sort_run<2, true>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
+    if (n <= MID_MAX) return sort_run<4, true>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
+    return p.items == 4 ? sort_run<4, false>(ps, p, keys, n, check_below, skeys, spos, scratch, st) : sort_run<16, false>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
 }
