@@ -26,6 +26,8 @@
 #include "common.h"
 #include "together.h"
 
+#include <algorithm>
+
 namespace {
 
 constexpr int SORT_THREADS = 256;          // 4 wavefronts per tile
@@ -200,6 +202,9 @@ __global__ __launch_bounds__(SORT_THREADS) void k_sort_scatter(const int64_t *ke
 
 // ---- up to MID_MAX pairs: counters tile by tile, every workgroup of the scatter sums them itself -------------------
 // MID_ITEMS pairs per thread: 4, or 2 up to MID_SHORT pairs, where tiles are what there are too few of.
+// TILES_AHEAD: tiles whose counters a thread asks for together - always so many (an unrolled loop's remainder goes one trip to memory
+// after the other: a scatter of 20,001 pairs 7.3 us, this way 6.7).
+constexpr int TILES_AHEAD = 16;
 constexpr int MID_THREADS = 512, MID_WAVES = MID_THREADS / 64, MID_MAX_TILES = 64;
 constexpr int64_t MID_MAX = (int64_t)MID_THREADS * 4 * MID_MAX_TILES, MID_SHORT = MID_MAX / 4;
 static_assert(2 * MID_THREADS >= 1 << SORT_MAX_BITS, "two buckets per thread");
@@ -255,11 +260,15 @@ __global__ __launch_bounds__(MID_THREADS) void k_sort_mid_scatter(const int64_t 
     // this thread's two buckets: pairs in all tiles, and in the tiles before this one
     uint2 total = make_uint2(0u, 0u), before_tile = total;
     if (2 * tid < R) {
-#pragma unroll 16
-        for (int t = 0; t < tiles; ++t) {
-            const uint2 v = *reinterpret_cast<const uint2 *>(&hist[(int64_t)t * R + 2 * tid]);
-            total.x += v.x; total.y += v.y;
-            if (t < tile) { before_tile.x += v.x; before_tile.y += v.y; }
+        for (int t0 = 0; t0 < tiles; t0 += TILES_AHEAD) {
+            uint2 v[TILES_AHEAD];
+#pragma unroll
+            for (int i = 0; i < TILES_AHEAD; ++i) v[i] = *reinterpret_cast<const uint2 *>(&hist[(int64_t)(t0 + i < tiles ? t0 + i : t0) * R + 2 * tid]);
+#pragma unroll
+            for (int i = 0; i < TILES_AHEAD; ++i) {
+                total.x += t0 + i < tiles ? v[i].x : 0u; total.y += t0 + i < tiles ? v[i].y : 0u;
+                before_tile.x += t0 + i < tile ? v[i].x : 0u; before_tile.y += t0 + i < tile ? v[i].y : 0u;
+            }
         }
     }
     if (stop) return;
@@ -319,6 +328,156 @@ __global__ __launch_bounds__(MID_THREADS) void k_sort_mid_scatter(const int64_t 
     }
 }
 
+// ---- from BIG_MIN up to BIG_MAX pairs: the same two launches per digit with tiles of 8,192 pairs, which a workgroup brings into the order of
+// their buckets in LDS first, so that the stores of a bucket's pairs (8 of a tile at 1,024 buckets) leave side by side.
+// Every workgroup sums all tiles' counters itself: 0.5 MB of them at a million pairs.  1,000,003 pairs of 19 bits: 63 us
+// in four launches; 78 in eight, as below BIG_MIN, where small tiles give more workgroups (200,000 pairs: as fast).
+constexpr int BIG_THREADS = 1024, BIG_WAVES = BIG_THREADS / 64, BIG_ITEMS = 8, BIG_TILE = BIG_THREADS * BIG_ITEMS;
+constexpr int64_t BIG_MIN = (int64_t)1 << 18, BIG_MAX = (int64_t)1 << 21;
+static_assert(BIG_THREADS >= 1 << SORT_MAX_BITS && BIG_TILE < 1 << 16, "a bucket per thread, places in a tile of 16 bits");
+struct BigLds {
+    uint64_t key[BIG_TILE];
+    uint32_t pos[BIG_TILE];
+    uint16_t place[BIG_WAVES][1 << SORT_MAX_BITS];     // a wavefront's pairs of a bucket, then where the first of them lies in the tile
+    int32_t out[1 << SORT_MAX_BITS];                   // from a pair's place in the tile to its place in the output
+    uint32_t sums[2][BIG_WAVES];
+};
+
+template <bool FIRST>
+__global__ __launch_bounds__(BIG_THREADS) void k_sort_big_count(const int64_t *keys_in, const uint64_t *pk_in, int64_t n, int shift, int bits, uint32_t *hist,
+                                                                int64_t check_below, int32_t *err) {
+    const int32_t stop = flag_ahead(err);
+    __shared__ uint32_t cnt[1 << SORT_MAX_BITS];
+    const int R = 1 << bits, tid = threadIdx.x;
+    const uint32_t mask = (uint32_t)R - 1u;
+    const int64_t base = (int64_t)blockIdx.x * BIG_TILE;
+    uint64_t key[BIG_ITEMS];
+#pragma unroll
+    for (int r = 0; r < BIG_ITEMS; ++r) {
+        const int64_t q = base + r * BIG_THREADS + tid;
+        key[r] = q < n ? (FIRST ? (uint64_t)keys_in[q] : pk_in[q]) : 0;
+    }
+    if (stop) return;
+    if (tid < R) cnt[tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < BIG_ITEMS; ++r) {
+        const bool valid = base + r * BIG_THREADS + tid < n;
+        if (FIRST && check_below > 0 && valid && key[r] >= (uint64_t)check_below) atomicExch(err, PS_EKEY);
+        // (a wavefront whose pairs are all of one bucket - few keys, keys in order - counts them at once: additions to one word
+        // come one by one)
+        const uint32_t d = digit_of(key[r], shift, mask), d0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)d);
+        const uint64_t there = __ballot(valid);
+        if (__ballot(valid && d != d0) == 0) {
+            if ((tid & 63) == 0 && there != 0) atomicAdd(&cnt[d0], (uint32_t)__popcll(there));
+        } else if (valid) atomicAdd(&cnt[d], 1u);
+    }
+    __syncthreads();
+    if (tid < R) hist[(int64_t)blockIdx.x * R + tid] = cnt[tid];
+}
+
+template <bool FIRST>
+__global__ __launch_bounds__(BIG_THREADS) void k_sort_big_scatter(const int64_t *keys_in, const uint64_t *pk_in, const uint32_t *pp_in, int64_t n, int shift,
+                                                                  int bits, const uint32_t *hist, uint64_t *pk_out, uint32_t *pp_out, const int32_t *err) {
+    const int32_t stop = flag_ahead(err);
+    extern __shared__ __attribute__((aligned(16))) unsigned char big_mem[];
+    BigLds &l = *reinterpret_cast<BigLds *>(big_mem);
+    const int R = 1 << bits, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, tile = blockIdx.x, tiles = gridDim.x;
+    const uint32_t mask = (uint32_t)R - 1u;
+    // wavefront w takes the tile's pairs [w * 64 * BIG_ITEMS, + 64 * BIG_ITEMS), 64 consecutive ones per round
+    const int64_t base = (int64_t)tile * BIG_TILE;
+    const int size = (int)(n - base < BIG_TILE ? n - base : BIG_TILE), first = wave * 64 * BIG_ITEMS;
+    uint64_t key[BIG_ITEMS];
+    uint32_t pos[BIG_ITEMS], rank[BIG_ITEMS];
+    const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+    for (int r = 0; r < BIG_ITEMS; ++r) {
+        const int q = first + r * 64 + lane;
+        key[r] = q < size ? (FIRST ? (uint64_t)keys_in[base + q] : pk_in[base + q]) : 0;
+        pos[r] = q < size ? (FIRST ? (uint32_t)(base + q) : pp_in[base + q]) : 0u;
+    }
+    // this thread's bucket: pairs in all tiles, and in the tiles before this one
+    uint32_t total = 0, before_tile = 0;
+    if (tid < R) {
+        for (int t0 = 0; t0 < tiles; t0 += TILES_AHEAD) {
+            uint32_t v[TILES_AHEAD];
+#pragma unroll
+            for (int i = 0; i < TILES_AHEAD; ++i) v[i] = hist[(int64_t)(t0 + i < tiles ? t0 + i : t0) * R + tid];
+#pragma unroll
+            for (int i = 0; i < TILES_AHEAD; ++i) {
+                total += t0 + i < tiles ? v[i] : 0u;
+                before_tile += t0 + i < tile ? v[i] : 0u;
+            }
+        }
+    }
+    if (stop) return;
+    for (int b = lane; b < R; b += 64) l.place[wave][b] = 0;
+    __asm__ volatile("" ::: "memory");                 // (a wavefront's own counters: LDS serves its accesses in order)
+#pragma unroll
+    for (int r = 0; r < BIG_ITEMS; ++r) {
+        const bool valid = first + r * 64 + lane < size;
+        const uint32_t d = digit_of(key[r], shift, mask);
+        uint64_t same = __ballot(valid);
+        for (int b = 0; b < bits; ++b) {
+            const bool bit = ((d >> b) & 1u) != 0u;
+            const uint64_t v = __ballot(valid && bit);
+            same &= bit ? v : ~v;
+        }
+        uint32_t before = 0;
+        const int leader = valid ? __ffsll((long long)same) - 1 : lane;
+        if (valid && lane == leader) {
+            before = l.place[wave][d];
+            l.place[wave][d] = (uint16_t)(before + (uint32_t)__popcll(same));
+        }
+        before = (uint32_t)__shfl((int)before, leader);
+        rank[r] = before + (uint32_t)__popcll(same & below);
+    }
+    __syncthreads();
+    // the bucket's pairs in the tile, wavefront by wavefront
+    uint32_t in_tile = 0;
+    if (tid < R)
+#pragma unroll
+        for (int w = 0; w < BIG_WAVES; ++w) {
+            const uint32_t c = l.place[w][tid];
+            l.place[w][tid] = (uint16_t)in_tile;
+            in_tile += c;
+        }
+    // the pairs in lower buckets, of all tiles and of this one: scans over the buckets
+    uint32_t all = total, own = in_tile;
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t a = (uint32_t)__shfl_up((int)all, off), o = (uint32_t)__shfl_up((int)own, off);
+        if (lane >= off) { all += a; own += o; }
+    }
+    if (lane == 63) { l.sums[0][wave] = all; l.sums[1][wave] = own; }
+    __syncthreads();
+    uint32_t lower = all - total, start = own - in_tile;
+    for (int w = 0; w < wave; ++w) { lower += l.sums[0][w]; start += l.sums[1][w]; }
+    if (tid < R) {
+        l.out[tid] = (int32_t)(lower + before_tile - start);
+#pragma unroll
+        for (int w = 0; w < BIG_WAVES; ++w) l.place[w][tid] = (uint16_t)(l.place[w][tid] + start);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < BIG_ITEMS; ++r)
+        if (first + r * 64 + lane < size) {
+            const uint32_t at = l.place[wave][digit_of(key[r], shift, mask)] + rank[r];
+            l.key[at] = key[r];
+            l.pos[at] = pos[r];
+        }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < BIG_ITEMS; ++r) {
+        const int i = r * BIG_THREADS + tid;
+        if (i < size) {
+            const uint64_t k = l.key[i];
+            const uint32_t dst = (uint32_t)(l.out[digit_of(k, shift, mask)] + i);
+            pk_out[dst] = k;
+            pp_out[dst] = l.pos[i];
+        }
+    }
+}
+
 // ---- up to FEW_MAX pairs: one workgroup, a bitonic network over key << FEW_BITS | position in LDS -----------------
 // A thread takes one comparison of every step.  Up to a distance of 64 a wavefront's comparisons stay within its 128
 // numbers, and LDS serves a wavefront's accesses in order: only longer distances need a barrier.
@@ -362,7 +521,7 @@ __global__ __launch_bounds__(FEW_THREADS) void k_sort_few(const int64_t *keys, i
 inline size_t up256(size_t x) { return (x + 255) / 256 * 256; }
 
 struct SortPlan {
-    int items;            // pairs per thread: a tile holds 256 * items
+    int items;            // a tile holds 256 * items pairs (beyond BIG_MAX; up to there no tile is smaller than that)
     int passes;
     int bits[8];
     int64_t num_tiles;
@@ -371,10 +530,10 @@ struct SortPlan {
 
 SortPlan sort_plan(int64_t n, int key_bits) {
     SortPlan p{};
-    p.items = n < ((int64_t)1 << 20) ? 4 : 16;
+    p.items = n <= BIG_MAX ? 4 : 16;
     // short inputs are bound by the number of launches: wide digits, few passes; long ones by memory
     // traffic, where narrower digits keep a tile's pairs of one bucket next to each other in the output
-    const int max_bits = n < ((int64_t)1 << 20) ? SORT_MAX_BITS : 8;
+    const int max_bits = n <= BIG_MAX ? SORT_MAX_BITS : 8;
     p.passes = (key_bits + max_bits - 1) / max_bits;
     if (p.passes < 1) p.passes = 1;
     for (int i = 0, left = key_bits; i < p.passes; ++i) {
@@ -392,7 +551,7 @@ SortPlan sort_plan(int64_t n, int key_bits) {
     return p;
 }
 
-// MID: up to MID_MAX pairs
+// MID: up to MID_MAX pairs; ITEMS 0: BIG_MIN to BIG_MAX
 template <int ITEMS, bool MID>
 int sort_run(dpaps_ps *ps, const SortPlan &p, const int64_t *keys, int64_t n, int64_t check_below, uint64_t *skeys, uint32_t *spos, void *scratch,
              hipStream_t st) {
@@ -415,6 +574,19 @@ int sort_run(dpaps_ps *ps, const SortPlan &p, const int64_t *keys, int64_t n, in
             PS_HIP(ps, hipGetLastError());
             if (i == 0) k_sort_mid_scatter<ITEMS, true><<<mid, MID_THREADS, 0, st>>>(keys, nullptr, nullptr, n, shift, bits, hist, out_k, out_p, ps->err);
             else k_sort_mid_scatter<ITEMS, false><<<mid, MID_THREADS, 0, st>>>(nullptr, in_k, in_p, n, shift, bits, hist, out_k, out_p, ps->err);
+            PS_HIP(ps, hipGetLastError());
+        } else if constexpr (ITEMS == 0) {
+            static const hipError_t lds_set[2] = {
+                hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sort_big_scatter<true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(BigLds)),
+                hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sort_big_scatter<false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(BigLds))};
+            PS_HIP(ps, lds_set[0]);
+            PS_HIP(ps, lds_set[1]);
+            const unsigned big = (unsigned)((n + BIG_TILE - 1) / BIG_TILE);
+            if (i == 0) k_sort_big_count<true><<<big, BIG_THREADS, 0, st>>>(keys, nullptr, n, shift, bits, hist, check_below, ps->err);
+            else k_sort_big_count<false><<<big, BIG_THREADS, 0, st>>>(nullptr, in_k, n, shift, bits, hist, 0, ps->err);
+            PS_HIP(ps, hipGetLastError());
+            if (i == 0) k_sort_big_scatter<true><<<big, BIG_THREADS, sizeof(BigLds), st>>>(keys, nullptr, nullptr, n, shift, bits, hist, out_k, out_p, ps->err);
+            else k_sort_big_scatter<false><<<big, BIG_THREADS, sizeof(BigLds), st>>>(nullptr, in_k, in_p, n, shift, bits, hist, out_k, out_p, ps->err);
             PS_HIP(ps, hipGetLastError());
         } else {
             if (i == 0) k_sort_count<ITEMS, true><<<tiles, SORT_THREADS, 0, st>>>(keys, nullptr, n, shift, bits, p.num_tiles, hist, check_below, ps->err);
@@ -446,7 +618,11 @@ int dpaps_key_bits(int64_t num_keys) {
 }
 
 // scratch (bytes) that dpaps_sort_pairs needs for n pairs, besides its two output arrays
-size_t dpaps_sort_scratch_bytes(int64_t n, int key_bits) { return sort_plan(n, key_bits).bytes; }
+// (no less for more pairs)
+size_t dpaps_sort_scratch_bytes(int64_t n, int key_bits) {
+    const size_t bytes = sort_plan(n, key_bits).bytes;
+    return n <= BIG_MAX ? bytes : std::max(bytes, sort_plan(BIG_MAX, key_bits).bytes);
+}
 
 // skeys[q], spos[q] (n each) <- the pairs (keys[p], p) ordered by key, equal keys by p.  Keys must be in
 // [0, 2^key_bits) - or `check` is asked for: a key outside [0, num_keys) then sets the handle's error, and the kernels do
@@ -462,5 +638,7 @@ int dpaps_sort_pairs(dpaps_ps *ps, const int64_t *keys, int64_t n, int key_bits,
     const SortPlan p = sort_plan(n, key_bits);
     if (n <= MID_SHORT) return sort_run<2, true>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
     if (n <= MID_MAX) return sort_run<4, true>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
-    return p.items == 4 ? sort_run<4, false>(ps, p, keys, n, check_below, skeys, spos, scratch, st) : sort_run<16, false>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
+    if (n < BIG_MIN) return sort_run<4, false>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
+    if (n <= BIG_MAX) return sort_run<0, false>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
+    return sort_run<16, false>(ps, p, keys, n, check_below, skeys, spos, scratch, st);
 }
