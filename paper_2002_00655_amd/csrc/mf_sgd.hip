@@ -352,7 +352,7 @@ __device__ __forceinline__ double sse_add_dpp(double x) {
 // NR: pieces of a row per lane (ceil(ceil(L / V) / 8); V = 1: at least that), 0: any number, in a loop
 template <int V, int NR>
 __global__ __launch_bounds__(256) void k_mf_sse(const int32_t *rows, const int32_t *cols, const float *vals, int64_t nnz,
-                                                const float *val, int64_t m, int32_t L, double *partial) {
+                                                const float *val, int64_t m, int32_t L, const int32_t *err, double *partial) {
     typedef float Piece __attribute__((ext_vector_type(V)));
     const int lane = threadIdx.x & 63, j = lane & 7, first = lane & ~7;
     const int pieces = L / V;                               // (V divides the rank)
@@ -434,6 +434,7 @@ __global__ __launch_bounds__(256) void k_mf_sse(const int32_t *rows, const int32
         double t = 0.0;
         for (int i = 0; i < 32; ++i) t += s[i];
         partial[blockIdx.x] = t;
+        if (blockIdx.x == 0) partial[gridDim.x] = (double)*err;
     }
 }
 
@@ -759,10 +760,10 @@ extern "C" int mf_train_sse(ps_handle ps, double *sse_host_out, void *stream) {
     if (!f.row) { ps->last_error = "mf_train_sse before mf_load_ratings"; return PS_EINVAL; }
     hipStream_t st = (hipStream_t)stream;
     const int blocks = sse_blocks(f.nnz), L = ps->L;
-    int rc = dpaps_ws_reserve(ps, SSE_BLOCKS * sizeof(double));
+    int rc = dpaps_ws_reserve(ps, (SSE_BLOCKS + 1) * sizeof(double));
     if (rc) return rc;
     double *partial = (double *)ps->ws;
-#define MF_SSE(V, NR) k_mf_sse<V, NR><<<blocks, 256, 0, st>>>(f.row, f.col, f.val, f.nnz, ps->val, f.m, L, partial)
+#define MF_SSE(V, NR) k_mf_sse<V, NR><<<blocks, 256, 0, st>>>(f.row, f.col, f.val, f.nnz, ps->val, f.m, L, ps->err, partial)
     if (L % 4 == 0) {
         switch ((L / 4 + 7) / 8) {
         case 1: MF_SSE(4, 1); break;
@@ -794,9 +795,11 @@ extern "C" int mf_train_sse(ps_handle ps, double *sse_host_out, void *stream) {
     else MF_SSE(1, 0);
 #undef MF_SSE
     PS_HIP(ps, hipGetLastError());
-    std::vector<double> h(blocks);
-    PS_HIP(ps, hipMemcpyAsync(h.data(), partial, blocks * sizeof(double), hipMemcpyDeviceToHost, st));
-    rc = dpaps_take_error(ps, st);
+    // the sums, and behind them the error flag, in one copy: a second one is 10 us
+    std::vector<double> h(blocks + 1);
+    PS_HIP(ps, hipMemcpyAsync(h.data(), partial, (blocks + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
+    PS_HIP(ps, hipStreamSynchronize(st));
+    rc = h[blocks] != 0.0 ? dpaps_take_error(ps, st) : PS_OK;
     double sse = 0.0;
     for (int i = 0; i < blocks; ++i) sse += h[i];
     *sse_host_out = sse;
