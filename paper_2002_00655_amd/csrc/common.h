@@ -219,7 +219,7 @@ struct PushDone {
 int dpaps_route_pull_push(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, hipStream_t st);   // without the key check
 int dpaps_localize_checked(dpaps_ps *ps, const int64_t *keys, int64_t n, int32_t worker, hipStream_t st);
 int dpaps_push_sort(dpaps_ps *ps, const int64_t *keys, int64_t n, hipStream_t st);     // the two halves of a push of checked keys
-int dpaps_push_reserve_two(dpaps_ps *ps, int64_t most);
+int dpaps_push_reserve(dpaps_ps *ps, int64_t most, int halves);
 int dpaps_push_sort_half(dpaps_ps *ps, int half, int64_t most, const int64_t *keys, int64_t n, hipStream_t st);
 int dpaps_push_add(dpaps_ps *ps, int64_t n, const float *deltas, const PushDone &done, hipStream_t st);
 int dpaps_push_add_step(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, const float *deltas, const PushDone &done, hipStream_t st);

@@ -110,7 +110,7 @@ __device__ __forceinline__ double loss_of(float score, int per) {
 // component per lane), 93 with every row.
 template <int NC, bool EXACT>
 __global__ __launch_bounds__(256) void k_kge_group(KgeBatch t, int32_t D, float lr, float eps, float *store, float *__restrict__ upd,
-                                                    int64_t *keys_out, int64_t num_keys, PushDone done, double *loss, int32_t *err) {
+                                                    int64_t *keys_out, int64_t num_keys, PushDone done, double *loss, bool add_loss, int32_t *err) {
     const int32_t stop = __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     const int lane = threadIdx.x & 63;
     // the data point is the same for all lanes of a wavefront: said so, its keys and row addresses stay in scalar registers
@@ -249,7 +249,7 @@ __global__ __launch_bounds__(256) void k_kge_group(KgeBatch t, int32_t D, float 
     // the losses of all scored triples at once, if anybody asks for them
     if (loss) {
         const double sum = loss_of(score, 1 + ns + no);
-        if (lane == 0) loss[b] = sum;
+        if (lane == 0) loss[b] = add_loss ? loss[b] + sum : sum;
     }
     // subject, relation, object: one AdaGrad step each on the summed gradient, with the accumulators as pulled
 #pragma unroll
@@ -434,12 +434,12 @@ static bool in_place_step(dpaps_ps *ps, const KgeBatch &t, int64_t most, hipStre
 }
 
 static int launch_group(dpaps_ps *ps, const KgeBatch &t, int32_t dim, float lr, float eps, float *upd, int64_t *keys_out, const PushDone &done, double *loss,
-                        hipStream_t st) {
+                        bool add_loss, hipStream_t st) {
     const unsigned blocks = grid_for(t.batch * 64, 256);
 #define KGE_GROUP(NC)                                                                                                                       \
     do {                                                                                                                                    \
-        if (ps->opt_kge_exact) k_kge_group<NC, true><<<blocks, 256, 0, st>>>(t, dim, lr, eps, ps->val, upd, keys_out, ps->K, done, loss, ps->err); \
-        else k_kge_group<NC, false><<<blocks, 256, 0, st>>>(t, dim, lr, eps, ps->val, upd, keys_out, ps->K, done, loss, ps->err);                  \
+        if (ps->opt_kge_exact) k_kge_group<NC, true><<<blocks, 256, 0, st>>>(t, dim, lr, eps, ps->val, upd, keys_out, ps->K, done, loss, add_loss, ps->err); \
+        else k_kge_group<NC, false><<<blocks, 256, 0, st>>>(t, dim, lr, eps, ps->val, upd, keys_out, ps->K, done, loss, add_loss, ps->err);                  \
     } while (0)
     switch ((dim + 63) / 64) {
     case 1: KGE_GROUP(1); break;
@@ -492,7 +492,7 @@ extern "C" int kge_sgd_step(ps_handle ps, int32_t worker, int64_t num_entities, 
     } else if (rows <= dpaps_few_keys()) {
         // Few slots: what costs is launches, and the two streams' waiting for each other.  The update rows' kernel checks
         // and writes the keys, then the sums follow on the one stream.
-        rc = launch_group(ps, t, dim, lr, eps, upd, ukeys, PushDone{}, wanted, st);
+        rc = launch_group(ps, t, dim, lr, eps, upd, ukeys, PushDone{}, wanted, false, st);
         if (rc) return rc;
         rc = dpaps_push_few_step(ps, worker, ukeys, rows, upd, st);
         if (rc) return rc;
@@ -513,7 +513,7 @@ extern "C" int kge_sgd_step(ps_handle ps, int32_t worker, int64_t num_entities, 
         rc = dpaps_push_sort(ps, ukeys, rows, bs);
         if (rc) return rc;
         PS_HIP(ps, hipEventRecord(ps->ev_sorted, bs));
-        rc = launch_group(ps, t, dim, lr, eps, upd, nullptr, done, wanted, st);
+        rc = launch_group(ps, t, dim, lr, eps, upd, nullptr, done, wanted, false, st);
         if (rc) return rc;
         PS_HIP(ps, hipStreamWaitEvent(st, ps->ev_sorted, 0));
         rc = dpaps_push_add_step(ps, worker, ukeys, rows, upd, done, st);
@@ -558,22 +558,6 @@ __global__ void k_kge_relation_keys(int64_t num_entities, int64_t t0, int64_t t1
     if (t < t1) keys[t - t0] = num_entities + rel[t];
 }
 
-// sums[i] <- the sum of loss[LOSS_SHARE i ..), a workgroup's share each
-constexpr int64_t LOSS_SHARE = 4096;
-__global__ __launch_bounds__(256) void k_kge_loss_shares(const double *loss, int64_t n, double *sums) {
-    __shared__ double s[256];
-    const int64_t lo = blockIdx.x * LOSS_SHARE, hi = lo + LOSS_SHARE < n ? lo + LOSS_SHARE : n;
-    double a = 0.0;
-    for (int64_t i = lo + threadIdx.x; i < hi; i += 256) a += loss[i];
-    s[threadIdx.x] = a;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) sums[blockIdx.x] = s[0];
-}
-
 extern "C" int kge_sgd_epoch(ps_handle ps, int64_t num_entities, int32_t dim, int64_t num_triples, const int32_t *subj, const int32_t *rel,
                              const int32_t *obj, int32_t n_neg_subj, const int32_t *neg_subj, int32_t n_neg_obj, const int32_t *neg_obj,
                              const int64_t *part_ptr_host, int32_t num_parts, int64_t batch, int32_t lookahead, float lr, float eps,
@@ -607,10 +591,7 @@ extern "C" int kge_sgd_epoch(ps_handle ps, int64_t num_entities, int32_t dim, in
     const size_t off_ukeys = off_loc + up((size_t)std::max(longest, bmax * ent) * 8);
     const size_t off_upd = off_ukeys + up((size_t)rows_max * 8);
     const size_t off_loss = off_upd + up((size_t)rows_max * ps->L * 4);
-    // (the losses of the whole epoch, in the order the steps have, added up once: after every step they were a launch of one
-    // workgroup on the stream that the steps wait for)
-    const int64_t losses = loss_host_out ? num_triples : 0, shares = (losses + LOSS_SHARE - 1) / LOSS_SHARE;
-    const size_t bytes = off_loss + (size_t)(losses + shares + 1) * 8;
+    const size_t bytes = off_loss + (size_t)(bmax + 2) * 8;
     if (bytes > ps->kge_ws_bytes) {
         PS_HIP(ps, hipStreamSynchronize(vs));
         if (ps->kge_ws) PS_HIP(ps, hipFree(ps->kge_ws));
@@ -623,7 +604,6 @@ extern "C" int kge_sgd_epoch(ps_handle ps, int64_t num_entities, int32_t dim, in
     int64_t *ukeys = (int64_t *)((char *)ps->kge_ws + off_ukeys);
     float *upd = (float *)((char *)ps->kge_ws + off_upd);
     double *loss = (double *)((char *)ps->kge_ws + off_loss);
-    double *loss_sums = loss + losses;
 
     // every index is checked once; both streams start after that
     k_kge_validate<<<grid_for(num_triples, 256), 256, 0, vs>>>(num_entities, ps->K - num_entities, num_triples, subj, rel, obj, ns, neg_subj,
@@ -631,8 +611,12 @@ extern "C" int kge_sgd_epoch(ps_handle ps, int64_t num_entities, int32_t dim, in
     PS_HIP(ps, hipGetLastError());
     PS_HIP(ps, hipEventRecord(ps->ev_fork, vs));
     PS_HIP(ps, hipStreamWaitEvent(bs, ps->ev_fork, 0));
-    int rc = dpaps_push_reserve_two(ps, rows_max);
+    // (without memory for two sets of sorted pairs the steps share one)
+    bool two = true;
+    int rc = dpaps_push_reserve(ps, rows_max, 2);
+    if (rc == PS_ENOMEM) { two = false; rc = dpaps_push_reserve(ps, rows_max, 1); }
     if (rc) return rc;
+    if (loss_host_out && dpaps_zero_words((uint32_t *)loss, 2 * (size_t)bmax, vs)) { ps->last_error = "knowledge-graph epoch: clearing the losses"; return PS_EHIP; }
     auto localize_entities = [&](int64_t t0, int64_t t1, int32_t w) {
         if (t1 <= t0) return (int)PS_OK;
         k_kge_entity_keys<<<grid_for(t1 - t0, 256), 256, 0, bs>>>(t0, t1, subj, obj, ns, neg_subj, no, neg_obj, lkeys);
@@ -650,7 +634,7 @@ extern "C" int kge_sgd_epoch(ps_handle ps, int64_t num_entities, int32_t dim, in
         for (int32_t w = 0; w < num_parts && !rc; ++w)                // the first batch's entities
             rc = localize_entities(part_ptr_host[w], std::min(part_ptr_host[w] + batch, part_ptr_host[w + 1]), w);
     }
-    int64_t steps_done = 0, points_done = 0;
+    int64_t steps_done = 0;
     for (int64_t r = 0; r * batch < longest && !rc; ++r) {
         for (int32_t w = 0; w < num_parts && !rc; ++w) {
             const int64_t t0 = part_ptr_host[w] + r * batch, end = part_ptr_host[w + 1];
@@ -663,8 +647,8 @@ extern "C" int kge_sgd_epoch(ps_handle ps, int64_t num_entities, int32_t dim, in
             // (sorted pairs and flags: two steps take turns with them, so the step before the last has to be through; with one
             // set of pairs, a step's sort waited for the sums of the one before it, and these for the sort: 2,970 us for 32 steps of
             // 1,024 data points over four workers, and 2,600 this way)
-            const int half = (int)(steps_done & 1);
-            if (steps_done > 1) PS_HIP(ps, hipStreamWaitEvent(bs, ps->ev_added[half], 0));
+            const int half = two ? (int)(steps_done & 1) : 0;
+            if (steps_done > (two ? 1 : 0)) PS_HIP(ps, hipStreamWaitEvent(bs, ps->ev_added[half], 0));
             PushDone done;
             const bool in_place = in_place_step(ps, t, bmax, bs, done);
             k_kge_keys<<<grid_for(std::max(nb * (3 + ns + no), n1 * ent), 256), 256, 0, bs>>>(t, ukeys, 0, in_place ? ps->kge_seen : nullptr,
@@ -681,14 +665,15 @@ extern "C" int kge_sgd_epoch(ps_handle ps, int64_t num_entities, int32_t dim, in
             PS_HIP(ps, hipEventRecord(ps->ev_sorted, bs));
             // first stream: the values
             if (in_place) PS_HIP(ps, hipStreamWaitEvent(vs, ps->ev_keys, 0));
-            rc = launch_group(ps, t, dim, lr, eps, upd, nullptr, done, loss_host_out ? loss + points_done : nullptr, vs);
+            // (its losses onto those of the data points at the same places of the batches before; added up once, at the end: after every
+            // step that was a launch of one workgroup on the stream that the steps wait for)
+            rc = launch_group(ps, t, dim, lr, eps, upd, nullptr, done, loss_host_out ? loss : nullptr, true, vs);
             if (rc) break;
             PS_HIP(ps, hipStreamWaitEvent(vs, ps->ev_sorted, 0));
             rc = dpaps_push_add(ps, nb * (3 + ns + no), upd, done, vs);
             if (rc) break;
             PS_HIP(ps, hipEventRecord(ps->ev_added[half], vs));
             ++steps_done;
-            points_done += nb;
         }
     }
     // the second stream joins the first
@@ -696,11 +681,9 @@ extern "C" int kge_sgd_epoch(ps_handle ps, int64_t num_entities, int32_t dim, in
     PS_HIP(ps, hipStreamWaitEvent(vs, ps->ev_join, 0));
     if (rc) return rc;
     if (loss_host_out) {
-        k_kge_loss_shares<<<(unsigned)shares, 256, 0, vs>>>(loss, losses, loss_sums);
+        k_kge_loss_sum<<<1, 256, 0, vs>>>(loss, bmax, loss + bmax);
         PS_HIP(ps, hipGetLastError());
-        k_kge_loss_sum<<<1, 256, 0, vs>>>(loss_sums, shares, loss_sums + shares);
-        PS_HIP(ps, hipGetLastError());
-        PS_HIP(ps, hipMemcpyAsync(loss_host_out, loss_sums + shares, sizeof(double), hipMemcpyDeviceToHost, vs));
+        PS_HIP(ps, hipMemcpyAsync(loss_host_out, loss + bmax, sizeof(double), hipMemcpyDeviceToHost, vs));
         PS_HIP(ps, hipStreamSynchronize(vs));
     }
     return PS_OK;

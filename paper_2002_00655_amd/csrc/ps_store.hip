@@ -733,10 +733,10 @@ int dpaps_push_sort(dpaps_ps *ps, const int64_t *keys, int64_t n, hipStream_t st
     const int rc = dpaps_ws_reserve(ps, push_layout(ps, n).bytes);
     return rc ? rc : push_sort_into(ps, ps->ws, keys, n, false, st);
 }
-// The same for steps that sort ahead of the sums of the step before: scratch for two steps of up to n keys each, and the sort
+// The same for steps that sort ahead of the sums of the step before: scratch for one or two steps of up to n keys each, and the sort
 // into one of the two halves.  (No number of keys needs more than a larger one.)
 static size_t push_half(const dpaps_ps *ps, int64_t most) { return align_up(push_layout(ps, most).bytes); }
-int dpaps_push_reserve_two(dpaps_ps *ps, int64_t most) { return dpaps_ws_reserve(ps, 2 * push_half(ps, most)); }
+int dpaps_push_reserve(dpaps_ps *ps, int64_t most, int halves) { return dpaps_ws_reserve(ps, halves * push_half(ps, most)); }
 int dpaps_push_sort_half(dpaps_ps *ps, int half, int64_t most, const int64_t *keys, int64_t n, hipStream_t st) {
     return push_sort_into(ps, (char *)ps->ws + (half ? push_half(ps, most) : 0), keys, n, false, st);
 }
