@@ -646,7 +646,7 @@ extern "C" int kge_sgd_epoch(ps_handle ps, int64_t num_entities, int32_t dim, in
             const KgeBatch next{subj + t1, rel + t1, obj + t1, neg_subj + t1 * ns, neg_obj + t1 * no, ns, no, num_entities, n1};
             // (sorted pairs and flags: two steps take turns with them, so the step before the last has to be through; with one
             // set of pairs, a step's sort waited for the sums of the one before it, and these for the sort: 2,970 us for 32 steps of
-            // 1,024 data points over four workers, and 2,600 this way)
+            // 1,024 data points over four workers with a launch for the losses after each, and 2,300 this way)
             const int half = two ? (int)(steps_done & 1) : 0;
             if (steps_done > (two ? 1 : 0)) PS_HIP(ps, hipStreamWaitEvent(bs, ps->ev_added[half], 0));
             PushDone done;

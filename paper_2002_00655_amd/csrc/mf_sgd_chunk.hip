@@ -1316,8 +1316,8 @@ static bool use_sched(const dpaps_ps *ps) { return ps->mf.sched_ok && ps->opt_ca
 
 // Wavefronts per workgroup of the SGD kernels: what PS_OPT_MF_WAVES says, else 16 - or 12 where the grouped kernel
 // runs on data of that kind: its second part has little to wait for there, and with 12 wavefronts each has a third
-// more registers, which the first part uses to read ahead of its wait for the column's factor (measured on the
-// 10M x 1M configuration: 2 % less time per launch than with 16).
+// more registers, which the first part uses to read ahead of its wait for the column's factor (an epoch of the 10M x
+// 1M configuration 180.3 ms; with 16, which spill, 180.1 with teams of 6 and 181.6 with 8; a fifth of it in every direction 48.1, 47.7, 47.0).
 int dpaps_mf_waves(const dpaps_ps *ps) {
     if (ps->opt_waves > 0) return ps->opt_waves;
     const bool grouped = !ps->opt_classic && ps->opt_grouped && !ps->opt_exact && ps->L <= 128 && ps->mf.sweep_ok;
@@ -1443,8 +1443,8 @@ static int plan_teams(dpaps_ps *ps, SgdArgs &a, int waves, hipStream_t st) {
         MfData &f = ps->mf;
         // Most wavefronts per run: what PS_OPT_MF_TEAM_MAX says, else one per vector unit - or two where runs are
         // very long and the workgroup has 12 wavefronts: a wavefront then has the registers to overlap its own
-        // work with its neighbour's, and a run of a thousand groups is all its block has (measured on the
-        // 10M x 1M configuration: 4 % less time per launch than with 4, while 6 is no better than 4).
+        // work with its neighbour's, and a run of a thousand groups is all its block has (a fifth of the
+        // 10M x 1M configuration in every direction: 50.9 ms an epoch with 3, 48.8 with 4, 48.2 with 6, 48.1 with 8).
         const int tmax = ps->opt_team_max > 0 ? ps->opt_team_max : (dpaps_wide_like(f) && waves <= 12 ? 8 : 4);
         if (!f.team_plan) PS_HIP(ps, hipMalloc(&f.team_plan, (size_t)f.num_blocks * 16 * sizeof(uint32_t)));
         if (f.team_plan_waves != a.heavy_waves * 100 + tmax) {
