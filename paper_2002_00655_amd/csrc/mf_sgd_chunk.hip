@@ -118,6 +118,9 @@ __device__ __forceinline__ void solve_last(const float &acc, float (&hs)[NV], co
 // in front of the first step: a DPP operand must also keep five wait states from a write of the execution mask
 __device__ __forceinline__ void solve_first() { __asm__ volatile("s_nop 4"); }
 
+// The sum of two offsets, either of which may be DPAPS_PAST_END (the hardware takes it as an unsigned number).
+__device__ __forceinline__ int past_end_sum(int a, int b) { return (int)((uint32_t)a + (uint32_t)b); }
+
 // NV (1 or 2) neighbouring floats of LDS
 template <int NV>
 __device__ __forceinline__ void lds_get(const float *p, float (&x)[NV]) {
@@ -142,12 +145,12 @@ __device__ __forceinline__ void put_row(const __amdgpu_buffer_rsrc_t buf, const 
 template <int NV, bool WIDE>
 __device__ __forceinline__ void get_row(const __amdgpu_buffer_rsrc_t buf, float (&x)[NV], int row_off, const int (&voff)[NV]) {
     if constexpr (NV == 2 && WIDE) {
-        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(buf, row_off + voff[0], 0, 0);
+        const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(buf, past_end_sum(row_off, voff[0]), 0, 0);
         const uint32_t v0 = v[0], v1 = v[1];
         x[0] = __uint_as_float(v0); x[1] = __uint_as_float(v1);
     } else
 #pragma unroll
-        for (int cc = 0; cc < NV; ++cc) x[cc] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, row_off + voff[cc], 0, 0));
+        for (int cc = 0; cc < NV; ++cc) x[cc] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buf, past_end_sum(row_off, voff[cc]), 0, 0));
 }
 
 // The new rows of a group from entry T on, to the store, and the column's factor along with them (scaled, after entry T
@@ -162,7 +165,7 @@ __device__ __forceinline__ void new_rows(const __amdgpu_buffer_rsrc_t wbuf, cons
     for (int cc = 0; cc < NV; ++cc) {
         w_n[cc] = __builtin_fmaf(row_bcast_lane<T>(f), h_t[cc], __builtin_fmaf(-delta, w[T][cc], w[T][cc]));
         h_t[cc] = __builtin_fmaf(row_bcast_lane<T>(g), w[T][cc], h_t[cc]);
-        to[cc] = row_off + voff[cc];
+        to[cc] = past_end_sum(row_off, voff[cc]);
     }
     put_row<NV, WIDE, 0>(wbuf, w_n, to);
     if constexpr (T + 1 < CH) new_rows<T + 1, NV, WIDE>(wbuf, w, h_t, f, g, delta, voff, off);
