@@ -32,8 +32,8 @@ HBM_PEAK_GBS = 8000.0     # MI355X HBM3E, published
 # counters read for a plain 1 GiB copy; summaries under profiles/).  Only valid for the kernel sources they were
 # taken with and for the default settings of the workload: bytes read, bytes written.
 KERNEL_SOURCES = ("mf_sgd_chunk.hip", "mf_sgd.hip", "mf_device.h", "common.h", "sgd_touch.h", "together.h")
-TRAFFIC = {"kernel_sha256_16": "f195c48c7ff97125",
-           "bytes_per_launch": {"large": (195936460.8, 127404646.4), "wide": (1324763545.6, 953185484.8)}}
+TRAFFIC = {"kernel_sha256_16": "72c9e4fef8fe7df8",
+           "bytes_per_launch": {"large": (183543268.0, 125100302.2), "wide": (1269322835.0, 952084510.5)}}
 
 # block boundaries per workload: a column of a block weighs this many entries on top of its own (see --col-cost)
 COL_COST = {"wide": 3.0}
