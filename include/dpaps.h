@@ -103,7 +103,7 @@ enum {
                                    and block */
     PS_OPT_MF_PROFILE = 4,      /* 1: bracket every SGD kernel launch with a pair of events (see mf_profile_read) */
     PS_OPT_MF_GROUPED = 5,      /* 1 (default): where rank <= 128 and PS_OPT_MF_EXACT is off, process the long column
-                                   runs of a block in groups of up to 15 entries with dense 16x16xr products and
+                                   runs of a block in groups of up to 15 entries with a dense 16x16xr product each and
                                    the other entries level by level of their dependencies or row by row; 0: every column run entry by entry */
     PS_OPT_MF_HEAVY_LEN = 6,    /* column runs with at least this many entries count as long (default 48; read by
                                    mf_load_ratings, so set it before) */
