@@ -46,6 +46,7 @@
 // column's entries in stored order - so the result is the same; it only takes the waiting
 // out.  (So do the levels.)
 #include "common.h"
+#include "factor_offsets.h"
 #include "mf_device.h"
 #include "sgd_touch.h"
 #include "together.h"
@@ -62,7 +63,6 @@ typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 
 #define CH 15                    // entries per group (the 16th row of X is the column's row)
 #define AUX_SC1 16               // cache policy of a buffer access: agent scope
-#define DPAPS_PAST_END 0x7F000000   // an offset past the end of any buffer of factors, also with a row's offset added (both below 2^31)
 
 // x, which is the same in all lanes, as a scalar
 __device__ __forceinline__ int64_t uniform_i64(int64_t x) {
@@ -117,9 +117,6 @@ __device__ __forceinline__ void solve_last(const float &acc, float (&hs)[NV], co
 }
 // in front of the first step: a DPP operand must also keep five wait states from a write of the execution mask
 __device__ __forceinline__ void solve_first() { __asm__ volatile("s_nop 4"); }
-
-// The sum of two offsets, either of which may be DPAPS_PAST_END (the hardware takes it as an unsigned number).
-__device__ __forceinline__ int past_end_sum(int a, int b) { return (int)((uint32_t)a + (uint32_t)b); }
 
 // NV (1 or 2) neighbouring floats of LDS
 template <int NV>
@@ -437,7 +434,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
             auto gather = [&](int ln) {
                 int voff[NV];                              // this lane's components, past the end where they do not exist
 #pragma unroll
-                for (int cc = 0; cc < NV; ++cc) voff[cc] = NV * ln + cc < L ? (NV * ln + cc) * 4 : DPAPS_PAST_END;
+                for (int cc = 0; cc < NV; ++cc) voff[cc] = component_at(NV * ln + cc, L);
                 if (NV == 1 || A4 || even_rank) {
 #pragma unroll
                     for (int t = 0; t < CH; ++t) get_row<NV, true>(wbuf, wn[t], rl_i(pf_off, t), voff);
@@ -447,7 +444,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
                 }
             };
             auto plan = [&](int n, int ln) {              // the group of n entries whose data meta_load has fetched
-                pf_off = lane < n ? (mq_row - (int)blk_r0) * L * 4 : DPAPS_PAST_END;
+                pf_off = row_start(lane < n, mq_row - (int)blk_r0, L);
                 pf_val = mq_val;
                 pf_info = lane < n ? mq_info : (int)INFO_NONE;
                 pf_n = n;
@@ -673,7 +670,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
 #pragma unroll
                     for (int cc = 0; cc < NV; ++cc) {
                         h_t[cc] = ho[cc];
-                        voff[cc] = NV * ln + cc < L ? (NV * ln + cc) * 4 : DPAPS_PAST_END;
+                        voff[cc] = component_at(NV * ln + cc, L);
                     }
                     if (NV == 1 || A4 || even_rank) new_rows<0, NV, true>(wbuf, wv, h_t, f_vec, g_vec, delta, voff, c_off);
                     else new_rows<0, NV, false>(wbuf, wv, h_t, f_vec, g_vec, delta, voff, c_off);
@@ -1336,7 +1333,7 @@ static int plan_block_lds(dpaps_ps *ps, SgdArgs &a, bool sched, size_t *lds_out)
     const MfData &f = ps->mf;
     const int L = a.L;
     // the kernel addresses the factors of a block's rows, and of its columns, with 32-bit byte offsets
-    if ((int64_t)f.max_block_rows * L * 4 >= ((int64_t)1 << 31) - 4096 || (int64_t)f.max_block_cols * L * 4 >= ((int64_t)1 << 31) - 4096) {
+    if (!dpaps_span_ok(f.max_block_rows, L) || !dpaps_span_ok(f.max_block_cols, L)) {
         ps->last_error = "a block's factors span 2 GiB or more: use the entry-by-entry kernel (PS_OPT_MF_GROUPED 0)";
         return PS_ELIMIT;
     }
