@@ -105,6 +105,7 @@ struct dpaps_ps {
     // growable scratch for ps_push
     void *ws = nullptr;
     size_t ws_bytes = 0;
+    size_t ws_two_refused = SIZE_MAX; // there was no memory for scratch of two steps of this size (see dpaps_push_reserve_steps)
     void *push_base = nullptr;        // what the sort of a push left for its sums: the scratch it used,
     int64_t push_sorted_n = -1;       // the number of pairs,
     size_t push_off_pos = 0, push_off_part = 0;   // the offsets of the sorted positions and of the partial sums
@@ -219,7 +220,7 @@ struct PushDone {
 int dpaps_route_pull_push(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, hipStream_t st);   // without the key check
 int dpaps_localize_checked(dpaps_ps *ps, const int64_t *keys, int64_t n, int32_t worker, hipStream_t st);
 int dpaps_push_sort(dpaps_ps *ps, const int64_t *keys, int64_t n, hipStream_t st);     // the two halves of a push of checked keys
-int dpaps_push_reserve(dpaps_ps *ps, int64_t most, int halves);
+int dpaps_push_reserve_steps(dpaps_ps *ps, int64_t most, bool *two);
 int dpaps_push_sort_half(dpaps_ps *ps, int half, int64_t most, const int64_t *keys, int64_t n, hipStream_t st);
 int dpaps_push_add(dpaps_ps *ps, int64_t n, const float *deltas, const PushDone &done, hipStream_t st);
 int dpaps_push_add_step(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, const float *deltas, const PushDone &done, hipStream_t st);

@@ -612,9 +612,8 @@ extern "C" int kge_sgd_epoch(ps_handle ps, int64_t num_entities, int32_t dim, in
     PS_HIP(ps, hipEventRecord(ps->ev_fork, vs));
     PS_HIP(ps, hipStreamWaitEvent(bs, ps->ev_fork, 0));
     // (without memory for two sets of sorted pairs the steps share one)
-    bool two = true;
-    int rc = dpaps_push_reserve(ps, rows_max, 2);
-    if (rc == PS_ENOMEM) { two = false; rc = dpaps_push_reserve(ps, rows_max, 1); }
+    bool two = false;
+    int rc = dpaps_push_reserve_steps(ps, rows_max, &two);
     if (rc) return rc;
     if (loss_host_out && dpaps_zero_words((uint32_t *)loss, 2 * (size_t)bmax, vs)) { ps->last_error = "knowledge-graph epoch: clearing the losses"; return PS_EHIP; }
     auto localize_entities = [&](int64_t t0, int64_t t1, int32_t w) {

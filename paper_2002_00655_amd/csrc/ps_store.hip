@@ -22,6 +22,7 @@ int dpaps_fail_hip(dpaps_ps *ps, hipError_t e, const char *what) {
     return e == hipErrorOutOfMemory ? PS_ENOMEM : PS_EHIP;
 }
 
+static size_t ws_with_room(size_t bytes) { return bytes + bytes / 4 + 4096; }
 int dpaps_ws_reserve(dpaps_ps *ps, size_t bytes) {
     if (bytes <= ps->ws_bytes) return PS_OK;
     if (ps->ws) {
@@ -30,7 +31,7 @@ int dpaps_ws_reserve(dpaps_ps *ps, size_t bytes) {
         ps->ws = nullptr;
         ps->ws_bytes = 0;
     }
-    size_t want = bytes + bytes / 4 + 4096;
+    const size_t want = ws_with_room(bytes);
     PS_HIP(ps, hipMalloc(&ps->ws, want));
     ps->ws_bytes = want;
     return PS_OK;
@@ -733,10 +734,34 @@ int dpaps_push_sort(dpaps_ps *ps, const int64_t *keys, int64_t n, hipStream_t st
     const int rc = dpaps_ws_reserve(ps, push_layout(ps, n).bytes);
     return rc ? rc : push_sort_into(ps, ps->ws, keys, n, false, st);
 }
-// The same for steps that sort ahead of the sums of the step before: scratch for one or two steps of up to n keys each, and the sort
+// The same for steps that sort ahead of the sums of the step before: scratch for two steps of up to n keys each, and the sort
 // into one of the two halves.  (No number of keys needs more than a larger one.)
+// Where there is no memory for two (*two false) the steps share one.  The scratch that is there is given up only for a larger one that
+// has been allocated, and a size that was refused is not asked for again: otherwise every call of that size would wait for the device.
 static size_t push_half(const dpaps_ps *ps, int64_t most) { return align_up(push_layout(ps, most).bytes); }
-int dpaps_push_reserve(dpaps_ps *ps, int64_t most, int halves) { return dpaps_ws_reserve(ps, halves * push_half(ps, most)); }
+int dpaps_push_reserve_steps(dpaps_ps *ps, int64_t most, bool *two) {
+    const size_t one = push_half(ps, most), both = 2 * one;
+    *two = true;
+    if (both <= ps->ws_bytes) return PS_OK;
+    if (both < ps->ws_two_refused) {
+        void *larger = nullptr;
+        const hipError_t e = hipMalloc(&larger, ws_with_room(both));
+        if (e == hipSuccess) {
+            if (ps->ws) {
+                const hipError_t through = hipDeviceSynchronize();
+                if (through != hipSuccess) { (void)hipFree(larger); PS_HIP(ps, through); }
+                (void)hipFree(ps->ws);
+            }
+            ps->ws = larger; ps->ws_bytes = ws_with_room(both);
+            return PS_OK;
+        }
+        if (e != hipErrorOutOfMemory) PS_HIP(ps, e);
+        (void)hipGetLastError();
+        ps->ws_two_refused = both;
+    }
+    *two = false;
+    return dpaps_ws_reserve(ps, one);
+}
 int dpaps_push_sort_half(dpaps_ps *ps, int half, int64_t most, const int64_t *keys, int64_t n, hipStream_t st) {
     return push_sort_into(ps, (char *)ps->ws + (half ? push_half(ps, most) : 0), keys, n, false, st);
 }

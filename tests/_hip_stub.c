@@ -17,7 +17,8 @@ static int num_blocks;
 size_t stub_fail_alloc_bytes;                 /* allocations of this size fail */
 size_t stub_fail_zero_bytes;                  /* and so does clearing of an allocation of this size, stub_fail_zero_times times */
 int stub_fail_zero_times;
-int stub_allocs_of_size, stub_device_syncs, stub_stream_syncs;
+int stub_allocs_of_size, stub_device_syncs, stub_stream_syncs, stub_frees, stub_allocs;
+size_t stub_alloc_bytes[4096];                /* what was asked for, in turn */
 char stub_watch[64];                          /* a kernel's name: of its launches are noted */
 int stub_watch_arg;                           /* the pointer that is this argument: */
 int stub_watched, stub_watched_null, stub_watched_uncleared;
@@ -63,12 +64,13 @@ int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t s, void *
     return OK;
 }
 int hipMalloc(void **p, size_t bytes) {
+    stub_alloc_bytes[stub_allocs++ % 4096] = bytes;
     if (bytes == stub_fail_alloc_bytes) { ++stub_allocs_of_size; *p = NULL; last_error = OUT_OF_MEMORY; return OUT_OF_MEMORY; }
     *p = malloc(bytes ? bytes : 1);
     blocks[num_blocks].p = *p; blocks[num_blocks].bytes = bytes; blocks[num_blocks].zeroed = 0; ++num_blocks;
     return OK;
 }
-int hipFree(void *p) { const int i = find(p); if (i >= 0) blocks[i].p = NULL; free(p); return OK; }
+int hipFree(void *p) { ++stub_frees; const int i = find(p); if (i >= 0) blocks[i].p = NULL; free(p); return OK; }
 int hipMemset(void *p, int v, size_t bytes) { (void)v; const int rc = clear(p, bytes); if (rc) last_error = rc; return rc; }
 int hipMemsetAsync(void *p, int v, size_t bytes, void *st) { (void)st; return hipMemset(p, v, bytes); }
 int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) { (void)d; (void)s; (void)n; (void)k; (void)st; return OK; }

@@ -1,5 +1,5 @@
 """CPU: the library's host code with a stand-in for the HIP runtime (tests/_hip_stub.c) whose calls fail on demand: the marks
-and flags of knowledge-graph steps that update rows in place."""
+and flags of knowledge-graph steps that update rows in place, and the two sets of sorted pairs of an epoch."""
 import os
 import subprocess
 import sys
@@ -24,6 +24,11 @@ C.memmove(C.addressof(var("stub_watch", C.c_char * 64)), b"k_kge_keys\0", 11)
 var("stub_watch_arg", C.c_int).value = 3            # where the marks are
 seen = 8 * K
 def flags(batch): return 8 * batch * (3 + ns + no)
+lib.ps_last_error.restype = C.c_char_p
+def epoch(n, batch, h=h):
+    part = (C.c_int64 * 3)(0, n // 2, n)
+    return lib.kge_sgd_epoch(h, C.c_int64(E), C.c_int32(dim), C.c_int64(n), x, x, x, C.c_int32(ns), x, C.c_int32(no), x, part, C.c_int32(2),
+                             C.c_int64(batch), C.c_int32(1), C.c_float(.1), C.c_float(1e-10), None, None)
 def get(*names): return [var("stub_" + n, C.c_int).value for n in names]
 exec(sys.argv[3])
 """
@@ -58,6 +63,39 @@ var("stub_fail_zero_bytes", C.c_size_t).value = flags(400)
 var("stub_fail_zero_times", C.c_int).value = 1
 assert [step(400) for _ in range(3)] == [0, 0, 0]
 assert get("watched_uncleared") == [0]
+""",
+    # an epoch's second set of sorted pairs: no memory, ever - asked for once, without an error's text; the scratch that is there is kept, and
+    # an epoch of a size seen before neither waits nor allocates
+    "no memory for two sets of pairs": """
+asked = (C.c_size_t * 4096).in_dll(stub, "stub_alloc_bytes")
+def server():
+    p = C.c_void_p()
+    assert lib.ps_create(C.c_int64(K), C.c_int32(4 * dim), C.c_int32(2), C.byref(p)) == 0
+    return p
+sizes = []
+for batch in (500, 700):                             # what two sets take: a new server's epoch allocates its own scratch, then these
+    other = server()
+    at = get("allocs")[0]
+    assert epoch(4 * batch, batch, other) == 0
+    new = [s for s in asked[at:get("allocs")[0]] if s not in (seen, flags(batch))]
+    assert len(new) == 2, new
+    sizes.append(new[1])
+var("stub_fail_alloc_bytes", C.c_size_t).value = sizes[0]
+for i in range(3):
+    before = get("device_syncs", "stream_syncs", "frees", "allocs")
+    assert epoch(2000, 500) == 0 and lib.ps_last_error(h) == b"", (i, lib.ps_last_error(h))
+    assert get("allocs_of_size") == [1], (i, get("allocs_of_size"))
+    if i > 0: assert get("device_syncs", "stream_syncs", "frees", "allocs") == before, (i, before)
+var("stub_fail_alloc_bytes", C.c_size_t).value = sizes[1]
+at = get("allocs")[0]
+assert epoch(2800, 700) == 0 and sizes[1] not in asked[at:get("allocs")[0]]      # nor is more than what was refused
+# scratch that one set fits into stays where it is
+other = server()
+assert lib.ps_push(other, C.c_int32(0), x, C.c_int64(500 * (3 + ns + no)), x, None) == 0
+var("stub_fail_alloc_bytes", C.c_size_t).value = sizes[0]
+var("stub_allocs_of_size", C.c_int).value = 0
+before = get("device_syncs", "frees")
+assert epoch(2000, 500, other) == 0 and get("device_syncs", "frees") == before and get("allocs_of_size") == [1]
 """,
     # what the header says: a step's own memory waits for the stream, not for the device
     "waits": """
