@@ -317,7 +317,7 @@ __global__ __launch_bounds__(1024) void k_mf_sgd(SgdArgs a) {
 // ---------------------------------------------------------------------------
 // Products and sums in double.  What bounds it is the way of the factor rows to the compute units - 2 rows of 4 L bytes per
 // entry, far more than the entries themselves - and the instructions on them.  So
-// - 8 lanes take an entry, 8 entries a wavefront at a time, SSE_AHEAD times as many in flight: a lane holds the pieces
+// - 8 lanes take an entry, 8 entries a wavefront at a time, up to rank 128 the next 8 in flight as well: a lane holds the pieces
 //   j, j + 8, ... of both rows (V numbers each: 16 bytes where the rank is a multiple of 4, 8 where it is even), and the
 //   8 partial sums are added with three lane exchanges inside the vector unit;
 // - the 8 lanes go through neighbouring entries one after the other, and most of those are of one column: its factor is read,
@@ -349,13 +349,17 @@ __device__ __forceinline__ double sse_add_dpp(double x) {
     return x + __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
 }
 
-// NR: pieces of a row per lane (ceil(ceil(L / V) / 8); V = 1: at least that), 0: any number, in a loop
+// NR: pieces of a row per lane (ceil(L / V / 8), or more where FULL leaves room), at most 32 numbers: ranks end at 256.  FULL: the
+// first FULL of a lane's pieces exist in all lanes.
+// (Ranks past 128 that are no multiple of 4 too: with a loop over the pieces instead, one on its way at a time, 2M entries of 200k x 50
+// took XXX.)
 template <int V, int NR>
 __global__ __launch_bounds__(256) void k_mf_sse(const int32_t *rows, const int32_t *cols, const float *vals, int64_t nnz,
                                                 const float *val, int64_t m, int32_t L, const int32_t *err, double *partial) {
     typedef float Piece __attribute__((ext_vector_type(V)));
     const int lane = threadIdx.x & 63, j = lane & 7, first = lane & ~7;
     const int pieces = L / V;                               // (V divides the rank)
+    constexpr int FULL = V == 1 ? (NR > 16 ? NR - 8 : 0) : (NR > 8 ? NR - 2 : NR - 1);
     // batches of 64 entries: this die's share, its wavefronts side by side
     const int64_t batches = (nnz + 63) / 64, share = (batches + SSE_DIES - 1) / SSE_DIES;
     const int64_t die = blockIdx.x % SSE_DIES;
@@ -367,63 +371,48 @@ __global__ __launch_bounds__(256) void k_mf_sse(const int32_t *rows, const int32
         const bool valid = p < nnz;
         const int32_t row = valid ? rows[p] : 0, col = valid ? cols[p] : 0;
         const float v = valid ? vals[p] : 0.0f;
-        if constexpr (NR > 0) {
-            constexpr int AHEAD = NR * V <= 16 ? 2 : 1;
-            auto in = [&](int r) { return (V > 1 && r + 1 < NR) || j + 8 * r < pieces; };   // (lanes past the row's end read its first piece and count it as zero)
-            int32_t last = -1;                              // the column whose factor is in h64
-            double h64[NR * V];
+        constexpr int AHEAD = NR * V <= 16 ? 2 : 1;
+        auto in = [&](int r) { return r < FULL || j + 8 * r < pieces; };   // (lanes past the row's end read its first piece and count it as zero)
+        int32_t last = -1;                              // the column whose factor is in h64
+        double h64[NR * V];
 #pragma unroll
-            for (int r = 0; r < NR * V; ++r) h64[r] = 0.0;
+        for (int r = 0; r < NR * V; ++r) h64[r] = 0.0;
 #pragma unroll 1
-            for (int u0 = 0; u0 < 8; u0 += AHEAD) {
-                Piece w[AHEAD][NR], h[AHEAD][NR];
-                bool fresh[AHEAD];
+        for (int u0 = 0; u0 < 8; u0 += AHEAD) {
+            Piece w[AHEAD][NR], h[AHEAD][NR];
+            bool fresh[AHEAD];
 #pragma unroll
-                for (int q = 0; q < AHEAD; ++q) {
-                    const int32_t c = __shfl(col, first + u0 + q);
-                    const Piece *pw = reinterpret_cast<const Piece *>(val + (int64_t)__shfl(row, first + u0 + q) * L);
+            for (int q = 0; q < AHEAD; ++q) {
+                const int32_t c = __shfl(col, first + u0 + q);
+                const Piece *pw = reinterpret_cast<const Piece *>(val + (int64_t)__shfl(row, first + u0 + q) * L);
 #pragma unroll
-                    for (int r = 0; r < NR; ++r) w[q][r] = pw[in(r) ? j + 8 * r : 0];
-                    fresh[q] = c != last;
-                    last = c;
-                    if (fresh[q]) {
-                        const Piece *ph = reinterpret_cast<const Piece *>(val + (m + c) * (int64_t)L);
+                for (int r = 0; r < NR; ++r) w[q][r] = pw[in(r) ? j + 8 * r : 0];
+                fresh[q] = c != last;
+                last = c;
+                if (fresh[q]) {
+                    const Piece *ph = reinterpret_cast<const Piece *>(val + (m + c) * (int64_t)L);
 #pragma unroll
-                        for (int r = 0; r < NR; ++r) h[q][r] = ph[in(r) ? j + 8 * r : 0];
-                    }
+                    for (int r = 0; r < NR; ++r) h[q][r] = ph[in(r) ? j + 8 * r : 0];
                 }
+            }
 #pragma unroll
-                for (int q = 0; q < AHEAD; ++q) {
-                    if (fresh[q]) {
-#pragma unroll
-                        for (int r = 0; r < NR; ++r)
-#pragma unroll
-                            for (int i = 0; i < V; ++i) h64[r * V + i] = (double)(in(r) ? h[q][r][i] : 0.0f);
-                    }
-                    double d = 0.0;
+            for (int q = 0; q < AHEAD; ++q) {
+                if (fresh[q]) {
 #pragma unroll
                     for (int r = 0; r < NR; ++r)
 #pragma unroll
-                        for (int i = 0; i < V; ++i) d = fma((double)(in(r) ? w[q][r][i] : 0.0f), h64[r * V + i], d);
-                    d = sse_add_dpp<0xB1>(d);               // quad_perm [1,0,3,2]: pairs
-                    d = sse_add_dpp<0x4E>(d);               // quad_perm [2,3,0,1]: quads
-                    d = sse_add_dpp<0x141>(d);              // row_half_mirror: 8 lanes
-                    const double e = (double)__shfl(v, first + u0 + q) - d;
-                    acc += p0 + u0 + q < nnz ? e * e : 0.0;
+                        for (int i = 0; i < V; ++i) h64[r * V + i] = (double)(in(r) ? h[q][r][i] : 0.0f);
                 }
-            }
-        } else {
-            for (int u = 0; u < 8; ++u) {
-                const float *pw = val + (int64_t)__shfl(row, first + u) * L, *ph = val + (m + __shfl(col, first + u)) * (int64_t)L;
                 double d = 0.0;
-                for (int k = j; k < pieces; k += 8)
 #pragma unroll
-                    for (int i = 0; i < V; ++i) d = fma((double)pw[k * V + i], (double)ph[k * V + i], d);
-                d = sse_add_dpp<0xB1>(d);
-                d = sse_add_dpp<0x4E>(d);
-                d = sse_add_dpp<0x141>(d);
-                const double e = (double)__shfl(v, first + u) - d;
-                acc += p0 + u < nnz ? e * e : 0.0;
+                for (int r = 0; r < NR; ++r)
+#pragma unroll
+                    for (int i = 0; i < V; ++i) d = fma((double)(in(r) ? w[q][r][i] : 0.0f), h64[r * V + i], d);
+                d = sse_add_dpp<0xB1>(d);               // quad_perm [1,0,3,2]: pairs
+                d = sse_add_dpp<0x4E>(d);               // quad_perm [2,3,0,1]: quads
+                d = sse_add_dpp<0x141>(d);              // row_half_mirror: 8 lanes
+                const double e = (double)__shfl(v, first + u0 + q) - d;
+                acc += p0 + u0 + q < nnz ? e * e : 0.0;
             }
         }
     }
@@ -773,8 +762,7 @@ extern "C" int mf_train_sse(ps_handle ps, double *sse_host_out, void *stream) {
         case 5: MF_SSE(4, 5); break;
         case 6: MF_SSE(4, 6); break;
         case 7: MF_SSE(4, 7); break;
-        case 8: MF_SSE(4, 8); break;
-        default: MF_SSE(4, 0); break;
+        default: MF_SSE(4, 8); break;
         }
     } else if (L % 2 == 0) {
         switch ((L / 2 + 7) / 8) {
@@ -786,13 +774,17 @@ extern "C" int mf_train_sse(ps_handle ps, double *sse_host_out, void *stream) {
         case 6: MF_SSE(2, 6); break;
         case 7: MF_SSE(2, 7); break;
         case 8: MF_SSE(2, 8); break;
-        default: MF_SSE(2, 0); break;
+        case 9: case 10: MF_SSE(2, 10); break;
+        case 11: case 12: MF_SSE(2, 12); break;
+        case 13: case 14: MF_SSE(2, 14); break;
+        default: MF_SSE(2, 16); break;
         }
     } else if (L <= 16) MF_SSE(1, 2);
     else if (L <= 32) MF_SSE(1, 4);
     else if (L <= 64) MF_SSE(1, 8);
     else if (L <= 128) MF_SSE(1, 16);
-    else MF_SSE(1, 0);
+    else if (L <= 192) MF_SSE(1, 24);
+    else MF_SSE(1, 32);
 #undef MF_SSE
     PS_HIP(ps, hipGetLastError());
     // the sums, and behind them the error flag, in one copy: a second one is 10 us

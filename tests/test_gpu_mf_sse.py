@@ -6,7 +6,8 @@ import pytest
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rank", [1, 2, 3, 4, 15, 16, 17, 32, 33, 50, 62, 64, 66, 100, 126, 127, 128, 129, 130, 200, 250, 255, 256])
+@pytest.mark.parametrize("rank", [1, 2, 3, 4, 15, 16, 17, 32, 33, 50, 62, 64, 66, 100, 126, 127, 128, 129, 130, 145, 146, 161, 162, 178, 191, 193, 200, 210, 225,
+                                  226, 242, 250, 254, 255, 256])
 def test_train_sse_sums_in_double(rank):
     import torch
     from paper_2002_00655_amd import ps as P
@@ -32,7 +33,7 @@ def test_train_sse_sums_in_double(rank):
         assert abs(got - want) <= 2 * bound, (got, want, bound)
 
 
-@pytest.mark.parametrize("nnz", [2047, 2048, 2049, 4097, 524288, 524289, 700001])
+@pytest.mark.parametrize("nnz", [2047, 2048, 2049, 4097, 131071, 131072, 131073, 700001])
 def test_train_sse_at_numbers_of_workgroups(nnz):
     """Entry counts at which the launch gets more workgroups, and the most it gets; the bound as above."""
     import torch
