@@ -352,7 +352,7 @@ __device__ __forceinline__ double sse_add_dpp(double x) {
 // NR: pieces of a row per lane (ceil(L / V / 8), or more where FULL leaves room), at most 32 numbers: ranks end at 256.  FULL: the
 // first FULL of a lane's pieces exist in all lanes.
 // (Ranks past 128 that are no multiple of 4 too: with a loop over the pieces instead, one on its way at a time, 2M entries of 200k x 50
-// took XXX.)
+// took 1,169 us at rank 255, now 268.)
 template <int V, int NR>
 __global__ __launch_bounds__(256) void k_mf_sse(const int32_t *rows, const int32_t *cols, const float *vals, int64_t nnz,
                                                 const float *val, int64_t m, int32_t L, const int32_t *err, double *partial) {
