@@ -168,6 +168,17 @@ __device__ __forceinline__ void new_rows(const __amdgpu_buffer_rsrc_t wbuf, cons
     if constexpr (T + 1 < CH) new_rows<T + 1, NV, WIDE>(wbuf, w, h_t, f, g, delta, voff, off);
 }
 
+// The same for rows of up to 16 components: four rows are kept, a row of 16 lanes each (sub: which), and leave together.
+template <int T>
+__device__ __forceinline__ void new_rows_by_four(const __amdgpu_buffer_rsrc_t wbuf, const float (&w)[CH][1], float &h_t, float keep, float f, float g,
+                                                 float delta, int voff, const int (&off)[4], int sub) {
+    const float w_n = __builtin_fmaf(row_bcast_lane<T>(f), h_t, __builtin_fmaf(-delta, w[T][0], w[T][0]));
+    h_t = __builtin_fmaf(row_bcast_lane<T>(g), w[T][0], h_t);
+    keep = sub == T % 4 ? w_n : keep;
+    if constexpr (T % 4 == 3 || T + 1 == CH) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(keep), wbuf, past_end_sum(off[T / 4], voff), 0, 0);
+    if constexpr (T + 1 < CH) new_rows_by_four<T + 1>(wbuf, w, h_t, keep, f, g, delta, voff, off, sub);
+}
+
 // NT = number of 16-component tiles of a factor row (rank <= 16 NT); A4: the rank is a multiple of 4,
 // so every row starts on a 16-byte boundary and is read in 16-byte pieces
 // (otherwise in 8-byte pieces where the rank is even, in 4-byte pieces where it is odd)
@@ -428,14 +439,20 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
             int pf_off = DPAPS_PAST_END, pf_info = (int)INFO_NONE, pf_n = 0;   // where the row starts in the block's (bytes; no entry: past the end)
             float pf_val = 0.0f;
             bool pf_ready = false;
-            float wn[CH][NV];
+            // rows of up to 16 components: four in one access, a row of 16 lanes each (60,000 x 5,000, 4M entries, rank 16: an
+            // epoch 2,877 us, one by one 3,078)
+            constexpr int RPA = NT == 1 ? 4 : 1, NA = (CH + RPA - 1) / RPA;
+            float wn[NA][NV];
             // (A row in one access: fewer lines are looked up than in accesses of a tile of every row, 64 bytes each wherever they
             // start.  100k x 10k, rank 50: an epoch with its loss 6.91 ms that way, 6.68 this; rank 100 the same both ways.)
             auto gather = [&](int ln) {
                 int voff[NV];                              // this lane's components, past the end where they do not exist
 #pragma unroll
-                for (int cc = 0; cc < NV; ++cc) voff[cc] = component_at(NV * ln + cc, L);
-                if (NV == 1 || A4 || even_rank) {
+                for (int cc = 0; cc < NV; ++cc) voff[cc] = component_at(RPA > 1 ? ln & 15 : NV * ln + cc, L);
+                if constexpr (RPA > 1) {
+#pragma unroll
+                    for (int i = 0; i < NA; ++i) get_row<NV, true>(wbuf, wn[i], bperm_i(pf_off, RPA * i + (ln >> 4)), voff);   // (lane 15: no entry)
+                } else if (NV == 1 || A4 || even_rank) {
 #pragma unroll
                     for (int t = 0; t < CH; ++t) get_row<NV, true>(wbuf, wn[t], rl_i(pf_off, t), voff);
                 } else {
@@ -506,7 +523,10 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
                 // X: rows 0 .. 14 from the read-ahead go to the staging area (row 15 stays zero), where the registers of the
                 // read-ahead are free again, and come back in the layout of the dense product: lane (n16, hi) has
                 // components 16 j + 4 hi .. + 3 of row n16 in xp[j]
-                if (NV * ln < 16 * NT) {
+                if constexpr (RPA > 1) {
+#pragma unroll
+                    for (int i = 0; i < NA; ++i) lds_put<NV>(&stg[(RPA * i + (ln >> 4)) * RS + (ln & 15)], wn[i]);
+                } else if (NV * ln < 16 * NT) {
 #pragma unroll
                     for (int t = 0; t < CH; ++t) lds_put<NV>(&stg[t * RS + NV * ln], wn[t]);
                 }
@@ -558,7 +578,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
 
                     // ---- the part that needs h as the previous group left it --------------------------------
                     f32x4 hq[NT];                          // h in quarters, for p_s = <w_s, h>
-                    const int ck = NV * ln < 16 * NT ? NV * ln : 0;
+                    const int ck = RPA > 1 ? ln & 15 : NV * ln < 16 * NT ? NV * ln : 0;
                     // the rows' components for the new h further down
                     if constexpr (RICH) {
 #pragma unroll
@@ -670,9 +690,14 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
 #pragma unroll
                     for (int cc = 0; cc < NV; ++cc) {
                         h_t[cc] = ho[cc];
-                        voff[cc] = component_at(NV * ln + cc, L);
+                        voff[cc] = component_at(RPA > 1 ? ln & 15 : NV * ln + cc, L);
                     }
-                    if (NV == 1 || A4 || even_rank) new_rows<0, NV, true>(wbuf, wv, h_t, f_vec, g_vec, delta, voff, c_off);
+                    if constexpr (RPA > 1) {
+                        int off[NA];
+#pragma unroll
+                        for (int i = 0; i < NA; ++i) off[i] = bperm_i(c_off, RPA * i + (ln >> 4));
+                        new_rows_by_four<0>(wbuf, wv, h_t[0], 0.0f, f_vec, g_vec, delta, voff[0], off, ln >> 4);
+                    } else if (NV == 1 || A4 || even_rank) new_rows<0, NV, true>(wbuf, wv, h_t, f_vec, g_vec, delta, voff, c_off);
                     else new_rows<0, NV, false>(wbuf, wv, h_t, f_vec, g_vec, delta, voff, c_off);
                 }
                 // ---- hand the rows on: the stores must have completed before the tickets move ---------

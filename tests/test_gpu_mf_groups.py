@@ -1,5 +1,5 @@
 """Long column runs in groups of up to 15 entries, at ranks around the edges of how a group's rows are gathered and stored:
-one or two neighbouring components per lane, rows that start on 4, 8 or 16 bytes, a last tile with one component and a full
+four rows in one access (up to 16 components) or one, with one or two neighbouring components per lane, rows that start on 4, 8 or 16 bytes, a last tile with one component and a full
 one; runs shorter than a group, of whole groups and one more; against the sequential fp32 oracle."""
 import numpy as np
 import pytest
@@ -8,7 +8,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("waves", [16, 12])
-@pytest.mark.parametrize("rank", [2, 3, 49, 62, 63, 64, 65, 66, 68, 97, 98, 99, 112, 126, 127, 128])
+@pytest.mark.parametrize("rank", [1, 2, 3, 4, 15, 16, 17, 49, 62, 63, 64, 65, 66, 68, 97, 98, 99, 112, 126, 127, 128])
 def test_group_rows_at_edges_of_the_rank(rank, waves):
     from paper_2002_00655_amd import workloads as wl
     from _util import compare_state, gpu_epochs, oracle_epochs

@@ -1,13 +1,14 @@
 """A row block whose factors span nearly 2 GiB, the most that the grouped SGD kernel takes: its accesses of rows past a group's end and of
 components past the rank must not reach rows of the block (rank 100: lanes past the rank; 127: the same, component by component; 128:
-only rows past a group's end), against the entry-by-entry kernel."""
+only rows past a group's end; 15 and 16: four rows in one access), against the entry-by-entry kernel."""
 import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("rank,m,waves", [(100, 5_340_000, 16), (100, 5_368_698, 12), (127, 4_210_000, 16), (128, 4_194_295, 16)])
+@pytest.mark.parametrize("rank,m,waves", [(100, 5_340_000, 16), (100, 5_368_698, 12), (127, 4_210_000, 16), (128, 4_194_295, 16),
+                                          (15, 35_600_000, 16), (16, 33_554_367, 16)])
 def test_a_row_block_of_nearly_two_gib(rank, m, waves):
     import torch
     from paper_2002_00655_amd import ps as P
