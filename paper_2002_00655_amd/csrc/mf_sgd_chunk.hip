@@ -443,6 +443,10 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
             // epoch 2,877 us, one by one 3,078)
             constexpr int RPA = NT == 1 ? 4 : 1, NA = (CH + RPA - 1) / RPA;
             float wn[NA][NV];
+            // Two components per lane at a rank that is no multiple of 4: pairs where the rank is even, one by one where it is odd, both in
+            // the code.  In the loop of blocks up to rank 96 one by one only: with both it spills 46 registers, with one 4 to 7 (60,000 x 5,000,
+            // rank 66: an epoch with hand-over 6,480 and 5,872 us, rank 82 6,802 and 6,149; rank 126: 9,120 and 9,440).
+            constexpr bool TWO_FORMS = !(AGENT_H && NT <= 6);
             // (A row in one access: fewer lines are looked up than in accesses of a tile of every row, 64 bytes each wherever they
             // start.  100k x 10k, rank 50: an epoch with its loss 6.91 ms that way, 6.68 this; rank 100 the same both ways.)
             auto gather = [&](int ln) {
@@ -452,7 +456,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
                 if constexpr (RPA > 1) {
 #pragma unroll
                     for (int i = 0; i < NA; ++i) get_row<NV, true>(wbuf, wn[i], bperm_i(pf_off, RPA * i + (ln >> 4)), voff);   // (lane 15: no entry)
-                } else if (NV == 1 || A4 || even_rank) {
+                } else if (NV == 1 || A4 || (TWO_FORMS && even_rank)) {
 #pragma unroll
                     for (int t = 0; t < CH; ++t) get_row<NV, true>(wbuf, wn[t], rl_i(pf_off, t), voff);
                 } else {
@@ -697,7 +701,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
 #pragma unroll
                         for (int i = 0; i < NA; ++i) off[i] = bperm_i(c_off, RPA * i + (ln >> 4));
                         new_rows_by_four<0>(wbuf, wv, h_t[0], 0.0f, f_vec, g_vec, delta, voff[0], off, ln >> 4);
-                    } else if (NV == 1 || A4 || even_rank) new_rows<0, NV, true>(wbuf, wv, h_t, f_vec, g_vec, delta, voff, c_off);
+                    } else if (NV == 1 || A4 || (TWO_FORMS && even_rank)) new_rows<0, NV, true>(wbuf, wv, h_t, f_vec, g_vec, delta, voff, c_off);
                     else new_rows<0, NV, false>(wbuf, wv, h_t, f_vec, g_vec, delta, voff, c_off);
                 }
                 // ---- hand the rows on: the stores must have completed before the tickets move ---------

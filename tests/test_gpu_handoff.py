@@ -12,11 +12,13 @@ from _util import oracle_epochs, compare_state, check_handoff_order, replay_sche
 pytestmark = pytest.mark.gpu
 
 
-def _server(w, rb, cb, blocked, workers):
+def _server(w, rb, cb, blocked, workers, heavy_len=None):
     import torch
     from paper_2002_00655_amd import ps as P
     br, bc, bv, bp = blocked
     srv = P.ParameterServer(w.m + w.n, w.rank, workers)
+    if heavy_len:
+        srv.set_option(P.OPT_MF_HEAVY_LEN, heavy_len)
     dev = torch.device("cuda")
     srv.push(torch.arange(w.m, device=dev), torch.from_numpy(w.W0).to(dev))
     srv.push(w.m + torch.arange(w.n, device=dev), torch.from_numpy(w.H0).to(dev))
@@ -153,6 +155,22 @@ def test_uncached_columns_and_rank_not_multiple_of_four():
     check_handoff_order(order)
     srv.status()
     compare_state(_oracle(w, rb, cb, blocked, d, [order]), srv, exact=False)
+
+
+@pytest.mark.parametrize("rank", [1, 15, 16, 17, 65, 66, 68, 82, 95, 96, 97, 98, 126, 127])
+def test_groups_at_edges_of_the_rank(rank):
+    """Column runs of up to 150 entries in groups of 15, at the ranks where a group's rows are fetched and stored in another
+    form: up to 16, up to and past 96, multiples of 4, even, odd."""
+    from oracle.oracle import mf_block_ratings
+    w = wl.make_mf("tiny", scale=0.3, seed=rank, rank=rank)
+    d = 2
+    rb, cb = wl.equal_bounds(w.m, d), wl.equal_bounds(w.n, d)
+    blocked = mf_block_ratings(w.m, w.n, w.rows, w.cols, w.vals, rb, cb)
+    print(f"case rank={rank} nnz={w.nnz}", flush=True)
+    srv = _server(w, rb, cb, blocked, d, heavy_len=4)
+    orders = [srv.mf_sgd_epoch_handoff(w.lr, w.lam) for _ in range(2)]
+    srv.status()
+    compare_state(_oracle(w, rb, cb, blocked, d, orders), srv, exact=False)
 
 
 def test_limits():
