@@ -793,6 +793,19 @@ static int push_few(dpaps_ps *ps, RouteArgs stats, const int64_t *keys, int64_t 
     PS_HIP(ps, hipGetLastError());
     return PS_OK;
 }
+// Whether a push of n checked or unchecked keys goes without sorted pairs, in one launch.  What k_push_few takes grows with its workgroups - one
+// for 16 keys and 64 pieces of a row - and in each with the keys it compares; the sort and the sums take 17 to 21 us up to 1,024
+// keys and 27 above, nearly whatever the row.  Up to so many workgroups it is the faster or as fast: 1,024 keys of 1,022 values
+// (512 workgroups) 20.5 us both ways, 850 of 1,023 (864) 23.1 and sorted 21.3, 700 (704) 16.9 and 21.6; 2,048 of 768 (384) 25.4 and 26.1, of
+// 510 (512) 29.9 and 28.0, of 255 (512; one value per piece, so few registers that two workgroups share a compute unit) 22.7 and 27.3, of
+// 1,023 (2,048) 68 and 28.
+static bool push_without_sort(const dpaps_ps *ps, int64_t n, const float *deltas) {
+    if (ps->opt_push_sequential || n > FEW_KEYS) return false;
+    if (n <= PUSH_RANGE) return true;
+    const int width = push_width(ps->L, deltas);
+    const int64_t groups = ceil_div64(n, FEW_WAVES) * ceil_div64(ps->L / width, 64);
+    return groups <= (n <= 1024 ? 768 : width == 1 ? 512 : 448);
+}
 // A push whose sums need no sorted pairs: one launch.
 static int push_at_once(dpaps_ps *ps, const RouteArgs &stats, const int64_t *keys, int64_t n, const float *deltas, hipStream_t st) {
     return n <= PUSH_RANGE ? push_tiny(ps, stats, keys, n, deltas, st) : push_few(ps, stats, keys, n, deltas, st);
@@ -850,11 +863,11 @@ RouteArgs dpaps_step_route(dpaps_ps *ps, int32_t worker, int64_t n, hipStream_t 
     return a;
 }
 
-// The same for a step of at most dpaps_few_keys() keys: one launch, unless its terms are to be added strictly in order or
-// its accesses are counted one after the other.
+// The same for a step of at most dpaps_few_keys() keys: one launch, unless its rows are too long for that, its terms are to be added
+// strictly in order or its accesses are counted one after the other.
 int64_t dpaps_few_keys() { return FEW_KEYS; }
 int dpaps_push_few_step(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64_t n, const float *deltas, hipStream_t st) {
-    if (ps->opt_push_sequential || ps->loc) {
+    if (ps->loc || !push_without_sort(ps, n, deltas)) {
         const int rc = dpaps_push_sort(ps, keys, n, st);
         return rc ? rc : dpaps_push_add_step(ps, worker, keys, n, deltas, PushDone{}, st);
     }
@@ -865,7 +878,7 @@ int dpaps_push_few_step(dpaps_ps *ps, int32_t worker, const int64_t *keys, int64
 // One push call with its scratch in `base` (NULL: the handle's own, which grows): the keys checked by the sort's first
 // kernel, the sums with the statistics beside them.
 static int push_call(dpaps_ps *ps, void *base, int32_t worker, const int64_t *keys, int64_t n, const float *deltas, hipStream_t st) {
-    const bool at_once = n <= FEW_KEYS && !ps->opt_push_sequential;
+    const bool at_once = push_without_sort(ps, n, deltas);
     int rc;
     if (!at_once) {
         if (!base) {

@@ -1,5 +1,6 @@
-"""A push of 65 to 2,048 keys, which is one launch: bit for bit the sums that the interface describes - the pairs ordered by
-key, in ranges of 64, a key's terms inside a range one after the other, its ranges' sums in order."""
+"""A push of 65 to 2,048 keys, which is one launch, or a sort and the sums where rows are long: bit for bit the sums that the
+interface describes - the pairs ordered by key, in ranges of 64, a key's terms inside a range one after the other, its ranges'
+sums in order."""
 import numpy as np
 import pytest
 
@@ -29,6 +30,18 @@ def _push(val, keys, d):
 @pytest.mark.parametrize("kind", ["distinct", "one", "two", "eight", "mixed"])
 @pytest.mark.parametrize("L", [1, 6, 64, 65, 100, 128, 130, 260, 400])
 def test_push_of_few_keys_is_what_the_interface_says(kind, L):
+    _check(kind, L, (65, 127, 128, 129, 333, 1023, 1025, 2047, 2048))
+
+
+# long rows: around the numbers of workgroups up to which it is one launch (768 up to 1,024 keys, then 448, or 512 of one value per piece)
+@pytest.mark.parametrize("kind", ["distinct", "mixed"])
+@pytest.mark.parametrize("L,sizes", [(1023, (768, 769, 1024, 1025, 2048)), (1022, (1024, 1025, 1500)), (1000, (1024, 1025, 1792, 1793, 2048)),
+                                     (255, (2047, 2048)), (257, (1632, 1633, 2048))])
+def test_push_of_few_long_rows(kind, L, sizes):
+    _check(kind, L, sizes)
+
+
+def _check(kind, L, sizes):
     import torch
     from oracle.oracle import Oracle
     from paper_2002_00655_amd import ps as P
@@ -36,7 +49,7 @@ def test_push_of_few_keys_is_what_the_interface_says(kind, L):
     rng = np.random.default_rng(L)
     srv, orc = P.ParameterServer(K, L, W), Oracle("f32", K, L, W)
     val = np.zeros((K, L), np.float32)
-    for n in (65, 127, 128, 129, 333, 1023, 1025, 2047, 2048):
+    for n in sizes:
         print(f"case kind={kind} L={L} n={n}", flush=True)
         if kind == "distinct":
             keys = rng.permutation(K)[:n]
