@@ -328,12 +328,14 @@ __global__ __launch_bounds__(MID_THREADS) void k_sort_mid_scatter(const int64_t 
     }
 }
 
-// ---- from BIG_MIN up to BIG_MAX pairs: the same two launches per digit with tiles of 8,192 pairs, which a workgroup brings into the order of
+// ---- from BIG_MIN up to BIG_MAX pairs: two launches per digit with tiles of 8,192 pairs, which a workgroup brings into the order of
 // their buckets in LDS first, so that the stores of a bucket's pairs (8 of a tile at 1,024 buckets) leave side by side.
 // Every workgroup sums all tiles' counters itself: 0.5 MB of them at a million pairs.  1,000,003 pairs of 19 bits: 63 us
-// in four launches; 78 in eight, as below BIG_MIN, where small tiles give more workgroups (200,000 pairs: as fast).
+// in four launches; 78 in eight, as below BIG_MIN, where smaller tiles give up to one workgroup per compute unit: pushes of rows of 4 with
+// keys of 19 bits, 131,073 pairs 68 us and 73 with large tiles, 180,000 72.6 and 75.9, 262,144 79.5 and 80.3 (keys of 22 bits 87.8 and 91.6); 280,000
+// 91.6 and 88.0, 400,000 102 and 96.5.
 constexpr int BIG_THREADS = 1024, BIG_WAVES = BIG_THREADS / 64, BIG_ITEMS = 8, BIG_TILE = BIG_THREADS * BIG_ITEMS;
-constexpr int64_t BIG_MIN = (int64_t)1 << 18, BIG_MAX = (int64_t)1 << 21;
+constexpr int64_t BIG_MIN = ((int64_t)1 << 18) + 1, BIG_MAX = (int64_t)1 << 21;
 static_assert(BIG_THREADS >= 1 << SORT_MAX_BITS && BIG_TILE < 1 << 16, "a bucket per thread, places in a tile of 16 bits");
 struct BigLds {
     uint64_t key[BIG_TILE];
