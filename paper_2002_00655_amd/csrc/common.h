@@ -1,6 +1,7 @@
 // Internal declarations shared by the translation units of libdpaps.
 #pragma once
 
+#include <atomic>
 #include <hip/hip_runtime.h>
 #include <cstdint>
 #include <string>
@@ -236,6 +237,12 @@ int dpaps_side_stream(dpaps_ps *ps);   // creates the library's second stream an
 int dpaps_zero_words(uint32_t *p, size_t words, hipStream_t st);
 int dpaps_fail_hip(dpaps_ps *ps, hipError_t e, const char *what);
 int dpaps_ws_reserve(dpaps_ps *ps, size_t bytes);
+
+// How much dynamic LDS a kernel may have, device by device: what is allowed holds for the device that is current, and a process may have
+// handles on several.  One of these, static, per kernel.
+constexpr int DPAPS_DEVICES = 64;
+struct LdsAllowed { std::atomic<size_t> on[DPAPS_DEVICES]; };
+int dpaps_allow_lds(dpaps_ps *ps, LdsAllowed &allowed, const void *kernel, size_t bytes);   // asked for where it is more than before
 
 #define PS_HIP(ps, call)                                                   \
     do {                                                                   \

@@ -578,11 +578,10 @@ int sort_run(dpaps_ps *ps, const SortPlan &p, const int64_t *keys, int64_t n, in
             else k_sort_mid_scatter<ITEMS, false><<<mid, MID_THREADS, 0, st>>>(nullptr, in_k, in_p, n, shift, bits, hist, out_k, out_p, ps->err);
             PS_HIP(ps, hipGetLastError());
         } else if constexpr (ITEMS == 0) {
-            static const hipError_t lds_set[2] = {
-                hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sort_big_scatter<true>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(BigLds)),
-                hipFuncSetAttribute(reinterpret_cast<const void *>(&k_sort_big_scatter<false>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)sizeof(BigLds))};
-            PS_HIP(ps, lds_set[0]);
-            PS_HIP(ps, lds_set[1]);
+            static LdsAllowed first, other;
+            int rc = dpaps_allow_lds(ps, first, reinterpret_cast<const void *>(&k_sort_big_scatter<true>), sizeof(BigLds));
+            if (!rc) rc = dpaps_allow_lds(ps, other, reinterpret_cast<const void *>(&k_sort_big_scatter<false>), sizeof(BigLds));
+            if (rc) return rc;
             const unsigned big = (unsigned)((n + BIG_TILE - 1) / BIG_TILE);
             if (i == 0) k_sort_big_count<true><<<big, BIG_THREADS, 0, st>>>(keys, nullptr, n, shift, bits, hist, check_below, ps->err);
             else k_sort_big_count<false><<<big, BIG_THREADS, 0, st>>>(nullptr, in_k, n, shift, bits, hist, 0, ps->err);

@@ -484,8 +484,9 @@ extern "C" int kge_sgd_step(ps_handle ps, int32_t worker, int64_t num_entities, 
     int rc;
     double *const wanted = loss_host_out ? loss : nullptr;            // the losses, if the caller asks for them
     if (rows <= KGE_FEW_SLOTS && kge_few_lds(rows, ps->L) <= KGE_FEW_LDS && !ps->opt_kge_exact && !ps->opt_push_sequential && !ps->loc) {
-        static const hipError_t lds_set = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_kge_few), hipFuncAttributeMaxDynamicSharedMemorySize, KGE_FEW_LDS);
-        PS_HIP(ps, lds_set);
+        static LdsAllowed allowed;
+        rc = dpaps_allow_lds(ps, allowed, reinterpret_cast<const void *>(&k_kge_few), KGE_FEW_LDS);
+        if (rc) return rc;
         const RouteArgs a = dpaps_step_route(ps, worker, rows, st);
         k_kge_few<<<1 + a.blocks, KGE_FEW_THREADS, kge_few_lds(rows, ps->L), st>>>(a, t, dim, lr, eps, ps->val, ps->K, wanted, ps->err);
         PS_HIP(ps, hipGetLastError());

@@ -435,12 +435,9 @@ int dpaps_take_error(dpaps_ps *ps, hipStream_t st);   // ps_store.hip
 template <int NV, bool EXACT>
 static int launch_sgd(dpaps_ps *ps, const SgdArgs &a, int ntasks, int threads, size_t lds, hipStream_t st) {
     constexpr int D = NV <= 2 ? 16 : 8;       // read-ahead depth (D*NV registers per lane)
-    static size_t configured = 0;
-    if (lds > configured) {
-        PS_HIP(ps, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mf_sgd<NV, EXACT, D>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        configured = lds;
-    }
+    static LdsAllowed allowed;
+    const int rc = dpaps_allow_lds(ps, allowed, reinterpret_cast<const void *>(&k_mf_sgd<NV, EXACT, D>), lds);
+    if (rc) return rc;
     k_mf_sgd<NV, EXACT, D><<<ntasks, threads, lds, st>>>(a);
     PS_HIP(ps, hipGetLastError());
     return PS_OK;

@@ -1388,14 +1388,11 @@ static int plan_block_lds(dpaps_ps *ps, SgdArgs &a, bool sched, size_t *lds_out)
 template <int NT, bool A4, int MAXT, bool LONG_RUNS, bool SCHED>
 static int launch_chunk_t(dpaps_ps *ps, SgdArgs a, int ntasks, int waves, hipStream_t st) {
     size_t lds = 0;
-    const int rc = plan_block_lds<NT>(ps, a, SCHED, &lds);
+    int rc = plan_block_lds<NT>(ps, a, SCHED, &lds);
     if (rc) return rc;
-    static size_t configured = 0;
-    if (lds > configured) {
-        PS_HIP(ps, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mf_sgd_chunk<NT, A4, MAXT, LONG_RUNS, SCHED>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-        configured = lds;
-    }
+    static LdsAllowed allowed;
+    rc = dpaps_allow_lds(ps, allowed, reinterpret_cast<const void *>(&k_mf_sgd_chunk<NT, A4, MAXT, LONG_RUNS, SCHED>), lds);
+    if (rc) return rc;
     k_mf_sgd_chunk<NT, A4, MAXT, LONG_RUNS, SCHED><<<ntasks, 64 * waves, lds, st>>>(a);
     PS_HIP(ps, hipGetLastError());
     return PS_OK;
@@ -1443,14 +1440,11 @@ __global__ void k_team_plan(const int64_t *blk_run_ptr, const int32_t *blk_nheav
 template <int NT, bool A4, bool LONG_RUNS, bool SCHED>
 static int launch_handoff_t(dpaps_ps *ps, SgdArgs a, int workers, hipStream_t st) {
     size_t lds = 0;
-    const int rc = plan_block_lds<NT>(ps, a, SCHED, &lds);
+    int rc = plan_block_lds<NT>(ps, a, SCHED, &lds);
     if (rc) return rc;
-    static size_t configured = 0;
-    if (lds > configured) {
-        PS_HIP(ps, hipFuncSetAttribute(reinterpret_cast<const void *>(&k_mf_sgd_handoff<NT, A4, LONG_RUNS, SCHED>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                       (int)lds));
-        configured = lds;
-    }
+    static LdsAllowed allowed;
+    rc = dpaps_allow_lds(ps, allowed, reinterpret_cast<const void *>(&k_mf_sgd_handoff<NT, A4, LONG_RUNS, SCHED>), lds);
+    if (rc) return rc;
     k_mf_sgd_handoff<NT, A4, LONG_RUNS, SCHED><<<workers, 1024, lds, st>>>(a);
     PS_HIP(ps, hipGetLastError());
     return PS_OK;

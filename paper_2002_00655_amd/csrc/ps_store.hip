@@ -37,6 +37,17 @@ int dpaps_ws_reserve(dpaps_ps *ps, size_t bytes) {
     return PS_OK;
 }
 
+int dpaps_allow_lds(dpaps_ps *ps, LdsAllowed &allowed, const void *kernel, size_t bytes) {
+    static std::mutex mutex;                           // (so that it never shrinks under a launch of another handle)
+    const bool kept = ps->device >= 0 && ps->device < DPAPS_DEVICES;
+    if (kept && bytes <= allowed.on[ps->device].load(std::memory_order_acquire)) return PS_OK;
+    std::lock_guard<std::mutex> lock(mutex);
+    if (kept && bytes <= allowed.on[ps->device].load(std::memory_order_relaxed)) return PS_OK;
+    PS_HIP(ps, hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes));
+    if (kept) allowed.on[ps->device].store(bytes, std::memory_order_release);
+    return PS_OK;
+}
+
 static inline size_t align_up(size_t x, size_t a = 256) { return (x + a - 1) / a * a; }
 
 // ---------------------------------------------------------------------------
@@ -911,12 +922,11 @@ extern "C" int ps_push(ps_handle ps, int32_t worker, const int64_t *keys, int64_
 // address only, never the array's name.
 constexpr size_t PUSH_STATIC_BYTES = (size_t)16 << 20;
 static __device__ __align__(256) unsigned char scratch[PUSH_STATIC_BYTES];
-constexpr int PUSH_STATIC_DEVICES = 64;
-static void *g_scratch_ptr[PUSH_STATIC_DEVICES];
+static void *g_scratch_ptr[DPAPS_DEVICES];
 static std::mutex g_scratch_mutex;
 
 static int static_scratch_init(dpaps_ps *ps) {
-    if (ps->device < 0 || ps->device >= PUSH_STATIC_DEVICES) return PS_OK;     // ps_push_noalloc will refuse
+    if (ps->device < 0 || ps->device >= DPAPS_DEVICES) return PS_OK;     // ps_push_noalloc will refuse
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
     if (!g_scratch_ptr[ps->device]) {
         void *p = nullptr;
@@ -930,7 +940,7 @@ extern "C" int ps_push_noalloc(ps_handle ps, int32_t worker, const int64_t *keys
     if (!ps || n < 0 || (n > 0 && (!keys || !deltas))) return PS_EINVAL;
     if (worker < -1 || worker >= ps->W) return PS_EWORKER;
     if (n == 0) return PS_OK;
-    void *base = ps->device >= 0 && ps->device < PUSH_STATIC_DEVICES ? g_scratch_ptr[ps->device] : nullptr;
+    void *base = ps->device >= 0 && ps->device < DPAPS_DEVICES ? g_scratch_ptr[ps->device] : nullptr;
     if (!base) { ps->last_error = "ps_push_noalloc: no fixed scratch on this device"; return PS_EINVAL; }
     if (n > PS_PUSH_NOALLOC_MAX_KEYS || (n + PUSH_RANGE - 1) / PUSH_RANGE * ps->L > PS_PUSH_NOALLOC_MAX_PARTIAL ||
         push_layout(ps, n).bytes > PUSH_STATIC_BYTES) {

@@ -23,6 +23,16 @@ char stub_watch[64];                          /* a kernel's name: of its launche
 int stub_watch_arg;                           /* the pointer that is this argument: */
 int stub_watched, stub_watched_null, stub_watched_uncleared;
 
+int stub_device;                              /* the current one; launches with more dynamic LDS than was allowed for the kernel there: */
+int stub_lds_refused, stub_lds_calls;
+static struct { const void *host; int device; size_t bytes; } lds[4096];
+static size_t lds_allowed(const void *host) {
+    size_t most = 65536;
+    for (int i = 0; i < stub_lds_calls && i < 4096; ++i)
+        if (lds[i].host == host && lds[i].device == stub_device && lds[i].bytes > most) most = lds[i].bytes;
+    return most;
+}
+
 static int find(const void *p) {
     for (int i = 0; i < num_blocks; ++i)
         if (blocks[i].p && (char *)p >= (char *)blocks[i].p && (char *)p < (char *)blocks[i].p + blocks[i].bytes) return i;
@@ -47,7 +57,8 @@ static dim3 cfg_g, cfg_b; static size_t cfg_s; static void *cfg_st;
 int __hipPushCallConfiguration(dim3 g, dim3 b, size_t s, void *st) { cfg_g = g; cfg_b = b; cfg_s = s; cfg_st = st; return OK; }
 int __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *s, void **st) { *g = cfg_g; *b = cfg_b; *s = cfg_s; *st = cfg_st; return OK; }
 int hipLaunchKernel(const void *f, dim3 g, dim3 b, void **args, size_t s, void *st) {
-    (void)g; (void)b; (void)s; (void)st;
+    (void)g; (void)b; (void)st;
+    if (s > lds_allowed(f)) ++stub_lds_refused;
     const char *name = "";
     for (int i = 0; i < num_kernels; ++i) if (kernels[i].host == f) name = kernels[i].name;
     if (strstr(name, "k_fill_u32")) {
@@ -76,7 +87,7 @@ int hipMemsetAsync(void *p, int v, size_t bytes, void *st) { (void)st; return hi
 int hipMemcpyAsync(void *d, const void *s, size_t n, int k, void *st) { (void)d; (void)s; (void)n; (void)k; (void)st; return OK; }
 int hipGetLastError(void) { const int e = last_error; last_error = OK; return e; }
 const char *hipGetErrorString(int e) { (void)e; return "stub"; }
-int hipGetDevice(int *d) { *d = 0; return OK; }
+int hipGetDevice(int *d) { *d = stub_device; return OK; }
 int hipDeviceGetAttribute(int *v, int a, int d) { (void)a; (void)d; *v = 65536; return OK; }
 int hipGetSymbolAddress(void **p, const void *s) { (void)s; static char x[16]; *p = x; return OK; }
 int hipDeviceSynchronize(void) { ++stub_device_syncs; return OK; }
@@ -87,4 +98,8 @@ int hipStreamWaitEvent(void *st, void *e, unsigned f) { (void)st; (void)e; (void
 int hipEventCreateWithFlags(void **e, unsigned f) { (void)f; *e = malloc(1); return OK; }
 int hipEventDestroy(void *e) { free(e); return OK; }
 int hipEventRecord(void *e, void *st) { (void)e; (void)st; return OK; }
-int hipFuncSetAttribute(const void *f, int a, int v) { (void)f; (void)a; (void)v; return OK; }
+int hipFuncSetAttribute(const void *f, int a, int v) {
+    (void)a;
+    if (stub_lds_calls < 4096) { lds[stub_lds_calls].host = f; lds[stub_lds_calls].device = stub_device; lds[stub_lds_calls].bytes = (size_t)v; ++stub_lds_calls; }
+    return OK;
+}

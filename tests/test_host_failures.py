@@ -1,5 +1,6 @@
 """CPU: the library's host code with a stand-in for the HIP runtime (tests/_hip_stub.c) whose calls fail on demand: the marks
-and flags of knowledge-graph steps that update rows in place, and the two sets of sorted pairs of an epoch."""
+and flags of knowledge-graph steps that update rows in place, the two sets of sorted pairs of an epoch, and what
+is set up per device."""
 import os
 import subprocess
 import sys
@@ -96,6 +97,22 @@ var("stub_fail_alloc_bytes", C.c_size_t).value = sizes[0]
 var("stub_allocs_of_size", C.c_int).value = 0
 before = get("device_syncs", "frees")
 assert epoch(2000, 500, other) == 0 and get("device_syncs", "frees") == before and get("allocs_of_size") == [1]
+""",
+    # kernels with more than 64 KB of dynamic LDS: allowed on the device of the handle, once per handle
+    "LDS on a second device": """
+handles = []
+for device in (0, 1):
+    var("stub_device", C.c_int).value = device
+    p = C.c_void_p()
+    assert lib.ps_create(C.c_int64(K), C.c_int32(256), C.c_int32(2), C.byref(p)) == 0
+    handles.append(p)
+    for i in range(2):
+        if i: before = get("lds_calls")
+        assert lib.ps_push(p, C.c_int32(0), x, C.c_int64(300_000), x, None) == 0
+        assert lib.kge_sgd_step(p, C.c_int32(-1), C.c_int64(E), C.c_int32(64), C.c_int64(8), x, x, x, C.c_int32(2), x, C.c_int32(3), x,
+                                C.c_float(.1), C.c_float(1e-10), None, None) == 0
+    assert get("lds_calls") == before, device
+    assert get("lds_refused") == [0], (device, get("lds_refused"))
 """,
     # what the header says: a step's own memory waits for the stream, not for the device
     "waits": """
