@@ -32,7 +32,8 @@
  *       allocates (the push's scratch: waits for the device; the step's own: for `stream`); calls of a size
  *       seen before do not wait.  kge_sgd_step / kge_sgd_epoch with loss_host_out also wait for `stream` to hand back the loss.
  *       A step of more than 2048 slots whose negatives are at most half of the entities keeps 8 bytes per key of the
- *       server (allocated by the first such step) and 8 per slot besides, and does without where there is no memory;
+ *       server (allocated by the first such step) and 8 per slot besides, and does without where there is no memory; so does an
+ *       epoch with the second of its two sets of sorted pairs.  What was refused is not asked for again;
  *   mf_sgd_epoch     the first epoch after mf_load_ratings allocates a small per-block plan; an epoch whose
  *       schedule differs from the previous call's waits for `stream` before it replaces the schedule on the
  *       device (and allocates if it is longer); repeated epochs with one schedule do neither;

@@ -20,7 +20,8 @@
 //                      offsets in wavefront order, so that pairs of one bucket keep their
 //                      input order - the pass is stable - and every pair is stored.
 // Up to MID_MAX pairs the tiles are few and larger, and every workgroup of the scatter works out its offsets from all
-// tiles' counters itself: two launches per pass instead of four.  Up to FEW_MAX pairs one workgroup sorts them in LDS.
+// tiles' counters itself: two launches per pass instead of four; so they are from BIG_MIN up to BIG_MAX pairs, in larger
+// tiles that are put in order in LDS before they are stored.  Up to FEW_MAX pairs one workgroup sorts them in LDS.
 // A caller that has not checked its keys asks for it: the first kernel then sets the handle's error, which ends the rest.
 // Integer work only: the result is the same bit for bit whatever the scheduling.
 #include "common.h"

@@ -272,8 +272,10 @@ __global__ __launch_bounds__(256) void k_kge_group(KgeBatch t, int32_t D, float 
 // A step of so few data points that their slots fit side by side in one workgroup's LDS: all of it in one launch - the keys
 // checked, every slot's row read once, a wavefront per scored triple for the scores and one per slot for gradient, AdaGrad step and
 // sum, each slot's terms in the order of the other path.  A second workgroup counts the statistics.
-// Bound by a launch and two trips to memory, keys and rows.  A data point with 5 + 5 negatives, dim 100, and its
-// rows read back: 19.7 us, 23.2 with the update rows and the push in launches of their own (11 + 6 us), which is what the host takes now.
+// Bound by a launch and two trips to memory, keys and rows, one compute unit's way to them.  A data point with 5 + 5 negatives, dim 100, and its
+// rows read back: 13.4 us, 22.5 with the update rows and the push in launches of their own (11 + 6 us).  A step by itself, this way and
+// that: 13 slots of dim 16, 100 and 256 6.9 us and 14.7, 7.9 and 19.9, 11.8 and 26.6; 52 to 64 slots of dim 16 and 50 9.3 to 13.9 and 22.8 to 28.0; what
+// no longer fits in LDS (52 slots of dim 100: 28.8) is not measured this way.  One workgroup is the faster one wherever it fits.
 // LDS: the keys, the rows as pulled, the update rows, and the derivatives of the scored triples' losses.
 constexpr int KGE_FEW_SLOTS = 64, KGE_FEW_THREADS = 1024, KGE_FEW_LDS = 128 << 10;
 static size_t kge_few_lds(int64_t slots, int32_t L) { return (size_t)slots * 2 * L * 4 > sizeof(RouteLds) ? (size_t)slots * 2 * L * 4 : sizeof(RouteLds); }

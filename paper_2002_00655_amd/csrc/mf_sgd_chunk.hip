@@ -61,7 +61,7 @@ typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 
 typedef __attribute__((address_space(3))) f32x4 lds_f32x4;
 
-#define CH 15                    // entries per group (the 16th row of X is the column's row)
+#define CH 15                    // entries per group (the 16th row of X is zero)
 #define AUX_SC1 16               // cache policy of a buffer access: agent scope
 
 // x, which is the same in all lanes, as a scalar
@@ -179,9 +179,9 @@ __device__ __forceinline__ void new_rows_by_four(const __amdgpu_buffer_rsrc_t wb
     if constexpr (T + 1 < CH) new_rows_by_four<T + 1>(wbuf, w, h_t, keep, f, g, delta, voff, off, sub);
 }
 
-// NT = number of 16-component tiles of a factor row (rank <= 16 NT); A4: the rank is a multiple of 4,
-// so every row starts on a 16-byte boundary and is read in 16-byte pieces
-// (otherwise in 8-byte pieces where the rank is even, in 4-byte pieces where it is odd)
+// NT = number of 16-component tiles of a factor row (rank <= 16 NT); A4: the rank is a multiple of 4, so every row starts on
+// a 16-byte boundary.  A group's rows are fetched and stored a row at a time (up to 16 components: four), 4 bytes a lane, or past 64 components
+// 8 where the rank is even; the second part takes rows in pieces of 16 bytes, otherwise of 8 where the rank is even and 4 where it is odd.
 // AGENT_H: the column factors and the owner map are read and written with agent-scope accesses, which the caches
 // of a compute die pass through to memory, so that the workgroup that takes the column block next - on any die -
 // reads what this one wrote, without a write-back or an invalidation of whole caches (the row factors need none
@@ -634,7 +634,7 @@ __device__ __forceinline__ void sgd_block(const SgdArgs &a, float *lds_f, const 
                     // dependent instruction per entry.  The new h = c^k h + lr c^(k-1) sum_s eps_s w_s collects its terms
                     // along the way with the same broadcast.  Steps past the group's end work on rows of X that are
                     // zero and on finite values, so what they compute changes nothing that is used; the chain has no
-                    // branches.  Lane 15 (the row of X that holds h) computes something finite that is never used.
+                    // branches.  Lane 15 (the row of X that is always zero) computes something finite that is never used.
                     float acc = vs - p;
                     float hs[NV];
 #pragma unroll
@@ -1346,7 +1346,8 @@ static bool use_sched(const dpaps_ps *ps) { return ps->mf.sched_ok && ps->opt_ca
 // Wavefronts per workgroup of the SGD kernels: what PS_OPT_MF_WAVES says, else 16 - or 12 where the grouped kernel
 // runs on data of that kind: its second part has little to wait for there, and with 12 wavefronts each has a third
 // more registers, which the first part uses to read ahead of its wait for the column's factor (an epoch of the 10M x
-// 1M configuration 180.3 ms; with 16, which spill, 180.1 with teams of 6 and 181.6 with 8; a fifth of it in every direction 48.1, 47.7, 47.0).
+// 1M configuration 180.1 ms twice; with 16, which spill, 179.7 with teams of 6 and 181.3 with 8; a fifth of it in every direction 42.5 and 42.6, with 16
+// and teams of 4, 6 and 8 43.6, 43.4 and 43.2).
 int dpaps_mf_waves(const dpaps_ps *ps) {
     if (ps->opt_waves > 0) return ps->opt_waves;
     const bool grouped = !ps->opt_classic && ps->opt_grouped && !ps->opt_exact && ps->L <= 128 && ps->mf.sweep_ok;
@@ -1467,7 +1468,7 @@ static int plan_teams(dpaps_ps *ps, SgdArgs &a, int waves, hipStream_t st) {
         // Most wavefronts per run: what PS_OPT_MF_TEAM_MAX says, else one per vector unit - or two where runs are
         // very long and the workgroup has 12 wavefronts: a wavefront then has the registers to overlap its own
         // work with its neighbour's, and a run of a thousand groups is all its block has (a fifth of the
-        // 10M x 1M configuration in every direction: 50.9 ms an epoch with 3, 48.8 with 4, 48.2 with 6, 48.1 with 8).
+        // 10M x 1M configuration in every direction, its column ranges of another weight: 50.9 ms an epoch with 3, 48.8 with 4, 48.2 with 6, 48.1 with 8).
         const int tmax = ps->opt_team_max > 0 ? ps->opt_team_max : (dpaps_wide_like(f) && waves <= 12 ? 8 : 4);
         if (!f.team_plan) PS_HIP(ps, hipMalloc(&f.team_plan, (size_t)f.num_blocks * 16 * sizeof(uint32_t)));
         if (f.team_plan_waves != a.heavy_waves * 100 + tmax) {

@@ -144,8 +144,8 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 // workgroup 256 * AHEAD consecutive pieces of the result, a thread every 256th of them: its keys, then its pieces, are
 // asked for together.  The first route.blocks workgroups count the statistics beside that; a call of few keys checks
 // them here (a larger one in a launch before).
-// Bound by the memory's random reads.  1,000,003 Zipf keys of 100 values on 256 nodes with the check and the
-// statistics: 118 us, 3,000 keys 10, 100 keys 7 in one launch; with the statistics in a launch of their own and one
+// Bound by the memory's random reads.  1,000,003 Zipf keys of 100 values on 256 nodes with the check (5 us) and the statistics: 130 us, 104
+// where the last-level cache still holds the store's 200 MB; 3,000 keys 10, 100 keys 7 in one launch; with the statistics in a launch of their own and one
 // piece per thread 172, 20 and 10.  4 pieces ahead of 16 bytes instead of one: 133 us instead of 151; 8 of 4 bytes (rows
 // of 51): 80 instead of 157, 4: 90.
 // STREAM: results that no cache holds are written past them: 300,000 rows of 400: 90 us instead of 143, a million of 100:
@@ -301,8 +301,7 @@ __device__ __forceinline__ void push_range(int cnt, int p0, int p1, u64 skips, u
 
 // The ranges of a call; the first route.blocks workgroups (of the first 64 components) count its statistics instead.
 // SPLIT wavefronts share a range, each the keys whose terms start in its part: where there are few ranges that is what
-// makes wavefronts enough (333 keys of 100 values: 8 us instead of 17, 20,001 of 50: 12 instead of 19); with many it only
-// repeats the reading of the keys.
+// makes wavefronts enough (20,001 keys of 50 values: 12 us instead of 19); with many it only repeats the reading of the keys.
 template <class Piece, int SPLIT>
 __global__ __launch_bounds__(256) void k_push_ranges(RouteArgs route, PushDone done, const uint64_t *skeys, const uint32_t *spos, int64_t n, int32_t P,
                                                       const Piece *deltas, Piece *val, Piece *part, const int32_t *err) {
@@ -361,7 +360,8 @@ __global__ __launch_bounds__(64) void k_push_tiny(RouteArgs route, const int64_t
 // range per wavefront, its sums in LDS.  The first route.blocks workgroups count the statistics.
 // Bound by a launch and two trips to memory behind each other (keys, rows), above 1,024 keys by the comparisons.  A push of 333 keys of
 // 100 values on 256 nodes: 7.6 us, sorted and added in three launches 16.8; 2,048 keys 13.3 and 27.3, all of them one key 28.2 and 33.1,
-// of 20 keys 17.2 and 32.0 (78 with a workgroup's positions side by side).
+// of 20 keys 17.2 and 32.0 (78 with a workgroup's positions side by side).  On 8 nodes, rows of 1, 16, 64, 256 and 400: 65 to 1,024 keys take
+// 0.32 to 0.63 of what sort and sums take, 2,048 keys 0.4 to 0.9; longer rows: see push_without_sort.
 constexpr int FEW_THREADS = 1024, FEW_WAVES = FEW_THREADS / 64, FEW_OWN = 2, FEW_RANGES = (int)FEW_KEYS / PUSH_RANGE + 1;
 template <class Piece>
 __global__ __launch_bounds__(FEW_THREADS) void k_push_few(RouteArgs route, const int64_t *keys, int n, int32_t P, const Piece *deltas, Piece *val,
@@ -558,8 +558,7 @@ extern "C" int ps_create(int64_t num_keys, int32_t value_len, int32_t num_worker
     ps->lds_bytes = v;
     CR(hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, ps->device));
     ps->num_cu = v;
-    // slack after the last row: the grouped SGD kernel reads rows in 16-byte pieces up to the next multiple of 16
-    // components, and parks switched-off lanes just past the end of a block's factors
+    // slack after the last row: a read of as many components as the longest factor has (256) that starts in it stays inside the allocation
     size_t vbytes = ((size_t)num_keys * value_len + 256) * sizeof(float);
     CR(hipMalloc(&ps->val, vbytes));
     CR(hipMemset(ps->val, 0, vbytes));

@@ -30,8 +30,10 @@ __device__ __forceinline__ bool few_keys_off(const int64_t *keys, int64_t n, int
     return few_keys_off<AHEAD>(keys, n, K, err, [](int64_t, int64_t) {});
 }
 
-// The flag as work before this launch left it, for kernels that nothing else in their launch sets it for: asked for here, looked at when
-// the kernel's first reads, which need no check, are on their way - a trip to memory less for every kernel of a call.
+// The flag as work before this launch left it: asked for here, looked at when the kernel's first reads, which need no check, are on their
+// way - a trip to memory less for every kernel of a call.  In the kernels that check the keys beside other work - the first count of
+// a sort, a step's keys - the launch may set the flag itself, so that wavefronts see it differently and part of a workgroup leaves.  There that is
+// harmless: what the others count or write lies in range, and every kernel behind them sees the flag and uses none of it.
 __device__ __forceinline__ int32_t flag_ahead(const int32_t *err) { return *(volatile const int32_t *)err; }
 
 // One thread's look at the flag, for the whole workgroup: what stands in `word` (in LDS) after the next barrier holds for all.
