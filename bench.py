@@ -31,9 +31,9 @@ HBM_PEAK_GBS = 8000.0     # MI355X HBM3E, published
 # HBM bytes per launch of the SGD kernel from rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE (scaled by what the same
 # counters read for a plain 1 GiB copy; summaries under profiles/).  Only valid for the kernel sources they were
 # taken with and for the default settings of the workload: bytes read, bytes written.
-KERNEL_SOURCES = ("mf_sgd_chunk.hip", "mf_sgd.hip", "mf_device.h", "common.h", "sgd_touch.h", "together.h")
-TRAFFIC = {"kernel_sha256_16": "72c9e4fef8fe7df8",
-           "bytes_per_launch": {"large": (183543268.0, 125100302.2), "wide": (1269322835.0, 952084510.5)}}
+KERNEL_SOURCES = ("mf_sgd_chunk.hip", "mf_sgd.hip", "mf_device.h", "common.h", "factor_offsets.h", "sgd_touch.h", "together.h")
+TRAFFIC = {"kernel_sha256_16": "fe4885762f4185c0",
+           "bytes_per_launch": {"large": (183590739.5, 125021433.5), "wide": (1269303035.0, 952084497.9)}}
 
 # block boundaries per workload: a column of a block weighs this many entries on top of its own (see --col-cost)
 COL_COST = {"wide": 3.0}
