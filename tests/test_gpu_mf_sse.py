@@ -33,7 +33,7 @@ def test_train_sse_sums_in_double(rank):
         assert abs(got - want) <= 2 * bound, (got, want, bound)
 
 
-@pytest.mark.parametrize("nnz", [2047, 2048, 2049, 4097, 131071, 131072, 131073, 700001])
+@pytest.mark.parametrize("nnz", [2047, 2048, 2049, 4097, 131071, 131072, 131073, 524288, 524289, 700001])
 def test_train_sse_at_numbers_of_workgroups(nnz):
     """Entry counts at which the launch gets more workgroups, and the most it gets; the bound as above."""
     import torch
